@@ -5,7 +5,12 @@
 // observables the solver produces; the solver generates its training data and
 // measures its error (paper_2307_07999_amd/surrogate.py).
 //
-// Dense products use v_mfma_f32_16x16x16_bf16: a 64 x 64 output tile per
+// Networks whose layers fit one workgroup (mlp_fused: up to 256 wide, at most
+// four hidden layers; the surrogate's is 5 -> 256 x 3 -> 2) run in the
+// whole-network kernels of mlp_rows.hpp.  Wider or deeper ones run layer by
+// layer with the general kernels here.
+//
+// Their dense products use v_mfma_f32_16x16x16_bf16: a 64 x 64 output tile per
 // 256-thread workgroup, each wave a 32 x 32 quarter as 2 x 2 MFMA blocks,
 // operands staged through LDS in 16-deep K slices.  Operand layout of one
 // 16x16x16 MFMA for lane l: A row l%16, k = 4(l/16)..+3; B column l%16,
@@ -21,21 +26,9 @@
 #include <vector>
 
 #include "../../include/glasma.h"
+#include "mlp_rows.hpp"
 
 namespace {
-
-typedef float floatx4 __attribute__((ext_vector_type(4)));
-typedef short bf16x4 __attribute__((ext_vector_type(4)));
-typedef uint16_t bf16;
-
-__device__ __forceinline__ float bf2f(bf16 h) { return __uint_as_float((uint32_t)h << 16); }
-
-// round to nearest even
-__device__ __forceinline__ bf16 f2bf(float f) {
-    uint32_t u = __float_as_uint(f);
-    u += 0x7FFFu + ((u >> 16) & 1u);
-    return (bf16)(u >> 16);
-}
 
 constexpr int BM = 64, BN = 64, BK = 16;
 
@@ -124,10 +117,7 @@ k_prep(const float *__restrict__ X, const float *__restrict__ Y, const int32_t *
     int r = blockIdx.x * 256 + threadIdx.x;
     if (r >= B) return;
     int64_t s = idx ? idx[off + r] : off + r;
-    for (int c = 0; c < nin; c++) {
-        float lo = sc[c], hi = sc[nin + c];
-        Xb[(size_t)r * nin + c] = f2bf(2.f * (X[s * nin + c] - lo) / (hi - lo) - 1.f);
-    }
+    for (int c = 0; c < nin; c++) Xb[(size_t)r * nin + c] = scaled_input(X[s * nin + c], sc, nin, c);
     if (Y)
         for (int c = 0; c < nout; c++) {
             float mu = sc[2 * nin + c], sd = sc[2 * nin + nout + c];
@@ -258,6 +248,13 @@ struct gl_mlp {
     std::vector<bf16 *> Hb;                     // BF16 activations per layer
     float *dZ, *dH;                             // FP32 scratch [max_batch][width_max]
     bf16 *dZb;
+    // whole-network kernels (mlp_rows.hpp): the network, and a step's buffers
+    // in place of the layer-by-layer ones (Wb, Xb, Yb, Z, Hb, dZb)
+    bool fused;
+    NetView v;
+    bf16 *Hf, *Df;
+    float *Dz, *dev;
+    int max_tiles;                              // row tiles of 16 of a batch
     float *loss;                                // 1 float
     int32_t *perm;                              // [max_samples]
     int64_t max_samples;
@@ -276,6 +273,28 @@ namespace {
 struct MlpSizes {
     size_t total;
 };
+
+// the networks the whole-network kernels take: hidden layers of at most
+// kRowWidth (a wave's weights of one layer are its registers), inputs and
+// outputs within one fragment row of that width, and pre-activations of all
+// layers in registers during training
+bool mlp_fused(const gl_mlp_desc &d) {
+    return d.width <= kRowWidth && d.n_in <= kRowWidth && d.n_out <= kRowWidth && d.depth <= kRowMaxDepth;
+}
+
+NetView net_view(const gl_mlp_desc &d, int64_t n_w) {
+    NetView v{};
+    v.n_in = d.n_in;
+    v.width = d.width;
+    v.depth = d.depth;
+    v.n_out = d.n_out;
+    v.kp_in = (d.n_in + 31) / 32;
+    v.ot_out = (d.n_out + 15) / 16;
+    v.kp_out = (d.n_out + 31) / 32;
+    v.pcol = -1;
+    v.n_w = n_w;
+    return v;
+}
 
 gl_status mlp_layout(const gl_mlp_desc *d, int64_t max_samples, gl_mlp *m, size_t *total) {
     if (!d || d->n_in < 1 || d->n_out < 1 || d->width < 1 || d->depth < 1 || d->max_batch < 1)
@@ -306,14 +325,32 @@ gl_status mlp_layout(const gl_mlp_desc *d, int64_t max_samples, gl_mlp *m, size_
         off = al(off + b);
         return o;
     };
-    size_t oP = take(np * 4), oG = take(np * 4), oM = take(np * 4), oV = take(np * 4), oW = take(nw * 2);
-    size_t osc = take((2 * d->n_in + 3 * d->n_out) * 4), oX = take(B * d->n_in * 2), oY = take(B * d->n_out * 4);
+    const bool fused = mlp_fused(*d);
+    const NetView v = net_view(*d, nw);
+    const int64_t tiles = (B + 15) / 16;
+    size_t oP = take(np * 4), oG = take(np * 4), oM = take(np * 4), oV = take(np * 4);
+    size_t osc = take((2 * d->n_in + 3 * d->n_out) * 4);
+    size_t odZ = take(B * wmax * 4), odH = take(B * wmax * 4), oloss = take(4);
+    size_t oW = 0, oX = 0, oY = 0, odZb = 0, oWf = 0, oWt = 0, oHf = 0, oDf = 0, oDz = 0, odev = 0;
     std::vector<size_t> oZ(L), oH(L);
-    for (int l = 0; l < L; l++) {
-        oZ[l] = take(B * dout[l] * 4);
-        oH[l] = take(B * dout[l] * 2);
+    if (fused) {
+        oWf = take(frag_elems(v) * 2);
+        oWt = take(frag_elems_t(v) * 2);
+        oHf = take(h_off(v, L, (int)tiles) * 2);
+        const size_t dz = d_off(v, d->depth, (int)tiles) + (size_t)tiles * kGradBlock * v.ot_out;
+        oDf = take(dz * 2);
+        oDz = take(dz * 4);
+        odev = take((size_t)B * d->n_out * 4);
+    } else {
+        oW = take(nw * 2);
+        oX = take(B * d->n_in * 2);
+        oY = take(B * d->n_out * 4);
+        for (int l = 0; l < L; l++) {
+            oZ[l] = take(B * dout[l] * 4);
+            oH[l] = take(B * dout[l] * 2);
+        }
+        odZb = take(B * wmax * 2);
     }
-    size_t odZ = take(B * wmax * 4), odH = take(B * wmax * 4), odZb = take(B * wmax * 2), oloss = take(4);
     size_t operm = take(std::max<int64_t>(1, max_samples) * 4);
     *total = off;
     if (m) {
@@ -343,6 +380,17 @@ gl_status mlp_layout(const gl_mlp_desc *d, int64_t max_samples, gl_mlp *m, size_
         m->dZ = (float *)(w + odZ);
         m->dH = (float *)(w + odH);
         m->dZb = (bf16 *)(w + odZb);
+        m->fused = fused;
+        m->v = v;
+        m->v.P = m->P;
+        m->v.sc = m->sc;
+        m->v.Wf = (bf16 *)(w + oWf);
+        m->v.Wt = (bf16 *)(w + oWt);
+        m->Hf = (bf16 *)(w + oHf);
+        m->Df = (bf16 *)(w + oDf);
+        m->Dz = (float *)(w + oDz);
+        m->dev = (float *)(w + odev);
+        m->max_tiles = (int)tiles;
         m->loss = (float *)(w + oloss);
         m->perm = (int32_t *)(w + operm);
         m->max_samples = max_samples;
@@ -398,7 +446,57 @@ gl_status backward(gl_mlp *m, int B) {
 }
 
 gl_status sync_weights(gl_mlp *m) {
+    if (m->fused) {
+        hipLaunchKernelGGL(k_put_weights, dim3(nb(m->n_w, 256)), dim3(256), 0, m->st, m->v);
+        MHIP(hipGetLastError());
+        return GL_OK;
+    }
     hipLaunchKernelGGL(k_to_bf16, dim3(nb(m->n_w, 256)), dim3(256), 0, m->st, m->P, m->n_w, m->Wb);
+    MHIP(hipGetLastError());
+    return GL_OK;
+}
+
+// rows per workgroup of the whole-network inference: 64 once that many fill
+// the chip's workgroup slots (two a compute unit), else 32 or 16
+template <int RT>
+void launch_rows(gl_mlp *m, const float *X, float *Y, int64_t n) {
+    hipLaunchKernelGGL((k_rows_infer<RT, RT == 1>), dim3(nb(n, 16 * RT)), dim3(kRowThreads),
+                       (m->v.depth + 1) * kRowWidth * sizeof(float), m->st, m->v, X, n, Y);
+}
+gl_status infer_rows(gl_mlp *m, const float *X, float *Y, int64_t n) {
+    constexpr int64_t kPass = (int64_t)1 << 30;   // rows of one launch
+    for (int64_t r0 = 0; r0 < n; r0 += kPass) {
+        const int64_t b = std::min(kPass, n - r0);
+        const float *x = X + r0 * m->d.n_in;
+        float *y = Y + r0 * m->d.n_out;
+        if (b >= 32768) launch_rows<4>(m, x, y, b);
+        else if (b > 4096) launch_rows<2>(m, x, y, b);
+        else launch_rows<1>(m, x, y, b);
+        MHIP(hipGetLastError());
+    }
+    return GL_OK;
+}
+
+// one pass of the whole-network training kernels over B rows (sample idx[off + r],
+// or off + r without idx): the loss is added to m->loss and the update done
+// (adam), or the gradients left in G (adam null)
+gl_status step_rows(gl_mlp *m, const float *X, const float *Y, const int32_t *idx, int64_t off, int B,
+                    const AdamArgs *adam) {
+    const NetView &v = m->v;
+    const int tiles = (B + 15) / 16;
+    const float scale = 1.f / (float)(B * v.n_out);
+    const TrainView a{X, Y, idx, off, B, scale, m->max_tiles, m->Hf, m->Df, m->Dz, m->dev};
+    switch (v.depth) {
+        case 1: hipLaunchKernelGGL(k_rows_train<1>, dim3(tiles), dim3(kRowThreads), 0, m->st, v, a); break;
+        case 2: hipLaunchKernelGGL(k_rows_train<2>, dim3(tiles), dim3(kRowThreads), 0, m->st, v, a); break;
+        case 3: hipLaunchKernelGGL(k_rows_train<3>, dim3(tiles), dim3(kRowThreads), 0, m->st, v, a); break;
+        default: hipLaunchKernelGGL(k_rows_train<4>, dim3(tiles), dim3(kRowThreads), 0, m->st, v, a); break;
+    }
+    MHIP(hipGetLastError());
+    int wgs = bias_groups(v) + 1;
+    for (int l = 0; l <= v.depth; l++) wgs += weight_groups(v, l);
+    hipLaunchKernelGGL(k_update, dim3(wgs), dim3(256), 0, m->st, v, a, m->P, m->Mo, m->Vo, adam ? nullptr : m->G,
+                       m->loss, tiles, adam ? *adam : AdamArgs{});
     MHIP(hipGetLastError());
     return GL_OK;
 }
@@ -454,6 +552,10 @@ gl_status gl_mlp_create(const gl_mlp_desc *d, int64_t max_samples, void *ws, siz
         hipMemsetAsync(m->Mo, 0, m->n_params * 4, m->st) != hipSuccess ||
         hipMemsetAsync(m->Vo, 0, m->n_params * 4, m->st) != hipSuccess)
         return bad("upload failed");
+    // the padding of the weight fragments stays zero
+    if (m->fused && (hipMemsetAsync(m->v.Wf, 0, frag_elems(m->v) * 2, m->st) != hipSuccess ||
+                     hipMemsetAsync(m->v.Wt, 0, frag_elems_t(m->v) * 2, m->st) != hipSuccess))
+        return bad("clearing the weight fragments failed");
     if (sync_weights(m) || hipStreamSynchronize(m->st) != hipSuccess) return bad("init failed");
     *out = m;
     return GL_OK;
@@ -484,7 +586,7 @@ gl_status gl_mlp_set_scaling(gl_mlp *m, const float *in_lo, const float *in_hi, 
 gl_status gl_mlp_set_output_power(gl_mlp *m, int32_t col, const float *powers) {
     if (!m) return mfail(GL_EINVAL, "null argument");
     if (col >= m->d.n_in || (col >= 0 && !powers)) return mfail(GL_EINVAL, "bad column or powers");
-    m->pcol = col < 0 ? -1 : col;
+    m->pcol = m->v.pcol = col < 0 ? -1 : col;
     if (col >= 0) {
         MHIP(hipMemcpyAsync(m->sc + 2 * m->d.n_in + 2 * m->d.n_out, powers, m->d.n_out * 4, hipMemcpyHostToDevice,
                             m->st));
@@ -499,16 +601,29 @@ gl_status gl_mlp_train(gl_mlp *m, const float *X, const float *Y, int64_t n, int
     if (n < 1 || n > m->max_samples || batch < 1 || batch > m->d.max_batch || epochs < 0)
         return mfail(GL_EINVAL, "bad sizes (n <= max_samples, batch <= max_batch)");
     std::mt19937_64 rng(seed);
-    std::vector<int32_t> perm(n);
+    // the shuffle of an epoch and, made while the device runs that epoch, the next one's
+    std::vector<int32_t> perm(n), next(n);
+    auto shuffle = [&](std::vector<int32_t> &p) {
+        for (int64_t i = 0; i < n; i++) p[i] = (int32_t)i;
+        for (int64_t i = n - 1; i > 0; i--) std::swap(p[i], p[(int64_t)(rng() % (uint64_t)(i + 1))]);
+    };
     const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
     const int64_t nbat = n / batch;   // whole batches only
     if (nbat < 1) return mfail(GL_EINVAL, "fewer samples than one batch");
+    if (epochs > 0) shuffle(next);
     for (int ep = 0; ep < epochs; ep++) {
-        for (int64_t i = 0; i < n; i++) perm[i] = (int32_t)i;
-        for (int64_t i = n - 1; i > 0; i--) std::swap(perm[i], perm[(int64_t)(rng() % (uint64_t)(i + 1))]);
+        perm.swap(next);
         MHIP(hipMemcpyAsync(m->perm, perm.data(), n * 4, hipMemcpyHostToDevice, m->st));
         hipLaunchKernelGGL(k_zero1, dim3(1), dim3(64), 0, m->st, m->loss);
+        MHIP(hipGetLastError());
         for (int64_t bi = 0; bi < nbat; bi++) {
+            m->adam_t++;
+            float c1 = 1.f - std::pow(b1, (float)m->adam_t), c2 = 1.f - std::pow(b2, (float)m->adam_t);
+            if (m->fused) {
+                const AdamArgs aa{lr, b1, b2, c1, c2, eps};
+                if (gl_status s = step_rows(m, X, Y, m->perm, bi * batch, batch, &aa)) return s;
+                continue;
+            }
             hipLaunchKernelGGL(k_prep, dim3(nb(batch, 256)), dim3(256), 0, m->st, X, Y, m->perm, bi * batch, batch,
                                m->d.n_in, m->d.n_out, m->sc, m->pcol, m->Xb, m->Yb);
             MHIP(hipGetLastError());
@@ -516,14 +631,13 @@ gl_status gl_mlp_train(gl_mlp *m, const float *X, const float *Y, int64_t n, int
             if (s) return s;
             s = backward(m, batch);
             if (s) return s;
-            m->adam_t++;
-            float c1 = 1.f - std::pow(b1, (float)m->adam_t), c2 = 1.f - std::pow(b2, (float)m->adam_t);
             hipLaunchKernelGGL(k_adam, dim3(nb(m->n_params, 256)), dim3(256), 0, m->st, m->P, m->G, m->Mo, m->Vo,
                                m->n_params, lr, b1, b2, c1, c2, eps);
             MHIP(hipGetLastError());
             s = sync_weights(m);
             if (s) return s;
         }
+        if (ep + 1 < epochs) shuffle(next);
         if (loss_per_epoch) {
             float l = 0;
             MHIP(hipMemcpyAsync(&l, m->loss, 4, hipMemcpyDeviceToHost, m->st));
@@ -538,6 +652,7 @@ gl_status gl_mlp_train(gl_mlp *m, const float *X, const float *Y, int64_t n, int
 gl_status gl_mlp_infer(gl_mlp *m, const float *X, float *Y, int64_t n) {
     if (!m || !X || !Y) return mfail(GL_EINVAL, "null argument");
     if (n < 0) return mfail(GL_EINVAL, "n must be >= 0");
+    if (m->fused) return infer_rows(m, X, Y, n);
     const int B = m->d.max_batch;
     for (int64_t off = 0; off < n; off += B) {
         int b = (int)std::min<int64_t>(B, n - off);
@@ -617,6 +732,7 @@ gl_status gl_mlp_infer_noalloc(gl_mlp *m, const float *X, float *Y, int64_t n) {
     hipDevice_t sdev = dev;
     if (m->st) MHIP(hipStreamGetDevice(m->st, &sdev));
     if (sdev != dev) return mfail(GL_EINVAL, "the device of the model's stream is not the current device");
+    if (m->fused) return infer_rows(m, X, Y, n);   // needs no scratch
     void *base = nullptr;
     if (gl_status s = infer_scratch_address(dev, &base)) return s;
     char *sp = (char *)base;
@@ -729,13 +845,18 @@ gl_status gl_mlp_grads(gl_mlp *m, const float *X, const float *Y, int32_t n, flo
     if (!m || !X || !Y || !grads) return mfail(GL_EINVAL, "null argument");
     if (n < 1 || n > m->d.max_batch) return mfail(GL_EINVAL, "n must be in [1, max_batch]");
     hipLaunchKernelGGL(k_zero1, dim3(1), dim3(64), 0, m->st, m->loss);
-    hipLaunchKernelGGL(k_prep, dim3(nb(n, 256)), dim3(256), 0, m->st, X, Y, (const int32_t *)nullptr, (int64_t)0, n,
-                       m->d.n_in, m->d.n_out, m->sc, m->pcol, m->Xb, m->Yb);
     MHIP(hipGetLastError());
-    gl_status s = forward(m, n);
-    if (s) return s;
-    s = backward(m, n);
-    if (s) return s;
+    if (m->fused) {
+        if (gl_status s = step_rows(m, X, Y, nullptr, 0, n, nullptr)) return s;
+    } else {
+        hipLaunchKernelGGL(k_prep, dim3(nb(n, 256)), dim3(256), 0, m->st, X, Y, (const int32_t *)nullptr, (int64_t)0,
+                           n, m->d.n_in, m->d.n_out, m->sc, m->pcol, m->Xb, m->Yb);
+        MHIP(hipGetLastError());
+        gl_status s = forward(m, n);
+        if (s) return s;
+        s = backward(m, n);
+        if (s) return s;
+    }
     MHIP(hipMemcpyAsync(grads, m->G, m->n_params * 4, hipMemcpyDeviceToHost, m->st));
     if (loss) MHIP(hipMemcpyAsync(loss, m->loss, 4, hipMemcpyDeviceToHost, m->st));
     MHIP(hipStreamSynchronize(m->st));

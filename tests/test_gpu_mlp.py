@@ -125,3 +125,46 @@ def test_forward_and_gradients_match_oracle_elementwise(gl):
     u = 2.0 ** -8
     assert rf.max() < u
     assert rg.max() < u
+
+
+@pytest.mark.parametrize("shape,n", [((1, 1, 1, 1), 1), ((5, 16, 1, 2), 15), ((5, 17, 2, 16), 16), ((33, 48, 3, 17), 17),
+                                     ((256, 255, 2, 40), 300), ((7, 256, 4, 256), 33), ((5, 256, 3, 2), 257)])
+def test_whole_network_kernels_at_their_edges(gl, shape, n):
+    """Networks up to 256 wide and four hidden layers run in whole-network
+    kernels of 16-row tiles and 16-output blocks: widths, depths, inputs,
+    outputs and rows around those sizes, every output and gradient element
+    within the BF16 bound derived above."""
+    g = np.random.default_rng(sum(shape) + n)
+    net = gl.MLP(*shape, max_batch=n + 3, max_samples=8, seed=5)
+    p = net.params()
+    nb = shape[1] * shape[2] + shape[3]
+    p[-nb:] = g.uniform(-0.2, 0.2, nb).astype(np.float32)     # biases too
+    net.params(set_to=p)
+    lo, hi = -np.ones(shape[0], np.float32), np.full(shape[0], 2.0, np.float32)
+    net.set_scaling(lo, hi, np.full(shape[3], 0.25), np.full(shape[3], 0.5))
+    X = g.uniform(-1, 2, (n, shape[0])).astype(np.float32)
+    Y = g.uniform(-1, 1, (n, shape[3])).astype(np.float32)
+    Xs, Ys = M.scale_inputs(X, lo, hi), (Y - 0.25) / 0.5
+    p = p.astype(np.float64)
+    got = net.infer(X).cpu().numpy()
+    Zs, _ = M.forward(p, Xs, shape, bf16=True)
+    rf = np.abs(got - (Zs[-1] * 0.5 + 0.25)) / (M.output_scales(p, Xs, shape, bf16=True) * 0.5 + 1e-30)
+    gr, loss = net.grads(X, Y)
+    lo_, go = M.loss_and_grads(p, Xs, Ys, shape, bf16=True)
+    rg = np.abs(gr - go) / (M.grad_scales(p, Xs, Ys, shape, bf16=True) + 1e-30)
+    print("shape %s n %d: forward %.1e, gradients %.1e of the scale" % (shape, n, rf.max(), rg.max()))
+    assert rf.max() < 2.0 ** -8 and rg.max() < 2.0 ** -8
+    assert abs(loss - lo_) < 2.0 ** -8 * lo_
+
+
+def test_inference_does_not_depend_on_the_rows_of_a_call(gl):
+    """The rows of a workgroup grow with the rows of a call (16, 32, 64): each
+    row's outputs are bitwise the same in a call of its own size class."""
+    import torch
+    net = gl.MLP(*SHAPE, max_batch=64, max_samples=8, seed=6)
+    net.set_scaling(LO, HI, MU, SD)
+    net.set_output_power(0, [3.0, 2.0])
+    X = torch.from_numpy(_data(33000, 7)[0].astype(np.float32)).cuda()
+    small = torch.cat([net.infer(x.contiguous()) for x in X.split(3001)])
+    for n in (33000, 32767, 4097, 4096):
+        assert torch.equal(net.infer(X[:n].contiguous()), small[:n])
