@@ -105,7 +105,7 @@ gl_status make_layout(const gl_lattice_desc *d, Layout &L) {
     L.diag = take(std::max(L.n_diag_blocks * 8, 2 * cas_blocks) * sizeof(double));
     L.VA = take(18 * n2 * sizeof(double));
     L.VB = take(18 * n2 * sizeof(double));
-    L.planes = take((size_t)kSheetChunk * 4 * n2 * sizeof(double2));
+    L.planes = take((size_t)sheet_chunk(n2) * 4 * n2 * sizeof(double2));
     L.fft_tab = take(kFftTableBytes);
     L.U0 = take(36 * n2 * sizeof(double));
     L.pi0 = take(8 * n2 * sizeof(double));
@@ -927,24 +927,21 @@ static gl_status wilson_lines(gl_event *ev, int n_sheets, double m_ir_GeV, doubl
     double2 *planes = (double2 *)(ev->ws + ev->L.planes);
     double2 *tab = (double2 *)(ev->ws + ev->L.fft_tab);
     HIP_TRY(launch_fft_tables(ev->stream, N, tab));
-    for (int nuc = 0; nuc < 2; nuc++) {
-        HIP_TRY(launch_wilson_init(ev->stream, N, V[nuc]));
-        for (int sh0 = 0; sh0 < n_sheets; sh0 += kSheetChunk) {
-            const int cnt = std::min(kSheetChunk, n_sheets - sh0);
-            if (rho_dev) {
-                for (int k = 0; k < cnt; k++)
-                    HIP_TRY(launch_charges_to_planes(
-                        ev->stream, N, rho_dev + ((size_t)nuc * n_sheets + sh0 + k) * 8 * ev->n2,
-                        planes + (size_t)k * 4 * ev->n2));
-                HIP_TRY(launch_poisson(ev->stream, N, m2, uv2, planes, cnt, tab));
-            } else {
-                // the forward row pass draws the charges itself
-                const MvDraw mv{sigma, seed, nuc, sh0};
-                HIP_TRY(launch_poisson(ev->stream, N, m2, uv2, planes, cnt, tab, &mv));
-            }
-            HIP_TRY(launch_wilson_accum(ev->stream, N, planes, cnt, V[nuc]));
+    // both nuclei together where a launch holds the sheets of more than one
+    // chunk of the paper's lattice (their chains of products are independent)
+    const int chunk = sheet_chunk(ev->n2), nn = chunk >= 2 * kSheetChunkMin ? 2 : 1, per = chunk / nn;
+    for (int nuc = 0; nuc < 2; nuc += nn)
+        for (int sh0 = 0; sh0 < n_sheets; sh0 += per) {
+            const int cnt = std::min(per, n_sheets - sh0);
+            const MvDraw mv{sigma, seed, nuc, sh0, cnt};
+            for (int k = 0; rho_dev && k < nn; k++)
+                HIP_TRY(launch_charges_to_planes(ev->stream, N,
+                                                 rho_dev + ((size_t)(nuc + k) * n_sheets + sh0) * 8 * ev->n2, cnt,
+                                                 planes + (size_t)k * cnt * 4 * ev->n2));
+            // without given charges the forward row pass draws them itself
+            HIP_TRY(launch_poisson(ev->stream, N, m2, uv2, planes, 4 * cnt * nn, tab, rho_dev ? nullptr : &mv));
+            HIP_TRY(launch_wilson_accum(ev->stream, N, planes, cnt, sh0 == 0, nn, V[nuc], V[1]));
         }
-    }
     return GL_OK;
 }
 
@@ -959,11 +956,11 @@ static gl_status init_common(gl_event *ev, int n_sheets, double m_ir_GeV, double
 // kernels; partials in the initialisation scratch planes)
 static gl_status dipole_curve(gl_event *ev, int nucleus, int rmax, std::vector<double> &D) {
     const double *V = (const double *)(ev->ws + (nucleus == 0 ? ev->L.VA : ev->L.VB));
-    double *part = (double *)(ev->ws + ev->L.planes);
-    const int nb = (int)((ev->n2 + 255) / 256);
-    double *Dd = part + (size_t)(rmax + 1) * nb;
-    HIP_TRY(launch_dipole(ev->stream, ev->N, V, rmax, part, Dd));
-    D.assign(rmax + 1, 0.0);
+    // a lattice without an MV initialisation has no Wilson lines
+    D.assign(rmax + 1, std::nan(""));
+    if (!valid_N_for_fft(ev->N)) return GL_OK;
+    double *scratch = (double *)(ev->ws + ev->L.planes), *Dd = scratch + dipole_scratch(ev->N);
+    HIP_TRY(launch_dipole(ev->stream, ev->N, V, rmax, (const double2 *)(ev->ws + ev->L.fft_tab), scratch, Dd));
     HIP_TRY(hipMemcpyAsync(D.data(), Dd, (rmax + 1) * sizeof(double), hipMemcpyDeviceToHost, ev->stream));
     HIP_TRY(hipStreamSynchronize(ev->stream));
     return GL_OK;

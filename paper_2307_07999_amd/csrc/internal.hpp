@@ -177,29 +177,42 @@ hipError_t launch_check_finite(hipStream_t st, const T *a, int64_t n, int64_t va
                                int *first_bad);
 
 // initial conditions (always FP64 internally)
-constexpr int kSheetChunk = 8;   // MV sheets per initialisation launch
-// the MV charges of one nucleus drawn for sheets sheet0.. (seeded, counter
-// based): colours 2j, 2j + 1 of sheet s at site x from one draw
+// MV sheets per initialisation launch: eight at 512^2, whose planes (134 MB)
+// stay in the last-level cache between the passes, and on smaller lattices as
+// many as keep to that size (at most 64), so that each launch fills the chip
+constexpr int kSheetChunkMin = 8, kSheetChunkMax = 64;
+inline int sheet_chunk(size_t n2) {
+    const size_t c = ((size_t)kSheetChunkMin << 18) / n2;
+    return c < kSheetChunkMin ? kSheetChunkMin : c > kSheetChunkMax ? kSheetChunkMax : (int)c;
+}
+// the MV charges drawn for `sheets` sheets from sheet0 of each nucleus from
+// `nucleus` (seeded, counter based): colours 2j, 2j + 1 of sheet s at site x
+// from one draw
 struct MvDraw {
     double sigma;
     uint64_t seed;
     int nucleus;
     int sheet0;
+    int sheets;
 };
 hipError_t launch_mv_charges(hipStream_t st, int N, double sigma, uint64_t seed, int nucleus,
                              int sheet0, int n_sheets, double2 *planes /* [n_sheets][4][n2] */);
-hipError_t launch_charges_to_planes(hipStream_t st, int N, const double *rho /* [8][n2] */,
-                                 double2 *planes);
+hipError_t launch_charges_to_planes(hipStream_t st, int N, const double *rho /* [n_sheets][8][n2] */, int n_sheets,
+                                    double2 *planes);
 hipError_t launch_planes_to_charges(hipStream_t st, int N, const double2 *planes, double *rho);
 // the twiddle and sin^2 tables of one solve size into tab (kFftTableBytes)
 constexpr size_t kFftTableBytes = 1024 * (sizeof(double2) + sizeof(double));
 hipError_t launch_fft_tables(hipStream_t st, int N, double2 *tab);
-hipError_t launch_poisson(hipStream_t st, int N, double m2, double uv2, double2 *planes, int n_sheets,
+hipError_t launch_poisson(hipStream_t st, int N, double m2, double uv2, double2 *planes, int n_planes,
                           const double2 *tab, const MvDraw *draw = nullptr);
 hipError_t launch_wilson_init(hipStream_t st, int N, double *V);
-// dipole correlator D[0..rmax] of a Wilson line; partials [(rmax+1)][ceil(N^2/256)]
-hipError_t launch_dipole(hipStream_t st, int N, const double *V, int rmax, double *partials, double *D);
-hipError_t launch_wilson_accum(hipStream_t st, int N, const double2 *planes, int n_sheets, double *V);
+// dipole correlator D[0..rmax] of a Wilson line; tab the tables of launch_fft_tables,
+// dipole_scratch(N) doubles of scratch
+size_t dipole_scratch(int N);
+hipError_t launch_dipole(hipStream_t st, int N, const double *V, int rmax, const double2 *tab, double *scratch,
+                         double *D);
+hipError_t launch_wilson_accum(hipStream_t st, int N, const double2 *planes /* [n_nuclei][n_sheets][4][n2] */,
+                               int n_sheets, bool first, int n_nuclei, double *V0, double *V1);
 hipError_t launch_match_pi0(hipStream_t st, int N, const double *VA, const double *VB,
                            double *U0 /* [2][18][n2] FP64 */, double *pi0 /* [8][n2] */,
                            int *status, int max_iter, double tol);
