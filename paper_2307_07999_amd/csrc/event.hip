@@ -45,12 +45,26 @@ inline size_t partial_slot_stride(int64_t slots) {
 }
 
 struct Layout {
-    size_t field[2], F, part[2], id[2], sort_keys[2], sort_vals[2], sort_counts, sort_totals, partials,
+    size_t field[3], F[2], part[2], id[2], sort_keys[2], sort_vals[2], sort_counts, sort_totals, partials,
         series, p0sum, diag, VA, VB, planes, fft_tab, U0, pi0, status, stat, stat_part, stat_series, ll, ll_part,
         ll_series, total;
     int64_t slots;         // particle capacity in slots (padding included)
     size_t n_diag_blocks;  // workgroups of the diagnostics kernel
 };
+
+// Lattices that run each field step beside the push before it (pair.hip): those
+// whose three field states and two site-field records fit the last-level
+// cache.  Beyond it the two kernels evict what the other is about to read
+// (FP64 288^2 12.9 -> 11.3 ms, but 324^2 15.5 -> 16.1 and 384^2 19.2 -> 22.8;
+// FP32 288^2 8.6 -> 7.2, 384^2 11.6 -> 10.9).
+constexpr size_t kPairBytes = (size_t)200 << 20;
+bool pair_lattice(size_t n2, size_t ts) { return (3 * kStateVals + 2 * (size_t)kSiteRec) * ts * n2 <= kPairBytes; }
+// A push beside a field step has its waves a SIMD (two in FP64, four in FP32)
+// instead of its own three and six, which pays while it is at most two rounds of
+// workgroups on the chip's 256 compute units (FP64 128^2: 171 and 684 push
+// blocks 5.8 -> 5.0 and 7.6 -> 7.1 ms, 2734 15.3 -> 15.2; 256^2: 2734 17.9 -> 18.9.
+// FP32 256^2: 684 and 2734 7.5 -> 6.3 and 11.5 -> 10.5, 10937 29.2 -> 33.3).
+constexpr int64_t pair_blocks(bool fp64) { return 2 * 256 * (fp64 ? 2 : 4); }
 
 bool valid_N_for_fft(int N) {
     int m = N;
@@ -88,8 +102,11 @@ gl_status make_layout(const gl_lattice_desc *d, Layout &L) {
         off = align256(off + bytes);
         return o;
     };
-    for (int b = 0; b < 2; b++) L.field[b] = take(kStateVals * n2 * ts);
-    L.F = take((size_t)kSiteRec * n2 * ts);
+    // a third state and a second site-field record where a step may run beside
+    // the push before it (run_paired)
+    const bool paired = L.slots > 0 && pair_lattice(n2, ts);
+    for (int b = 0; b < 3; b++) L.field[b] = b < 2 || paired ? take(kStateVals * n2 * ts) : 0;
+    for (int b = 0; b < 2; b++) L.F[b] = b < 1 || paired ? take((size_t)kSiteRec * n2 * ts) : 0;
     for (int b = 0; b < 2; b++) L.part[b] = take((size_t)L.slots * ((part_rec(ts) + 3) * ts + 12));
     for (int b = 0; b < 2; b++) L.id[b] = take((size_t)L.slots * sizeof(int32_t));
     for (int b = 0; b < 2; b++) L.sort_keys[b] = take((size_t)L.slots * sizeof(uint32_t));
@@ -141,7 +158,9 @@ struct gl_event {
     double a_fm, a_gev, dtau;   // dtau in lattice units
     hipStream_t stream;
     char *ws;
-    int cur = 0;
+    int cur = 0;                // current field state (0 or 1), the other holds the one before
+    int fmap[3] = {0, 1, 2};    // buffers of states 0 and 1 and the spare one of run_paired
+    int fcur = 0;               // current site-field record
     int64_t n = 0;
     bool ready = false, push_due = false;
     int64_t rows = 0;           // series rows written
@@ -187,9 +206,12 @@ struct gl_event {
     std::vector<std::pair<int, size_t>> prof_marks;   // (class, index of start event)
 
     bool fp64() const { return desc.precision == 64; }
+    char *field_base(int b) const { return ws + L.field[fmap[b]]; }
+    template <typename T>
+    T *site_fields() const { return (T *)(ws + L.F[fcur]); }
     template <typename T>
     FieldPtrs<T> fields(int b) const {
-        T *base = (T *)(ws + L.field[b]);
+        T *base = (T *)field_base(b);
         return FieldPtrs<T>{base, base + 2 * kLinkVals * n2, base + (2 * kLinkVals + 16) * n2,
                             base + (2 * kLinkVals + 24) * n2};
     }
@@ -315,10 +337,10 @@ gl_status prof_end(gl_event *ev, size_t idx) {
         HIP_TRY(call);                                          \
     } while (0)
 
-// one field step n -> n+1; site fields F^n in the same pass when the event
-// has particles
+// one field step n -> n+1, with the site fields F^n in the same pass when the
+// event has particles; with p, the push of the step before in the same launch
 template <typename T>
-gl_status field_step(gl_event *ev, bool site_fields) {
+gl_status field_step(gl_event *ev, bool site_fields, const PushCall<T> *p = nullptr) {
     const int nxt = 1 - ev->cur;
     const double tau = ev->n * ev->dtau;
     int reunit = 0;
@@ -327,14 +349,23 @@ gl_status field_step(gl_event *ev, bool site_fields) {
         reunit = 1;
     const bool stat = ev->stat_on && ev->n >= ev->stat_n0 && ev->n - 1 < ev->desc.max_steps;
     const bool ll = ev->ll_on && ev->n >= ev->ll_n0 && ev->n - 1 < ev->desc.max_steps;
-    PROF_KERNEL(ev, 0, (launch_field_step<T>(ev->stream, ev->N, ev->fields<T>(ev->cur), ev->fields<T>(nxt),
-                                             site_fields || stat || ll ? (T *)(ev->ws + ev->L.F) : nullptr, tau,
-                                             ev->dtau, reunit, kt_)));
+    if (p) {
+        // the push reads state nxt and the current site fields: the step writes
+        // the spare ones, which take their place
+        std::swap(ev->fmap[nxt], ev->fmap[2]);
+        ev->fcur ^= 1;
+        HIP_TRY(launch_field_push<T>(ev->stream, ev->N, ev->fields<T>(ev->cur), ev->fields<T>(nxt),
+                                     ev->site_fields<T>(), tau, ev->dtau, reunit, *p));
+    } else {
+        PROF_KERNEL(ev, 0, (launch_field_step<T>(ev->stream, ev->N, ev->fields<T>(ev->cur), ev->fields<T>(nxt),
+                                                 site_fields || stat || ll ? ev->site_fields<T>() : nullptr, tau,
+                                                 ev->dtau, reunit, kt_)));
+    }
     if (stat) {
         // static quarks: accumulate the site fields at tau_n, series row n - 1 (time tau_{n+1/2})
         int nb = 0;
         double *part = (double *)(ev->ws + ev->L.stat_part);
-        PROF(ev, 1, (launch_static_accum<T>(ev->stream, ev->N, (const T *)(ev->ws + ev->L.F),
+        PROF(ev, 1, (launch_static_accum<T>(ev->stream, ev->N, ev->site_fields<T>(),
                                             (double *)(ev->ws + ev->L.stat), ev->dtau, part, &nb)));
         HIP_TRY(launch_series_reduce(ev->stream, part, nb, 1, ev->stat_series() + (ev->n - 1) * kMaxSpecies * 4,
                                      nullptr));
@@ -345,7 +376,7 @@ gl_status field_step(gl_event *ev, bool site_fields) {
         int nb = 0;
         double *part = (double *)(ev->ws + ev->L.ll_part);
         double *W = (double *)(ev->ws + ev->L.ll), *I = W + 18 * ev->n2;
-        PROF(ev, 1, (launch_lightlike_accum<T>(ev->stream, ev->N, (const T *)(ev->ws + ev->L.F),
+        PROF(ev, 1, (launch_lightlike_accum<T>(ev->stream, ev->N, ev->site_fields<T>(),
                                                ev->fields<T>(ev->cur).U, W, I, ev->n - ev->ll_n0, ev->dtau, part,
                                                &nb)));
         HIP_TRY(launch_series_reduce(ev->stream, part, nb, 1, ev->ll_series() + (ev->n - 1) * kMaxSpecies * 4,
@@ -368,27 +399,34 @@ gl_status flush_series(gl_event *ev) {
     return GL_OK;
 }
 
+// the push n-1 -> n that is due, as the event stands
 template <typename T>
-gl_status push(gl_event *ev) {
-    const int64_t n_prev = ev->n - 1;   // particles advance n_prev -> n
+PushCall<T> push_call(gl_event *ev) {
+    PushCall<T> p;
+    const int nb = 1 - ev->pbuf;
+    p.P = ev->parts<T>(ev->pbuf);
+    p.W = ev->parts<T>(ev->perm_pending ? nb : ev->pbuf);
+    p.perm = ev->perm_pending ? sort_perm(ev->scratch()) : nullptr;
+    p.id_src = ev->ids(ev->pbuf);
+    p.id_dst = ev->ids(nb);
+    p.n_slots = ev->slots_used;
+    p.f = ev->fields<T>(1 - ev->cur);
+    p.F = ev->site_fields<T>();
+    p.tab = ev->tab<T>();
+    p.n_species = (int)ev->species.size();
+    p.n = (int)(ev->n - 1);
+    p.dtau = (T)ev->dtau;
+    p.partials = ev->partials(ev->pend);
+    return p;
+}
+
+// what a launched push n_prev -> n_prev + 1 leaves: buffers moved, its partial
+// rows pending
+gl_status push_done(gl_event *ev, int64_t n_prev) {
     const int64_t row = n_prev - 1;
-    if (row >= ev->desc.max_steps) return fail(GL_EINVAL, "series capacity (max_steps) exhausted");
-    const int ns = (int)ev->species.size();
+    if (ev->perm_pending) ev->pbuf = 1 - ev->pbuf;
+    ev->perm_pending = false;
     if (ev->pend == 0) ev->pend_row0 = row;
-    if (ev->perm_pending) {
-        const int nb = 1 - ev->pbuf;
-        PROF_KERNEL(ev, 4, (launch_push_permuted<T>(ev->stream, ev->N, ev->parts<T>(ev->pbuf), ev->parts<T>(nb),
-                                                    sort_perm(ev->scratch()), ev->ids(ev->pbuf), ev->ids(nb),
-                                                    ev->slots_used, ev->fields<T>(1 - ev->cur),
-                                                    (const T *)(ev->ws + ev->L.F), ev->tab<T>(), ns, (int)n_prev,
-                                                    ev->dtau, ev->partials(ev->pend), kt_)));
-        ev->pbuf = nb;
-        ev->perm_pending = false;
-    } else {
-        PROF_KERNEL(ev, 2, (launch_push<T>(ev->stream, ev->N, ev->parts<T>(), ev->slots_used,
-                                           ev->fields<T>(1 - ev->cur), (const T *)(ev->ws + ev->L.F), ev->tab<T>(),
-                                           ns, (int)n_prev, ev->dtau, ev->partials(ev->pend), kt_)));
-    }
     ev->pend++;
     if (ev->pend == kReduceSlots) {
         gl_status s = flush_series(ev);
@@ -398,6 +436,15 @@ gl_status push(gl_event *ev) {
     ev->push_due = false;
     ev->since_sort++;
     return GL_OK;
+}
+
+template <typename T>
+gl_status push(gl_event *ev) {
+    const int64_t n_prev = ev->n - 1;   // particles advance n_prev -> n
+    if (n_prev - 1 >= ev->desc.max_steps) return fail(GL_EINVAL, "series capacity (max_steps) exhausted");
+    const PushCall<T> p = push_call<T>(ev);
+    PROF_KERNEL(ev, p.perm ? 4 : 2, (launch_push<T>(ev->stream, ev->N, p, kt_)));
+    return push_done(ev, n_prev);
 }
 
 template <typename T>
@@ -497,6 +544,37 @@ gl_status one_step(gl_event *ev, bool has_particles) {
     return do_push(ev, true);
 }
 
+// whether a run of this event pairs each field step with the push before it
+bool pairs(const gl_event *ev) {
+    return ev->slots_used > 0 && pair_lattice(ev->n2, ev->fp64() ? 8 : 4) &&
+           ev->slots_used / kPushBlock <= pair_blocks(ev->fp64());
+}
+
+gl_status due_sort(gl_event *ev, bool defer);
+
+// n_steps coupled steps, the push of each beside the field step of the next:
+// the launches of one_step with the same results, the last push alone
+template <typename T>
+gl_status run_paired_t(gl_event *ev, int32_t n_steps) {
+    gl_status s = field_step<T>(ev, true);
+    for (int32_t k = 1; k < n_steps && !s; k++) {
+        const PushCall<T> p = push_call<T>(ev);
+        const int64_t n_prev = ev->n - 1;
+        s = field_step<T>(ev, true, &p);
+        if (!s) s = push_done(ev, n_prev);
+        if (!s) s = due_sort(ev, true);
+    }
+    if (s) return s;
+    ev->push_due = true;
+    return do_push(ev, true);
+}
+
+gl_status run_paired(gl_event *ev, int32_t n_steps) {
+    const gl_status s = ev->fp64() ? run_paired_t<double>(ev, n_steps) : run_paired_t<float>(ev, n_steps);
+    if (s) ev->ready = false;   // the push lags the fields: not an event to continue
+    return s;
+}
+
 // the executable graphs of gl_run, after the stream has finished with them
 void free_graphs(gl_event *ev) {
     if (!ev->gexec[0] && !ev->gexec[1]) return;
@@ -578,7 +656,10 @@ gl_status do_push(gl_event *ev, bool defer = false) {
     gl_status s = settle_particles(ev);
     if (s) return s;
     s = ev->fp64() ? push<double>(ev) : push<float>(ev);
-    if (s) return s;
+    return s ? s : due_sort(ev, defer);
+}
+
+gl_status due_sort(gl_event *ev, bool defer) {
     if (ev->sort_every > 0 && ev->since_sort >= ev->sort_every && ev->slots_used > 0) {
         if (defer) return ev->fp64() ? sort_order_t<double>(ev) : sort_order_t<float>(ev);
         return sort_particles(ev);
@@ -683,7 +764,7 @@ gl_status get_site_fields_t(gl_event *ev, double *F) {
     // stored apart (half_stored)
     const size_t n2 = ev->n2;
     std::vector<T> tmp((size_t)kSiteRec * n2);
-    HIP_TRY(hipMemcpyAsync(tmp.data(), ev->ws + ev->L.F, tmp.size() * sizeof(T), hipMemcpyDeviceToHost, ev->stream));
+    HIP_TRY(hipMemcpyAsync(tmp.data(), ev->site_fields<T>(), tmp.size() * sizeof(T), hipMemcpyDeviceToHost, ev->stream));
     HIP_TRY(hipStreamSynchronize(ev->stream));
     // device records in chunked planes
     auto at = [&](int k, size_t x) { return (double)tmp[chunk_index<T>(n2, k, x)]; };
@@ -1061,7 +1142,12 @@ gl_status gl_run(gl_event *ev, int32_t n_steps) {
     // whole blocks of graph_steps from captured graphs (not while kernels are
     // timed or checked: those keep direct launches), the rest launched directly
     const bool graphs = ev->graph_steps > 0 && ev->prof == 0 && !checks;
-    for (int32_t k = 0; k < n_steps && !s;) {
+    int32_t k = 0;
+    if (!s && n_steps > 1 && ev->graph_steps == 0 && ev->prof == 0 && !checks && pairs(ev)) {
+        s = run_paired(ev, n_steps);
+        k = n_steps;
+    }
+    for (; k < n_steps && !s;) {
         if (graphs && n_steps - k >= ev->graph_steps) {
             s = graph_block(ev, ev->graph_steps, has_particles);
             k += ev->graph_steps;
@@ -1629,12 +1715,12 @@ struct Blob {
 std::vector<Blob> ckpt_blobs(gl_event *ev) {
     const size_t ts = ev->fp64() ? 8 : 4, n2 = ev->n2, row = (size_t)kMaxSpecies * 4 * sizeof(double);
     std::vector<Blob> b;
-    b.push_back({1, ev->ws + ev->L.field[ev->cur], (size_t)kStateVals * n2 * ts});
+    b.push_back({1, ev->field_base(ev->cur), (size_t)kStateVals * n2 * ts});
     if (ev->push_due) {
         // the pending push reads the site fields and the state at tau_n (links
         // for the crossings, phi for the eta rotation), the other buffer
-        b.push_back({2, ev->ws + ev->L.F, (size_t)kSiteRec * n2 * ts});
-        b.push_back({11, ev->ws + ev->L.field[1 - ev->cur], (size_t)kStateVals * n2 * ts});
+        b.push_back({2, ev->ws + ev->L.F[ev->fcur], (size_t)kSiteRec * n2 * ts});
+        b.push_back({11, ev->field_base(1 - ev->cur), (size_t)kStateVals * n2 * ts});
     }
     if (ev->L.slots > 0) {
         b.push_back({3, ev->ws + ev->L.part[ev->pbuf], (size_t)ev->L.slots * ((part_rec(ts) + 3) * ts + 12)});
@@ -1907,7 +1993,7 @@ BatchEv<T> batch_desc(const gl_batch *b, int e) {
     d.f[1] = ev->fields<T>(1 - b->cur0[e]);
     d.P[0] = ev->parts<T>(b->pbuf0[e]);
     d.P[1] = ev->parts<T>(1 - b->pbuf0[e]);
-    d.F = (T *)(ev->ws + ev->L.F);
+    d.F = ev->site_fields<T>();
     d.partials = ev->partials();
     d.p0sum = ev->p0sum();
     d.series = ev->series();

@@ -315,7 +315,7 @@ hipError_t launch_check_finite(hipStream_t st, const T *a, int64_t n, int64_t va
 template <typename T>
 hipError_t launch_field_step(hipStream_t st, int N, FieldPtrs<T> in, FieldPtrs<T> out, T *F, double tau,
                              double dtau, int reunit, const KernelTimer &kt) {
-    dim3 grid(((N + SX - 1) / SX) * ((N + SY - 1) / SY)), block(2 * SX, SY);
+    dim3 grid(field_tiles(N)), block(2 * SX, SY);
     GL_LAUNCH_TIMED(kt, k_field_step<T>, grid, block, 0, st, N, in, out, F, (T)tau, (T)dtau, (T)(tau + 0.5 * dtau),
                     reunit);
     return hipGetLastError();

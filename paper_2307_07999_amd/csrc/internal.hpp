@@ -132,18 +132,32 @@ inline hipError_t timer_skip(hipStream_t st, const KernelTimer &kt) {
 template <typename T>
 hipError_t launch_field_step(hipStream_t st, int N, FieldPtrs<T> in, FieldPtrs<T> out, T *F,
                              double tau, double dtau, int reunit, const KernelTimer &kt);
+// one push of the n_slots slots of P by the fields f and site fields F at
+// tau_n; with perm, a sort still to be applied: position j is pushed from
+// slot perm[j] of P and written, with the particle's other arrays and id, to
+// slot j of W
 template <typename T>
-hipError_t launch_push(hipStream_t st, int N, PartPtrs<T> p, int64_t n_slots, FieldPtrs<T> f,
-                       const T *F, SpeciesTab<T> tab, int n_species, int n, double dtau,
-                       double *partials, const KernelTimer &kt);
-// the push of particles still to be moved by a sort permutation: position j
-// is pushed from slot perm[j] of p and written, with the particle's other
-// arrays and id, to slot j of dst
+struct PushCall {
+    PartPtrs<T> P, W;
+    const int32_t *perm, *id_src;
+    int32_t *id_dst;
+    int64_t n_slots;
+    FieldPtrs<T> f;
+    const T *F;
+    SpeciesTab<T> tab;
+    int n_species, n;
+    T dtau;
+    double *partials;
+};
 template <typename T>
-hipError_t launch_push_permuted(hipStream_t st, int N, PartPtrs<T> p, PartPtrs<T> dst, const int32_t *perm,
-                                const int32_t *id_src, int32_t *id_dst, int64_t n_slots, FieldPtrs<T> f,
-                                const T *F, SpeciesTab<T> tab, int n_species, int n, double dtau,
-                                double *partials, const KernelTimer &kt);
+hipError_t launch_push(hipStream_t st, int N, const PushCall<T> &p, const KernelTimer &kt);
+// workgroups of a field step, 32 x 4 sites each
+inline int field_tiles(int N) { return ((N + 31) / 32) * ((N + 3) / 4); }
+// the field step in -> out (writing F) and the push p of the step before in one
+// launch; neither may touch what the other writes
+template <typename T>
+hipError_t launch_field_push(hipStream_t st, int N, FieldPtrs<T> in, FieldPtrs<T> out, T *F, double tau, double dtau,
+                             int reunit, const PushCall<T> &p);
 hipError_t launch_iota(hipStream_t st, int32_t *id, int64_t n, int64_t n_valid, int32_t base);
 // fixed-order sum of per-workgroup partial rows into a series row; a
 // non-null sub [kMaxSpecies][4] is subtracted from the first three terms of

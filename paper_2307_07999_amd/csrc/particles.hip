@@ -25,46 +25,17 @@
 
 namespace gl {
 
+// the push, and the push that also applies a pending sort
 template <typename T>
-__global__ void __launch_bounds__(kPushBlock)
-k_push(int N, PartPtrs<T> P, int64_t n_slots, FieldPtrs<T> f, const T *__restrict__ F,
-       SpeciesTab<T> tab, int n_species, int n, T dtau, double *__restrict__ partials) {
+__global__ void __launch_bounds__(kPushBlock) k_push(int N, PushCall<T> p) {
+    __shared__ SpeciesReduce lds;
     // neighbouring blocks (neighbouring cells, the particles being sorted) on one XCD
-    const int64_t blk = xcd_remap(blockIdx.x, gridDim.x);
-    const int64_t i = blk * kPushBlock + threadIdx.x;
-    double acc[4] = {0.0, 0.0, 0.0, 0.0};
-    int s = -1;
-    if (i < n_slots) s = push_particle<T>(N, P, i, P, i, f, F, tab, n, dtau, acc);
-    block_species_reduce(s, acc, n_species, partials + (size_t)blk * n_species * 4);
+    push_block<T, false>(lds, N, xcd_remap(blockIdx.x, gridDim.x), p);
 }
-
-// The push that also applies a pending sort: position j takes the particle
-// in slot perm[j] of P, pushes it and writes it, with its species, momenta at
-// formation and id, to slot j of W.  The blocks (and so the partial rows) are
-// those of a push after the permutation.
 template <typename T>
-__global__ void __launch_bounds__(kPushBlock)
-k_push_permuted(int N, PartPtrs<T> P, PartPtrs<T> W, const int32_t *__restrict__ perm,
-                const int32_t *__restrict__ id_src, int32_t *__restrict__ id_dst, int64_t n_slots, FieldPtrs<T> f,
-                const T *__restrict__ F, SpeciesTab<T> tab, int n_species, int n, T dtau,
-                double *__restrict__ partials) {
-    const int64_t blk = xcd_remap(blockIdx.x, gridDim.x);
-    const int64_t j = blk * kPushBlock + threadIdx.x;
-    double acc[4] = {0.0, 0.0, 0.0, 0.0};
-    int s = -1;
-    if (j < n_slots) {
-        const int64_t i = perm[j];
-        // the fields that only move go first, so that nothing of them stays
-        // live through the push
-        W.species[j] = P.species[i];
-        W.px0[j] = P.px0[i];
-        W.py0[j] = P.py0[i];
-        W.pz0[j] = P.pz0[i];
-        id_dst[j] = id_src[i];
-        __builtin_amdgcn_sched_barrier(0);
-        s = push_particle<T, true>(N, P, i, W, j, f, F, tab, n, dtau, acc);
-    }
-    block_species_reduce(s, acc, n_species, partials + (size_t)blk * n_species * 4);
+__global__ void __launch_bounds__(kPushBlock) k_push_permuted(int N, PushCall<T> p) {
+    __shared__ SpeciesReduce lds;
+    push_block<T, true>(lds, N, xcd_remap(blockIdx.x, gridDim.x), p);
 }
 
 // series row [kMaxSpecies][4]: species s sums the partial rows of all push
@@ -297,25 +268,11 @@ hipError_t launch_iota(hipStream_t st, int32_t *id, int64_t n, int64_t n_valid, 
 }
 
 template <typename T>
-hipError_t launch_push(hipStream_t st, int N, PartPtrs<T> p, int64_t n_slots, FieldPtrs<T> f,
-                       const T *F, SpeciesTab<T> tab, int n_species, int n, double dtau, double *partials,
-                       const KernelTimer &kt) {
-    if (n_slots <= 0) return timer_skip(st, kt);
-    unsigned blocks = (unsigned)((n_slots + kPushBlock - 1) / kPushBlock);
-    GL_LAUNCH_TIMED(kt, k_push<T>, dim3(blocks), dim3(kPushBlock), 0, st, N, p, n_slots, f, F, tab, n_species, n,
-                    (T)dtau, partials);
-    return hipGetLastError();
-}
-
-template <typename T>
-hipError_t launch_push_permuted(hipStream_t st, int N, PartPtrs<T> p, PartPtrs<T> dst, const int32_t *perm,
-                                const int32_t *id_src, int32_t *id_dst, int64_t n_slots, FieldPtrs<T> f,
-                                const T *F, SpeciesTab<T> tab, int n_species, int n, double dtau,
-                                double *partials, const KernelTimer &kt) {
-    if (n_slots <= 0) return timer_skip(st, kt);
-    unsigned blocks = (unsigned)((n_slots + kPushBlock - 1) / kPushBlock);
-    GL_LAUNCH_TIMED(kt, k_push_permuted<T>, dim3(blocks), dim3(kPushBlock), 0, st, N, p, dst, perm, id_src, id_dst,
-                    n_slots, f, F, tab, n_species, n, (T)dtau, partials);
+hipError_t launch_push(hipStream_t st, int N, const PushCall<T> &p, const KernelTimer &kt) {
+    if (p.n_slots <= 0) return timer_skip(st, kt);
+    const dim3 blocks((unsigned)((p.n_slots + kPushBlock - 1) / kPushBlock)), wg(kPushBlock);
+    if (p.perm) GL_LAUNCH_TIMED(kt, k_push_permuted<T>, blocks, wg, 0, st, N, p);
+    else GL_LAUNCH_TIMED(kt, k_push<T>, blocks, wg, 0, st, N, p);
     return hipGetLastError();
 }
 
@@ -345,13 +302,7 @@ hipError_t launch_particles_init(hipStream_t st, int N, PartPtrs<T> p, int64_t s
 }
 
 #define GL_INST(T)                                                                               \
-    template hipError_t launch_push<T>(hipStream_t, int, PartPtrs<T>, int64_t, FieldPtrs<T>,      \
-                                       const T *, SpeciesTab<T>, int, int, double, double *,     \
-                                       const KernelTimer &);                                     \
-    template hipError_t launch_push_permuted<T>(hipStream_t, int, PartPtrs<T>, PartPtrs<T>,       \
-                                                const int32_t *, const int32_t *, int32_t *,     \
-                                                int64_t, FieldPtrs<T>, const T *, SpeciesTab<T>, \
-                                                int, int, double, double *, const KernelTimer &); \
+    template hipError_t launch_push<T>(hipStream_t, int, const PushCall<T> &, const KernelTimer &); \
     template hipError_t launch_particles_init<T>(hipStream_t, int, PartPtrs<T>, int64_t, int64_t, \
                                                  uint64_t, int, int, double);                    \
     template hipError_t launch_casimir<T>(hipStream_t, PartPtrs<T>, int64_t, double *, int *);             \

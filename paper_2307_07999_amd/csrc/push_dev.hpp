@@ -192,12 +192,18 @@ __device__ __forceinline__ int push_particle(int N, const PartPtrs<T> &P, int64_
 // sums term c % 4 of species c / 4 over the 32 particles of segment g in
 // particle order, and thread c adds the segments in order -- a fixed order,
 // so the partial sums are deterministic.  Writes out[sp * 4 + k].
-__device__ __forceinline__ void block_species_reduce(int s, const double *acc, int n_species,
+struct SpeciesReduce {
+    static constexpr int kSeg = 8, kLen = kPushBlock / kSeg;
+    double val[4][kPushBlock];
+    int spc[kPushBlock];
+    double part[kSeg][kMaxSpecies * 4];
+};
+__device__ __forceinline__ void block_species_reduce(SpeciesReduce &lds, int s, const double *acc, int n_species,
                                                      double *__restrict__ out) {
-    constexpr int kSeg = 8, kLen = kPushBlock / kSeg;
-    __shared__ double val[4][kPushBlock];
-    __shared__ int spc[kPushBlock];
-    __shared__ double part[kSeg][kMaxSpecies * 4];
+    constexpr int kSeg = SpeciesReduce::kSeg, kLen = SpeciesReduce::kLen;
+    auto &val = lds.val;
+    auto &spc = lds.spc;
+    auto &part = lds.part;
     const int t = threadIdx.x;
     spc[t] = s;
 #pragma unroll
@@ -218,6 +224,39 @@ __device__ __forceinline__ void block_species_reduce(int s, const double *acc, i
         for (int g = 0; g < kSeg; g++) sum += part[g][t];
         out[t] = sum;
     }
+}
+__device__ __forceinline__ void block_species_reduce(int s, const double *acc, int n_species,
+                                                     double *__restrict__ out) {
+    __shared__ SpeciesReduce lds;
+    block_species_reduce(lds, s, acc, n_species, out);
+}
+
+// Block blk of a push; with PERM the one that also applies a pending sort:
+// position j takes the particle in slot perm[j] of P, pushes it and writes it,
+// with its species, momenta at formation and id, to slot j of W.  The blocks (and
+// so the partial rows) are those of a push after the permutation.
+template <typename T, bool PERM, bool ST = kStreamed<T>>
+__device__ __forceinline__ void push_block(SpeciesReduce &lds, int N, int64_t blk, const PushCall<T> &p) {
+    const int64_t j = blk * kPushBlock + threadIdx.x;
+    double acc[4] = {0.0, 0.0, 0.0, 0.0};
+    int s = -1;
+    if (j < p.n_slots) {
+        if constexpr (PERM) {
+            const int64_t i = p.perm[j];
+            // the fields that only move go first, so that nothing of them stays
+            // live through the push
+            p.W.species[j] = p.P.species[i];
+            p.W.px0[j] = p.P.px0[i];
+            p.W.py0[j] = p.P.py0[i];
+            p.W.pz0[j] = p.P.pz0[i];
+            p.id_dst[j] = p.id_src[i];
+            __builtin_amdgcn_sched_barrier(0);
+            s = push_particle<T, true, ST>(N, p.P, i, p.W, j, p.f, p.F, p.tab, p.n, p.dtau, acc);
+        } else {
+            s = push_particle<T, false, ST>(N, p.P, j, p.P, j, p.f, p.F, p.tab, p.n, p.dtau, acc);
+        }
+    }
+    block_species_reduce(lds, s, acc, p.n_species, p.partials + (size_t)blk * p.n_species * 4);
 }
 
 }  // namespace gl
