@@ -12,7 +12,7 @@ struct BatchEv {
     int reunit_every;
     int n_species;
     int max_steps;
-    int64_t n_slots;
+    int64_t n_slots, n_particles;   // used slots, the valid ones first
     FieldPtrs<T> f[2];     // f[p] and f[p ^ 1]: state at step n and at n + 1 for parity p
     PartPtrs<T> P[2];      // particle buffers; the current one alternates at each sort
     T *F;                  // site-field records (chunked planes), written by the field phase when n_species > 0
@@ -21,7 +21,7 @@ struct BatchEv {
     double *series;        // [max_steps][kMaxSpecies][4]
     SpeciesTab<T> tab;
     SortScratch sort;      // the event's radix-sort scratch
-    int64_t sort_tiles;    // sort tiles over n_slots
+    int64_t sort_tiles;    // sort tiles over n_particles
     int32_t *ids[2];       // particle ids, alternating with P
     int32_t *fail;         // first step at which the event failed (kNotFailed: none); failed events are skipped
 };
@@ -66,7 +66,7 @@ hipError_t launch_batch_fields(hipStream_t st, int shape, const BatchEv<T> *evs,
 // next push moves them (launch_batch_push with permuted) or
 // launch_batch_permute does.
 template <typename T>
-hipError_t launch_batch_sort(hipStream_t st, const BatchEv<T> *evs, int n_events, const int2 *pblocks,
+hipError_t launch_batch_sort(hipStream_t st, const BatchEv<T> *evs, int n_events, int passes, const int2 *pblocks,
                              int64_t n_pblocks, const int2 *stiles, int64_t n_stiles, int ppar, bool permute);
 template <typename T>
 hipError_t launch_batch_permute(hipStream_t st, const BatchEv<T> *evs, const int2 *pblocks, int64_t n_pblocks,

@@ -111,8 +111,8 @@ gl_status make_layout(const gl_lattice_desc *d, Layout &L) {
     for (int b = 0; b < 2; b++) L.id[b] = take((size_t)L.slots * sizeof(int32_t));
     for (int b = 0; b < 2; b++) L.sort_keys[b] = take((size_t)L.slots * sizeof(uint32_t));
     for (int b = 0; b < 2; b++) L.sort_vals[b] = take((size_t)L.slots * sizeof(int32_t));
-    L.sort_counts = take((size_t)256 * std::max<int64_t>(1, sort_tiles(L.slots)) * sizeof(uint32_t));
-    L.sort_totals = take(256 * sizeof(uint32_t));
+    L.sort_counts = take((size_t)kDigits * std::max<int64_t>(1, sort_tiles(L.slots)) * sizeof(uint32_t));
+    L.sort_totals = take(kDigits * sizeof(uint32_t));
     // partial rows of up to kReduceSlots pushes, reduced into the series in one launch
     L.partials = take(kReduceSlots * partial_slot_stride(L.slots) * sizeof(double));
     L.series = take(std::max(1, d->max_steps) * (size_t)kMaxSpecies * 4 * sizeof(double));
@@ -447,11 +447,17 @@ gl_status push(gl_event *ev) {
     return push_done(ev, n_prev);
 }
 
+int64_t total_particles(const gl_event *ev) {
+    int64_t t = 0;
+    for (auto &s : ev->species) t += s.n;
+    return t;
+}
+
 template <typename T>
 gl_status sort_t(gl_event *ev) {
     const int nb = 1 - ev->pbuf;
-    HIP_TRY(launch_sort_particles<T>(ev->stream, ev->N, ev->parts<T>(ev->pbuf), ev->parts<T>(nb), ev->slots_used,
-                                     ev->scratch(), ev->ids(ev->pbuf), ev->ids(nb)));
+    HIP_TRY(launch_sort_particles<T>(ev->stream, ev->N, ev->parts<T>(ev->pbuf), ev->parts<T>(nb), total_particles(ev),
+                                     ev->slots_used, ev->scratch(), ev->ids(ev->pbuf), ev->ids(nb)));
     ev->pbuf = nb;
     ev->since_sort = 0;
     ev->perm_pending = false;   // a full sort supersedes a pending order
@@ -466,7 +472,8 @@ gl_status sort_particles(gl_event *ev) {
 // the sorted order only; the next push moves the particles by it
 template <typename T>
 gl_status sort_order_t(gl_event *ev) {
-    HIP_TRY(launch_sort_order<T>(ev->stream, ev->N, ev->parts<T>(ev->pbuf), ev->slots_used, ev->scratch()));
+    HIP_TRY(launch_sort_order<T>(ev->stream, ev->N, ev->parts<T>(ev->pbuf), total_particles(ev), ev->slots_used,
+                                 ev->scratch()));
     ev->perm_pending = true;
     ev->since_sort = 0;
     return GL_OK;
@@ -902,12 +909,6 @@ gl_status get_particles_t(gl_event *ev, int64_t n, int32_t *cell, double *off, d
         }
     }
     return GL_OK;
-}
-
-int64_t total_particles(const gl_event *ev) {
-    int64_t t = 0;
-    for (auto &s : ev->species) t += s.n;
-    return t;
 }
 
 gl_status read_series_species(gl_event *ev, int32_t species, std::vector<double> &rows4) {
@@ -1969,7 +1970,7 @@ gl_status batch_sizes(gl_event *const *evs, int n, BatchSizes &z) {
     for (int e = 0; e < n; e++) z.n_pblocks += evs[e]->L.slots / kPushBlock;
     z.pblocks = take((size_t)std::max<int64_t>(1, z.n_pblocks) * sizeof(int2));
     z.n_stiles = 0;
-    for (int e = 0; e < n; e++) z.n_stiles += evs[e]->slots_used > 0 ? sort_tiles(evs[e]->slots_used) : 0;
+    for (int e = 0; e < n; e++) z.n_stiles += sort_tiles(total_particles(evs[e]));
     z.stiles = take((size_t)std::max<int64_t>(1, z.n_stiles) * sizeof(int2));
     z.ctl = take(sizeof(BatchCtl));
     z.fail = take((size_t)n * sizeof(int32_t));
@@ -1999,11 +2000,19 @@ BatchEv<T> batch_desc(const gl_batch *b, int e) {
     d.series = ev->series();
     d.tab = ev->tab<T>();
     d.sort = ev->scratch();
-    d.sort_tiles = ev->slots_used > 0 ? sort_tiles(ev->slots_used) : 0;
+    d.n_particles = total_particles(ev);
+    d.sort_tiles = sort_tiles(d.n_particles);
     d.ids[0] = ev->ids(b->pbuf0[e]);
     d.ids[1] = ev->ids(1 - b->pbuf0[e]);
     d.fail = (int32_t *)(b->ws + b->fail) + e;
     return d;
+}
+
+// digit passes that sort every event of the batch
+int batch_sort_passes(const gl_batch *b) {
+    int p = 1;
+    for (const gl_event *ev : b->evs) p = std::max(p, sort_passes(ev->N));
+    return p;
 }
 
 template <typename T>
@@ -2021,7 +2030,8 @@ gl_status batch_step(gl_batch *b) {
     b->fpar ^= 1;
     b->since_sort++;
     if (b->any_particles && b->sort_every > 0 && b->since_sort >= b->sort_every) {
-        HIP_TRY(launch_batch_sort<T>(b->stream, d, (int)b->evs.size(), (const int2 *)(b->ws + b->pblocks),
+        HIP_TRY(launch_batch_sort<T>(b->stream, d, (int)b->evs.size(), batch_sort_passes(b),
+                                     (const int2 *)(b->ws + b->pblocks),
                                      b->total_pblocks, (const int2 *)(b->ws + b->stiles), b->total_stiles, b->ppar,
                                      false));
         b->sort_pending = true;
@@ -2303,7 +2313,7 @@ gl_status gl_batch_create(gl_event *const *evs, int32_t n_events, void *workspac
     std::vector<int2> stl;
     for (int e = 0; e < n_events; e++)
         if (evs[e]->slots_used > 0)
-            for (int64_t j = 0; j < sort_tiles(evs[e]->slots_used); j++) stl.push_back(make_int2(e, (int)j));
+            for (int64_t j = 0; j < sort_tiles(total_particles(evs[e])); j++) stl.push_back(make_int2(e, (int)j));
     b->total_stiles = (int64_t)stl.size();
     if (!stl.empty() && hipMemcpyAsync(b->ws + b->stiles, stl.data(), stl.size() * sizeof(int2), hipMemcpyHostToDevice,
                                        b->stream) != hipSuccess)

@@ -88,13 +88,17 @@ struct SortScratch {
     uint32_t *totals;
 };
 int64_t sort_tiles(int64_t n);
+constexpr int kDigitBits = 9, kDigits = 1 << kDigitBits;   // widest digit of a pass
+int sort_passes(int N);                                    // passes on the cells of an N x N lattice
+// sorts the n valid slots [0, n) of src by cell into dst, the padding up to
+// n_slots in place
 template <typename T>
-hipError_t launch_sort_particles(hipStream_t st, int N, PartPtrs<T> src, PartPtrs<T> dst, int64_t n,
+hipError_t launch_sort_particles(hipStream_t st, int N, PartPtrs<T> src, PartPtrs<T> dst, int64_t n, int64_t n_slots,
                                  SortScratch s, int32_t *id_src, int32_t *id_dst);
 // the two halves of launch_sort_particles: the sorted order (its
 // permutation then at sort_perm), and moving every particle array by it
 template <typename T>
-hipError_t launch_sort_order(hipStream_t st, int N, PartPtrs<T> src, int64_t n, SortScratch s);
+hipError_t launch_sort_order(hipStream_t st, int N, PartPtrs<T> src, int64_t n, int64_t n_slots, SortScratch s);
 const int32_t *sort_perm(SortScratch s);
 template <typename T>
 hipError_t launch_permute(hipStream_t st, PartPtrs<T> src, PartPtrs<T> dst, const int32_t *perm, int64_t n,
