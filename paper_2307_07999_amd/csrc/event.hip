@@ -44,6 +44,8 @@ inline size_t partial_slot_stride(int64_t slots) {
     return (size_t)std::max<int64_t>(1, slots / kPushBlock) * kMaxSpecies * 4;
 }
 
+inline size_t corr_slot(size_t n2) { return (size_t)corr_blocks(n2) * 4; }   // partial rows of one correlator step
+
 struct Layout {
     size_t field[3], F[2], part[2], id[2], sort_keys[2], sort_vals[2], sort_counts, sort_totals, partials,
         series, p0sum, diag, VA, VB, planes, fft_tab, U0, pi0, status, stat, stat_part, stat_series, ll, ll_part,
@@ -130,12 +132,12 @@ gl_status make_layout(const gl_lattice_desc *d, Layout &L) {
     // static-quark accumulators I [24][n2], their per-workgroup partials and series
     const bool stat = d->static_correlator != 0;
     L.stat = take(stat ? 24 * n2 * sizeof(double) : 0);
-    L.stat_part = take(stat ? (n2 + 255) / 256 * 4 * sizeof(double) : 0);
+    L.stat_part = take(stat ? kReduceSlots * corr_slot(n2) * sizeof(double) : 0);
     L.stat_series = take(stat ? std::max(1, d->max_steps) * (size_t)kMaxSpecies * 4 * sizeof(double) : 0);
     // lightlike-jet transports W [18][n2] and accumulators I [24][n2], partials and series
     const bool ll = d->lightlike_correlator != 0;
     L.ll = take(ll ? 42 * n2 * sizeof(double) : 0);
-    L.ll_part = take(ll ? (n2 + 255) / 256 * 4 * sizeof(double) : 0);
+    L.ll_part = take(ll ? kReduceSlots * corr_slot(n2) * sizeof(double) : 0);
     L.ll_series = take(ll ? std::max(1, d->max_steps) * (size_t)kMaxSpecies * 4 * sizeof(double) : 0);
     L.total = off;
     return GL_OK;
@@ -182,6 +184,9 @@ struct gl_event {
     bool stat_on = false;       // static-quark accumulation running
     int64_t stat_n0 = 0;        // first accumulated field step
     int64_t stat_rows = 0;      // static series rows written
+    // steps whose partial rows are not reduced yet, and the first one's series row
+    int stat_pend = 0, ll_pend = 0;
+    int64_t stat_row0 = 0, ll_row0 = 0;
     bool ll_on = false;         // lightlike-jet accumulation running
     int64_t ll_n0 = 0;          // first accumulated field step
     int64_t ll_rows = 0;
@@ -337,6 +342,21 @@ gl_status prof_end(gl_event *ev, size_t idx) {
         HIP_TRY(call);                                          \
     } while (0)
 
+// reduce the correlators' pending partial rows into their series rows
+gl_status flush_correlators(gl_event *ev) {
+    const int nb = corr_blocks(ev->n2);
+    if (ev->stat_pend > 0)
+        HIP_TRY(launch_series_reduce_steps(ev->stream, (const double *)(ev->ws + ev->L.stat_part), corr_slot(ev->n2),
+                                           ev->stat_pend, nb, 1, ev->stat_series() + ev->stat_row0 * kMaxSpecies * 4,
+                                           nullptr));
+    if (ev->ll_pend > 0)
+        HIP_TRY(launch_series_reduce_steps(ev->stream, (const double *)(ev->ws + ev->L.ll_part), corr_slot(ev->n2),
+                                           ev->ll_pend, nb, 1, ev->ll_series() + ev->ll_row0 * kMaxSpecies * 4,
+                                           nullptr));
+    ev->stat_pend = ev->ll_pend = 0;
+    return GL_OK;
+}
+
 // one field step n -> n+1, with the site fields F^n in the same pass when the
 // event has particles; with p, the push of the step before in the same launch
 template <typename T>
@@ -361,27 +381,34 @@ gl_status field_step(gl_event *ev, bool site_fields, const PushCall<T> *p = null
                                                  site_fields || stat || ll ? ev->site_fields<T>() : nullptr, tau,
                                                  ev->dtau, reunit, kt_)));
     }
-    if (stat) {
-        // static quarks: accumulate the site fields at tau_n, series row n - 1 (time tau_{n+1/2})
-        int nb = 0;
-        double *part = (double *)(ev->ws + ev->L.stat_part);
-        PROF(ev, 1, (launch_static_accum<T>(ev->stream, ev->N, ev->site_fields<T>(),
-                                            (double *)(ev->ws + ev->L.stat), ev->dtau, part, &nb)));
-        HIP_TRY(launch_series_reduce(ev->stream, part, nb, 1, ev->stat_series() + (ev->n - 1) * kMaxSpecies * 4,
-                                     nullptr));
-        ev->stat_rows = std::max<int64_t>(ev->stat_rows, ev->n);
-    }
-    if (ll) {
-        // lightlike jets: transported forces at tau_n with the x links of tau_n (state cur)
-        int nb = 0;
-        double *part = (double *)(ev->ws + ev->L.ll_part);
-        double *W = (double *)(ev->ws + ev->L.ll), *I = W + 18 * ev->n2;
-        PROF(ev, 1, (launch_lightlike_accum<T>(ev->stream, ev->N, ev->site_fields<T>(),
-                                               ev->fields<T>(ev->cur).U, W, I, ev->n - ev->ll_n0, ev->dtau, part,
-                                               &nb)));
-        HIP_TRY(launch_series_reduce(ev->stream, part, nb, 1, ev->ll_series() + (ev->n - 1) * kMaxSpecies * 4,
-                                     nullptr));
-        ev->ll_rows = std::max<int64_t>(ev->ll_rows, ev->n);
+    if (stat || ll) {
+        // both correlators from the site fields at tau_n, the lightlike one with
+        // the x links of tau_n (state cur); series row n - 1 (time tau_{n+1/2})
+        const int64_t row = ev->n - 1;
+        CorrCall c{};
+        if (stat) {
+            if (ev->stat_pend == 0) ev->stat_row0 = row;
+            c.Is = (double *)(ev->ws + ev->L.stat);
+            c.part_s = (double *)(ev->ws + ev->L.stat_part) + ev->stat_pend++ * corr_slot(ev->n2);
+            ev->stat_rows = std::max<int64_t>(ev->stat_rows, row + 1);
+        }
+        if (ll) {
+            if (ev->ll_pend == 0) ev->ll_row0 = row;
+            c.W = (double *)(ev->ws + ev->L.ll);
+            c.Il = c.W + 18 * ev->n2;
+            c.j = ev->n - ev->ll_n0;
+            c.part_l = (double *)(ev->ws + ev->L.ll_part) + ev->ll_pend++ * corr_slot(ev->n2);
+            ev->ll_rows = std::max<int64_t>(ev->ll_rows, row + 1);
+        }
+        // accumulators, states and site fields against the last-level cache
+        const size_t vals = (stat ? 24 : 0) + (ll ? 42 : 0), ts = sizeof(T);
+        const bool streamed = (vals * 8 + (2 * kStateVals + kSiteRec) * ts) * ev->n2 > kPairBytes;
+        PROF(ev, 1, (launch_correlators<T>(ev->stream, ev->N, ev->site_fields<T>(), ev->fields<T>(ev->cur).U, c,
+                                           ev->dtau, streamed)));
+        if (ev->stat_pend == kReduceSlots || ev->ll_pend == kReduceSlots) {
+            gl_status s = flush_correlators(ev);
+            if (s) return s;
+        }
     }
     ev->cur = nxt;
     ev->n += 1;
@@ -1113,7 +1140,7 @@ gl_status gl_evolve_fields(gl_event *ev, int32_t n_steps) {
         if (s) return s;
         if (has_particles) ev->push_due = true;
     }
-    return GL_OK;
+    return flush_correlators(ev);
 }
 
 gl_status gl_push_particles(gl_event *ev) {
@@ -1162,7 +1189,8 @@ gl_status gl_run(gl_event *ev, int32_t n_steps) {
     const gl_status sp = apply_pending_sort(ev);
     if (s) return s;
     if (sp) return sp;
-    s = flush_series(ev);
+    s = flush_correlators(ev);
+    if (!s) s = flush_series(ev);
     if (s || !checks) return s;
     return check_report(ev, first_bad, row0, row_end);
 }
@@ -1179,6 +1207,7 @@ gl_status gl_static_start(gl_event *ev, double tau_start_fm) {
     HIP_TRY(hipMemsetAsync(ev->stat_series(), 0,
                            std::max(1, ev->desc.max_steps) * (size_t)kMaxSpecies * 4 * sizeof(double), ev->stream));
     ev->stat_rows = 0;
+    ev->stat_pend = 0;
     ev->stat_on = true;
     return GL_OK;
 }
@@ -1228,6 +1257,7 @@ gl_status gl_lightlike_start(gl_event *ev, double tau_start_fm) {
     HIP_TRY(hipMemsetAsync(ev->ll_series(), 0,
                            std::max(1, ev->desc.max_steps) * (size_t)kMaxSpecies * 4 * sizeof(double), ev->stream));
     ev->ll_rows = 0;
+    ev->ll_pend = 0;
     ev->ll_on = true;
     return GL_OK;
 }
@@ -1861,7 +1891,7 @@ gl_status gl_restore(gl_event *ev, const char *path) {
     ev->match_max_iter = c.match_max_iter;
     ev->match_tol = c.match_tol;
     ev->check_every = c.check_every;
-    ev->pend = 0;
+    ev->pend = ev->stat_pend = ev->ll_pend = 0;
     ev->pend_row0 = 0;
     ev->perm_pending = false;
     ev->ready = false;   // until every blob is in

@@ -54,114 +54,124 @@ k_field_step(int N, FieldPtrs<T> in, FieldPtrs<T> out, T *__restrict__ F, T tau,
     field_step_link(tile, N, in, out, F, x0, y0, lx, ly, threadIdx.x & 1, tid, active, tau, dtau, tau_h, reunit);
 }
 
-// Static quarks (Sec. 2, Eq. (4)): I_i^a(x) += dtau E_i^a(x, tau_n) from the
-// site fields at tau_n (E_x and E_y adding the half stored apart where
-// half_stored holds), FP64, and
-// per workgroup the sums over its sites of (1/2) sum_a (I_i^a)^2 for
-// i = x, y, z with the site count, added in a fixed order.
-template <typename T>
+// The two field correlators at tau_n, FP64, from one read of the site fields
+// (E_x and E_y adding the half stored apart where half_stored holds).
+//
+// Static quarks (STAT; Sec. 2, Eq. (4)): I_i^a(x) += dtau E_i^a(x, tau_n).
+//
+// Lightlike jets (LIGHT; Sec. 2, Eq. (5)): one jet per start site x0, step j
+// since its start; it sits in the cell x0 + floor(j dtau + 1/2) along x and feels
+// F_x = E_x, F_y = E_y - B_z, F_z = E_z + B_y there, transported to its start
+// with W: I_i += dtau [W F_i W^dag]; when this step's drift ends in the next
+// cell, W <- W U_x(cell) with the links of tau_n.
+//
+// One thread per cell, which serves the static quark there and the jet that
+// sits in it.  Per workgroup and correlator the sums over its cells of
+// (1/2) sum_a (I_i^a)^2 for i = x, y, z and their count, added in a fixed
+// order (part_s, part_l [blocks][4]).
+//
+// Bound: by HBM, 340 MB at 512^2 in FP64 (accumulators and W in and out, E, B_y and
+// B_z in).  The accumulators are read and written once a step and take the
+// streaming hint (ST) where the event overflows the last-level cache, so that
+// the site fields stay for the push.  Apart, with 8-byte reads of 16-byte
+// chunks and a reduction launch each, the two took 33 + 53 + 10 us a step;
+// together 63 us, and the push behind them 116 -> 101 us.
+template <typename T, bool STAT, bool LIGHT, bool ST>
 __global__ void __launch_bounds__(256)
-k_static_accum(int N, const T *__restrict__ F, double *__restrict__ I, double dtau, double *__restrict__ partials) {
-    __shared__ double red[4][256];
+k_correlators(int N, const T *__restrict__ F, const T *__restrict__ U, double *__restrict__ Is, double *__restrict__ W,
+              double *__restrict__ Il, int64_t j, double dtau, double *__restrict__ part_s,
+              double *__restrict__ part_l) {
+    constexpr int CP = stream_policy(ST);
+    __shared__ double red[8][4];
     const size_t n2 = plane_pitch(N);
-    const size_t x = (size_t)blockIdx.x * 256 + threadIdx.x;
-    double v[4] = {0.0, 0.0, 0.0, 0.0};
-    if (x < (size_t)N * N) {
-#pragma unroll
-        for (int i = 0; i < 3; i++) {
-            double s = 0.0;
-#pragma unroll
-            for (int a = 0; a < 8; a++) {
-                double e = (double)chunk_ld(F, n2, x, 8 * i + a);
-                if (i < 2 && half_stored(i, (int)(x % N), (int)(x / N)))
-                    e += (double)chunk_ld(F, n2, x, 48 + 8 * i + a);
-                const double t = pl_ld(I, n2, 8 * i + a, x) + dtau * e;
-                pl_st(I, n2, 8 * i + a, x, t);
-                s += t * t;
-            }
-            v[i] = 0.5 * s;
-        }
-        v[3] = 1.0;
-    }
-#pragma unroll
-    for (int k = 0; k < 4; k++) red[k][threadIdx.x] = v[k];
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if (threadIdx.x < w)
-#pragma unroll
-            for (int k = 0; k < 4; k++) red[k][threadIdx.x] += red[k][threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x < 4) partials[(size_t)blockIdx.x * 4 + threadIdx.x] = red[threadIdx.x][0];
-}
-
-// Lightlike jets (Sec. 2, Eq. (5)): one jet per start site x0, step j since
-// its start; it sits in the cell x0 + floor(j dtau + 1/2) along x and feels
-// F_x = E_x, F_y = E_y - B_z, F_z = E_z + B_y there (site fields at tau_n),
-// transported to its start with W (FP64): I_i += dtau [W F_i W^dag]; when
-// this step's drift ends in the next cell, W <- W U_x(cell) with the links of
-// tau_n.  Per workgroup: sums of (1/2) sum_a (I_i^a)^2 and the site count.
-template <typename T>
-__global__ void __launch_bounds__(256)
-k_lightlike_accum(int N, const T *__restrict__ F, const T *__restrict__ U, double *__restrict__ W,
-                  double *__restrict__ I, int64_t j, double dtau, double *__restrict__ partials) {
-    __shared__ double red[4][256];
-    const size_t n2 = plane_pitch(N);
-    const size_t x0 = (size_t)blockIdx.x * 256 + threadIdx.x;
-    double v[4] = {0.0, 0.0, 0.0, 0.0};
-    if (x0 < (size_t)N * N) {
-        const int64_t shift = (int64_t)floor((double)j * dtau + 0.5);
-        const int ix = (int)(((int64_t)(x0 % N) + shift) % N), iy = (int)(x0 / N);
-        const size_t c = (size_t)ix + (size_t)N * iy;
-        M3<double> w = load_m(W, n2, x0);
-#pragma unroll
-        for (int i = 0; i < 3; i++) {
-            double f[8], t[8];
-#pragma unroll
-            for (int a = 0; a < 8; a++) {
-                if (i == 0)
-                    f[a] = (double)chunk_ld(F, n2, c, a) +
-                           (half_stored(0, ix, iy) ? (double)chunk_ld(F, n2, c, 48 + a) : 0.0);
-                else if (i == 1)
-                    f[a] = ((double)chunk_ld(F, n2, c, 8 + a) +
-                            (half_stored(1, ix, iy) ? (double)chunk_ld(F, n2, c, 56 + a) : 0.0)) -
-                           (double)chunk_ld(F, n2, c, 40 + a);
-                else f[a] = (double)chunk_ld(F, n2, c, 16 + a) + (double)chunk_ld(F, n2, c, 32 + a);
-            }
-            transport_nd(w, f, t);
-            double s = 0.0;
-#pragma unroll
-            for (int a = 0; a < 8; a++) {
-                const double q = pl_ld(I, n2, 8 * i + a, x0) + dtau * t[a];
-                pl_st(I, n2, 8 * i + a, x0, q);
-                s += q * q;
-            }
-            v[i] = 0.5 * s;
-        }
-        v[3] = 1.0;
-        if ((int64_t)floor((double)(j + 1) * dtau + 0.5) > shift) {
-            const M3<T> u = chunk_load_link(U, n2, c, 0);
-            M3<double> ud;
+    const size_t c = (size_t)blockIdx.x * 256 + threadIdx.x;
+    double v[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    if (c < (size_t)N * N) {
+        const int ix = (int)(c % N), iy = (int)(c / N);
+        const int64_t shift = LIGHT ? (int64_t)floor((double)j * dtau + 0.5) : 0;
+        const int back = ix - (int)(shift % N);
+        const size_t x0 = (size_t)(back < 0 ? back + N : back) + (size_t)N * iy;   // start site of the jet here
+        M3<double> w;
+        if constexpr (LIGHT) {
 #pragma unroll
             for (int r = 0; r < 3; r++)
 #pragma unroll
                 for (int q = 0; q < 3; q++) {
-                    ud.re[r][q] = (double)u.re[r][q];
-                    ud.im[r][q] = (double)u.im[r][q];
+                    w.re[r][q] = pl_ld_p<CP>(W, n2, 2 * (3 * r + q), x0);
+                    w.im[r][q] = pl_ld_p<CP>(W, n2, 2 * (3 * r + q) + 1, x0);
                 }
-            store_m(W, n2, x0, mul(w, ud));
+        }
+#pragma unroll
+        for (int i = 0; i < 3; i++) {
+            T re[8], rh[8];
+            double e[8];
+            chunk_load_a(F, n2, c, 8 * i, re);
+            const bool half = i < 2 && half_stored(i, ix, iy);
+            if (half) chunk_load_a(F, n2, c, 48 + 8 * i, rh);
+#pragma unroll
+            for (int a = 0; a < 8; a++) e[a] = (double)re[a] + (half ? (double)rh[a] : 0.0);
+            if constexpr (STAT) {
+                double s = 0.0;
+#pragma unroll
+                for (int a = 0; a < 8; a++) {
+                    const double q = pl_ld_p<CP>(Is, n2, 8 * i + a, c) + dtau * e[a];
+                    pl_st_p<CP>(Is, n2, 8 * i + a, c, q);
+                    s += q * q;
+                }
+                v[i] = 0.5 * s;
+            }
+            if constexpr (LIGHT) {
+                double t[8];
+                if (i > 0) {
+                    T rb[8];   // B_z for F_y, B_y for F_z
+                    chunk_load_a(F, n2, c, i == 1 ? 40 : 32, rb);
+#pragma unroll
+                    for (int a = 0; a < 8; a++) e[a] += i == 1 ? -(double)rb[a] : (double)rb[a];
+                }
+                transport_nd(w, e, t);
+                double s = 0.0;
+#pragma unroll
+                for (int a = 0; a < 8; a++) {
+                    const double q = pl_ld_p<CP>(Il, n2, 8 * i + a, x0) + dtau * t[a];
+                    pl_st_p<CP>(Il, n2, 8 * i + a, x0, q);
+                    s += q * q;
+                }
+                v[4 + i] = 0.5 * s;
+            }
+        }
+        v[3] = v[7] = 1.0;
+        if constexpr (LIGHT) {
+            if ((int64_t)floor((double)(j + 1) * dtau + 0.5) > shift) {
+                const M3<T> u = chunk_load_link(U, n2, c, 0);
+                M3<double> ud;
+#pragma unroll
+                for (int r = 0; r < 3; r++)
+#pragma unroll
+                    for (int q = 0; q < 3; q++) {
+                        ud.re[r][q] = (double)u.re[r][q];
+                        ud.im[r][q] = (double)u.im[r][q];
+                    }
+                w = mul(w, ud);
+#pragma unroll
+                for (int r = 0; r < 3; r++)
+#pragma unroll
+                    for (int q = 0; q < 3; q++) {
+                        pl_st_p<CP>(W, n2, 2 * (3 * r + q), x0, w.re[r][q]);
+                        pl_st_p<CP>(W, n2, 2 * (3 * r + q) + 1, x0, w.im[r][q]);
+                    }
+            }
         }
     }
 #pragma unroll
-    for (int k = 0; k < 4; k++) red[k][threadIdx.x] = v[k];
-    __syncthreads();
-    for (int w2 = 128; w2 > 0; w2 >>= 1) {
-        if (threadIdx.x < w2)
+    for (int k = STAT ? 0 : 4; k < (LIGHT ? 8 : 4); k++) {
 #pragma unroll
-            for (int k = 0; k < 4; k++) red[k][threadIdx.x] += red[k][threadIdx.x + w2];
-        __syncthreads();
+        for (int m = 1; m < 64; m <<= 1) v[k] += __shfl_xor(v[k], m, 64);
+        if ((threadIdx.x & 63) == 0) red[k][threadIdx.x >> 6] = v[k];
     }
-    if (threadIdx.x < 4) partials[(size_t)blockIdx.x * 4 + threadIdx.x] = red[threadIdx.x][0];
+    __syncthreads();
+    const int k = threadIdx.x;
+    if (k < 8 && (k < 4 ? STAT : LIGHT))
+        (k < 4 ? part_s : part_l)[(size_t)blockIdx.x * 4 + (k & 3)] = (red[k][0] + red[k][1]) + (red[k][2] + red[k][3]);
 }
 
 // Diagnostics per site, reduced per workgroup in FP64:
@@ -322,20 +332,23 @@ hipError_t launch_field_step(hipStream_t st, int N, FieldPtrs<T> in, FieldPtrs<T
 }
 
 template <typename T>
-hipError_t launch_static_accum(hipStream_t st, int N, const T *F, double *I, double dtau, double *partials,
-                               int *n_blocks_out) {
-    const int nb = (int)(((size_t)N * N + 255) / 256);
-    *n_blocks_out = nb;
-    hipLaunchKernelGGL(k_static_accum<T>, dim3(nb), dim3(256), 0, st, N, F, I, dtau, partials);
-    return hipGetLastError();
-}
-
-template <typename T>
-hipError_t launch_lightlike_accum(hipStream_t st, int N, const T *F, const T *U, double *W, double *I, int64_t j,
-                                  double dtau, double *partials, int *n_blocks_out) {
-    const int nb = (int)(((size_t)N * N + 255) / 256);
-    *n_blocks_out = nb;
-    hipLaunchKernelGGL(k_lightlike_accum<T>, dim3(nb), dim3(256), 0, st, N, F, U, W, I, j, dtau, partials);
+hipError_t launch_correlators(hipStream_t st, int N, const T *F, const T *U, const CorrCall &c, double dtau,
+                              bool streamed) {
+    const dim3 blocks((unsigned)(((size_t)N * N + 255) / 256)), wg(256);
+#define GL_CORR(S, L, ST)                                                                                          \
+    hipLaunchKernelGGL((k_correlators<T, S, L, ST>), blocks, wg, 0, st, N, F, U, c.Is, c.W, c.Il, c.j, dtau, c.part_s, \
+                       c.part_l)
+    if (c.Is && c.Il) {
+        if (streamed) GL_CORR(true, true, true);
+        else GL_CORR(true, true, false);
+    } else if (c.Is) {
+        if (streamed) GL_CORR(true, false, true);
+        else GL_CORR(true, false, false);
+    } else {
+        if (streamed) GL_CORR(false, true, true);
+        else GL_CORR(false, true, false);
+    }
+#undef GL_CORR
     return hipGetLastError();
 }
 
@@ -353,9 +366,7 @@ hipError_t launch_diag(hipStream_t st, int N, FieldPtrs<T> f, double tau, double
                                              double, double, int, const KernelTimer &);      \
     template hipError_t launch_diag<T>(hipStream_t, int, FieldPtrs<T>, double, double *, int *);     \
     template hipError_t launch_check_finite<T>(hipStream_t, const T *, int64_t, int64_t, int, int *);   \
-    template hipError_t launch_static_accum<T>(hipStream_t, int, const T *, double *, double, double *, int *); \
-    template hipError_t launch_lightlike_accum<T>(hipStream_t, int, const T *, const T *, double *, double *, \
-                                                  int64_t, double, double *, int *);
+    template hipError_t launch_correlators<T>(hipStream_t, int, const T *, const T *, const CorrCall &, double, bool);
 // the FP64 instantiations come from fields_f64.hip, which includes this file
 // and is compiled with its own scheduling flag
 #ifdef GL_FIELDS_FP64

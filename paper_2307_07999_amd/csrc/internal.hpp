@@ -177,14 +177,20 @@ hipError_t launch_series_reduce_steps(hipStream_t st, const double *partials, si
 template <typename T>
 hipError_t launch_p0_sums(hipStream_t st, PartPtrs<T> p, int64_t n_slots, int n_species, double *partials,
                           double *out);
-// static-quark accumulators I [24][n2] FP64; partials [blocks][4]
+// one step of the field correlators (null Is or Il: that one is off):
+// static-quark accumulators Is [24][n2], lightlike-jet transports W [18][n2] and
+// accumulators Il [24][n2] at step j since their start, all FP64; partial rows
+// part_s, part_l [corr_blocks][4].  U: the x links at tau_n.  streamed: the arrays
+// overflow the last-level cache
+struct CorrCall {
+    double *Is, *W, *Il;
+    int64_t j;
+    double *part_s, *part_l;
+};
+inline int corr_blocks(size_t n2) { return (int)((n2 + 255) / 256); }
 template <typename T>
-hipError_t launch_static_accum(hipStream_t st, int N, const T *F, double *I, double dtau, double *partials,
-                               int *n_blocks_out);
-// lightlike-jet transports W [18][n2] and accumulators I [24][n2] FP64; U the x links at tau_n
-template <typename T>
-hipError_t launch_lightlike_accum(hipStream_t st, int N, const T *F, const T *U, double *W, double *I, int64_t j,
-                                  double dtau, double *partials, int *n_blocks_out);
+hipError_t launch_correlators(hipStream_t st, int N, const T *F, const T *U, const CorrCall &c, double dtau,
+                              bool streamed);
 template <typename T>
 hipError_t launch_diag(hipStream_t st, int N, FieldPtrs<T> f, double tau, double *partials,
                        int *n_blocks_out);

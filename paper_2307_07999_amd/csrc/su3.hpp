@@ -601,6 +601,18 @@ template <typename T>
 __device__ __forceinline__ void pl_st(T *p, size_t n2, int k, size_t x, T v) {
     bst(buf(p), (uint32_t)(x * sizeof(T)), (uint32_t)((size_t)k * n2 * sizeof(T)), v);
 }
+// the same with the cache policy CP, FP64
+template <int CP>
+__device__ __forceinline__ double pl_ld_p(const double *p, size_t n2, int k, size_t x) {
+    return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(buf(p), (uint32_t)(x * 8),
+                                                                           (uint32_t)((size_t)k * n2 * 8), CP));
+}
+template <int CP>
+__device__ __forceinline__ void pl_st_p(double *p, size_t n2, int k, size_t x, double v) {
+    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), buf(p), (uint32_t)(x * 8),
+                                          (uint32_t)((size_t)k * n2 * 8), CP);
+}
 // element x of a single array
 template <typename T>
 __device__ __forceinline__ T el_ld(const T *p, size_t x) {
