@@ -167,6 +167,30 @@ __device__ __forceinline__ void stage_biases(const NetView &v, float *bias) {
 
 __device__ __forceinline__ float silu(float v) { return v / (1.f + __expf(-v)); }
 
+// silu of four values.  For |v| <= 80 numerator and denominator (1 to 2^116)
+// need no scaling, and the division is the compiler's own sequence without its
+// three scaling instructions, rounded the same (a fifth of the vector time of
+// an activation); a wave with a larger value takes the division itself.
+__device__ __forceinline__ floatx4 silu4(floatx4 v) {
+    floatx4 h;
+    const float big = fmaxf(fmaxf(fabsf(v[0]), fabsf(v[1])), fmaxf(fabsf(v[2]), fabsf(v[3])));
+    if (__any(!(big <= 80.f))) {
+#pragma unroll
+        for (int j = 0; j < 4; j++) h[j] = silu(v[j]);
+        return h;
+    }
+#pragma unroll
+    for (int j = 0; j < 4; j++) {
+        const float d = 1.f + __expf(-v[j]);
+        float r = __builtin_amdgcn_rcpf(d);
+        r = fmaf(fmaf(-d, r, 1.f), r, r);
+        float q = v[j] * r;
+        q = fmaf(fmaf(-d, q, v[j]), r, q);
+        h[j] = fmaf(fmaf(-d, q, v[j]), r, q);
+    }
+    return h;
+}
+
 // four outputs of a lane as BF16 activations, zero beyond dout (whatever the
 // row holds: a non-finite activation must not reach a padded weight)
 __device__ __forceinline__ bf16x4 pack_act(floatx4 h, int o0, int dout) {
@@ -191,7 +215,7 @@ __device__ __forceinline__ bf16x4 *act_slot(bf16x8 *act, int ot, int lane) {
 // RT = 1, few rows: bound by latency, a chain of layers that each wait for their
 // weights; with the registers of one workgroup a compute unit, the next
 // layer's weights are loaded a whole layer ahead (AHEAD).
-// 5 -> 256 x 3 -> 2, against six launches per 4096 rows: 10^6 rows 20.5 -> 0.72 ms,
+// 5 -> 256 x 3 -> 2, against six launches per 4096 rows: 10^6 rows 20.5 -> 0.67 ms,
 // 410 rows 83 -> 11 us on the device.
 template <int RT, bool AHEAD>
 __global__ void __launch_bounds__(kRowThreads, AHEAD ? 2 : 4)
@@ -232,9 +256,7 @@ k_rows_infer(NetView v, const float *__restrict__ X, int64_t n, float *__restric
             const floatx4 b = *(const floatx4 *)(bias + l * kRowWidth + o);
 #pragma unroll
             for (int rt = 0; rt < RT; rt++) {
-                floatx4 h;
-#pragma unroll
-                for (int j = 0; j < 4; j++) h[j] = silu(acc[rt][k][j] + b[j]);
+                const floatx4 h = silu4(acc[rt][k] + b);
                 *act_slot(act[cur ^ 1] + rt * kStride, 2 * wave + k, lane) = pack_act(h, o, v.width);
             }
         }
@@ -294,7 +316,7 @@ k_rows_infer(NetView v, const float *__restrict__ X, int64_t n, float *__restric
 // BF16 weights (k_update).  Every sum runs in the order of the general
 // kernels (weight gradients over the rows in steps of 16, biases and loss
 // over 256 strided shares and a tree), so training is bitwise the same too.
-// A step of 4096 rows of 5 -> 256 x 3 -> 2: 1350 us in 20 launches, 46 us in two.
+// A step of 4096 rows of 5 -> 256 x 3 -> 2: 1350 us in 20 launches, 39 us in two.
 struct TrainView {
     const float *X, *Y;
     const int32_t *idx;                        // sample of each row, or null: off + row
@@ -353,6 +375,7 @@ __global__ void __launch_bounds__(kRowThreads, 2)
 k_rows_train(NetView v, TrainView a) {
     __shared__ bf16x8 act[2][kRowPairs * 64];
     __shared__ float bias[(DEPTH + 1) * kRowWidth];
+    __shared__ float target[16 * kRowWidth];
     const int t = threadIdx.x, wave = t >> 6, lane = t & 63;
     const int tile = blockIdx.x, row = 16 * tile + (lane & 15);
     const bool valid = row < a.B;
@@ -384,21 +407,16 @@ k_rows_train(NetView v, TrainView a) {
         }
         act[0][u] = x;
     }
-    // the lane's standardised targets
-    floatx4 y[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
-    if (valid && 2 * wave < v.ot_out) {
-        const int64_t s = a.idx ? (int64_t)a.idx[a.off + row] : a.off + row;
+    // the standardised targets, by the last waves while the first one gathers
+    // the inputs
+    for (int u = kRowThreads - 1 - t; u < 16 * v.n_out; u += kRowThreads) {
+        const int r = u / v.n_out, c = u - r * v.n_out;
+        if (16 * tile + r >= a.B) continue;
+        const int64_t s = a.idx ? (int64_t)a.idx[a.off + 16 * tile + r] : a.off + 16 * tile + r;
         const float *sc_out = v.sc + 2 * v.n_in;
-#pragma unroll
-        for (int k = 0; k < 2; k++)
-#pragma unroll
-            for (int j = 0; j < 4; j++) {
-                const int c = o0 + 16 * k + j;
-                if (c >= v.n_out) continue;
-                float q = a.Y[s * v.n_out + c];
-                if (v.pcol >= 0) q /= powf(a.X[s * v.n_in + v.pcol], sc_out[2 * v.n_out + c]);
-                y[k][j] = (q - sc_out[c]) / sc_out[v.n_out + c];
-            }
+        float q = a.Y[s * v.n_out + c];
+        if (v.pcol >= 0) q /= powf(a.X[s * v.n_in + v.pcol], sc_out[2 * v.n_out + c]);
+        target[r * kRowWidth + c] = (q - sc_out[c]) / sc_out[v.n_out + c];
     }
     __syncthreads();
     store_rows(act[0], in_blocks(v, 0), a.Hf + (size_t)tile * in_blocks(v, 0) * kGradBlock);
@@ -411,12 +429,8 @@ k_rows_train(NetView v, TrainView a) {
 #pragma unroll
         for (int k = 0; k < 2; k++) {
             const floatx4 b = *(const floatx4 *)(bias + l * kRowWidth + o0 + 16 * k);
-            floatx4 h;
-#pragma unroll
-            for (int j = 0; j < 4; j++) {
-                z[l][k][j] = acc[0][k][j] + b[j];
-                h[j] = silu(z[l][k][j]);
-            }
+            z[l][k] = acc[0][k] + b;
+            const floatx4 h = silu4(z[l][k]);
             *act_slot(act[cur ^ 1], 2 * wave + k, lane) = pack_act(h, o0 + 16 * k, valid ? v.width : 0);
         }
         cur ^= 1;
@@ -436,7 +450,7 @@ k_rows_train(NetView v, TrainView a) {
         for (int j = 0; j < 4; j++) {
             const int c = o0 + 16 * k + j;
             if (valid && c < v.n_out) {
-                const float zz = acc[0][k][j] + b[j], d = zz - y[k][j];
+                const float zz = acc[0][k][j] + b[j], d = zz - target[(lane & 15) * kRowWidth + c];
                 a.dev[(size_t)row * v.n_out + c] = d;
                 g[j] = 2.f * d * a.scale;
             }
@@ -485,11 +499,9 @@ __device__ __forceinline__ float adam(float w, float g, float *__restrict__ m, f
     return w - a.lr * (mi / a.c1) / (sqrtf(vi / a.c2) + a.eps);
 }
 
-// workgroups of k_update: four waves each form one 16 x 16 block of a layer's
+// workgroups (of one wave) of k_update: one per 16 x 16 block of a layer's
 // weights; then one per four biases; then one for the loss
-__host__ __device__ inline int weight_groups(const NetView &v, int l) {
-    return out_blocks(v, l) * ((in_blocks(v, l) + 3) / 4);
-}
+__host__ __device__ inline int weight_groups(const NetView &v, int l) { return out_blocks(v, l) * in_blocks(v, l); }
 __host__ __device__ inline int bias_groups(const NetView &v) { return v.depth * ((v.width + 3) / 4) + (v.n_out + 3) / 4; }
 
 // Gradients of one batch: dW[o][i] = sum over the rows of dZ[o] H[i], one chain
@@ -497,18 +509,21 @@ __host__ __device__ inline int bias_groups(const NetView &v) { return v.depth * 
 // dZ[o]; the loss.  Then Adam and the new weights in both fragment orders (G
 // null), or the gradients to G.
 //
-// Bound: by the operands' way from the other XCDs' writes through the last-level
-// cache (each block reads 16 KB per 256 rows, kUpdateAhead loads in flight
-// a wave).  Blocks are numbered so that each XCD takes one contiguous run
-// of them, a layer's rows of blocks one after another: its L2 then
-// holds the layer's H once and its own share of dZ, instead of all operands
-// passing through every L2.
-constexpr int kUpdateAhead = 16;
-__global__ void __launch_bounds__(256)
+// Bound: by the way of the operands (dZ and H of all layers, 15 MB at 4096 rows,
+// and 16 MB of FP32 dZ for the biases) from the other XCDs' L2 and by their
+// latency; the MFMA chain itself is under 2 us.  So every block is a workgroup of
+// one wave, which spreads the loads over all compute units, with kUpdateAhead row
+// tiles in flight, and the biases' shares are fetched 16 at a time: a step of 4096
+// rows of 5 -> 256 x 3 -> 2 took 22.7 us with four blocks and 16 tiles a workgroup,
+// 36 with single shares, 19.1 / 18.2 / 17.3 us with 16 / 24 / 32 tiles.  Blocks are
+// numbered so that each XCD takes one contiguous run of them, a layer's rows of
+// blocks one after another: its L2 then holds the layer's H once and its own share
+// of dZ, instead of all operands passing through every L2.
+constexpr int kUpdateAhead = 32;
+__global__ void __launch_bounds__(64)
 k_update(NetView v, TrainView a, float *__restrict__ P, float *__restrict__ Mo, float *__restrict__ Vo,
          float *__restrict__ G, float *__restrict__ loss, int tiles, AdamArgs aa) {
-    __shared__ floatx4 red[256];
-    const int t = threadIdx.x, lane = t & 63;
+    const int lane = threadIdx.x;
     int l = 0, q = 0, n_groups = 0;
     for (int k = 0; k <= v.depth; k++) n_groups += weight_groups(v, k);
     if ((int)blockIdx.x < n_groups) {
@@ -516,32 +531,45 @@ k_update(NetView v, TrainView a, float *__restrict__ P, float *__restrict__ Mo, 
         const int per = n_groups / 8, rem = n_groups % 8, x = blockIdx.x % 8, k = blockIdx.x / 8;
         q = x * per + min(x, rem) + k;
         while (q >= weight_groups(v, l)) q -= weight_groups(v, l++);
-        const int ni = in_blocks(v, l), no = out_blocks(v, l), cols = (ni + 3) / 4;
-        const int ob = q / cols, ib = 4 * (q % cols) + (t >> 6);
-        if (ib >= ni) return;
-        const bf16x4 *D = (const bf16x4 *)(a.Df + d_off(v, l, a.max_tiles)) + (size_t)ob * 64 + lane;
-        const bf16x4 *H = (const bf16x4 *)(a.Hf + h_off(v, l, a.max_tiles)) + (size_t)ib * 64 + lane;
-        floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+        const int ni = in_blocks(v, l), no = out_blocks(v, l);
+        const int ob = q / ni, ib = q % ni;
+        // tile b of the block's operands is `step` bytes after tile b - 1: a
+        // scalar base per group of tiles and a scalar offset per tile, since one
+        // wave a SIMD issues every address instruction itself
+        const uint32_t d_step = no * kGradBlock * sizeof(bf16), h_step = ni * kGradBlock * sizeof(bf16);
+        const char *D = (const char *)(a.Df + d_off(v, l, a.max_tiles)) + (size_t)ob * kGradBlock * sizeof(bf16);
+        const char *H = (const char *)(a.Hf + h_off(v, l, a.max_tiles)) + (size_t)ib * kGradBlock * sizeof(bf16);
         // the loads of the next kUpdateAhead row tiles fly while these are multiplied
         bf16x4 d[kUpdateAhead], h[kUpdateAhead];
-        auto load = [&](int u, int b) {
-            b = min(b, tiles - 1);
-            d[u] = D[(size_t)b * no * 64];
-            h[u] = H[(size_t)b * ni * 64];
+        auto base = [](const char *p) {
+            return __builtin_amdgcn_make_buffer_rsrc((void *)p, (short)0, 0x7FFFFFFF, 0x00020000);
         };
+        auto load = [&](int u, int left, __amdgpu_buffer_rsrc_t rd, __amdgpu_buffer_rsrc_t rh) {
+            const uint32_t w = min(u, left - 1);   // past the last tile: the last one again, not multiplied
+            d[u] = __builtin_bit_cast(bf16x4, __builtin_amdgcn_raw_buffer_load_b64(rd, 8 * lane, w * d_step, 0));
+            h[u] = __builtin_bit_cast(bf16x4, __builtin_amdgcn_raw_buffer_load_b64(rh, 8 * lane, w * h_step, 0));
+        };
+        floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+        {
+            const auto rd = base(D), rh = base(H);
 #pragma unroll
-        for (int u = 0; u < kUpdateAhead; u++) load(u, u);
-        int b = 0;
-        for (; b + kUpdateAhead <= tiles; b += kUpdateAhead) {
+            for (int u = 0; u < kUpdateAhead; u++) load(u, tiles, rd, rh);
+        }
+        int left = tiles - kUpdateAhead;   // tiles not loaded yet
+        for (; left > 0; left -= kUpdateAhead) {
+            D += (size_t)kUpdateAhead * d_step;
+            H += (size_t)kUpdateAhead * h_step;
+            const auto rd = base(D), rh = base(H);
 #pragma unroll
             for (int u = 0; u < kUpdateAhead; u++) {
                 acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(d[u], h[u], acc, 0, 0, 0);
-                load(u, b + kUpdateAhead + u);
+                load(u, left, rd, rh);
             }
         }
+        left += kUpdateAhead;              // tiles of the last group
 #pragma unroll
         for (int u = 0; u < kUpdateAhead; u++)
-            if (b + u < tiles) acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(d[u], h[u], acc, 0, 0, 0);
+            if (u < left) acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(d[u], h[u], acc, 0, 0, 0);
         const int di = layer_in(v, l), dd = layer_out(v, l), i = 16 * ib + (lane & 15);
 #pragma unroll
         for (int j = 0; j < 4; j++) {
@@ -558,39 +586,58 @@ k_update(NetView v, TrainView a, float *__restrict__ P, float *__restrict__ Mo, 
         }
         return;
     }
+    // the sums of biases and loss: 256 strided shares and a tree over them, four
+    // shares a lane
     q = (int)blockIdx.x - n_groups;
-    floatx4 s = {0.f, 0.f, 0.f, 0.f};
+    const int per_layer = (v.width + 3) / 4;
     const bool is_loss = q >= bias_groups(v);
-    const int o = 4 * (q % ((v.width + 3) / 4));
+    floatx4 s[4];
+#pragma unroll
+    for (int k = 0; k < 4; k++) s[k] = floatx4{0.f, 0.f, 0.f, 0.f};
+    l = min(q / per_layer, v.depth);
+    const int o = 4 * (q - l * per_layer), no = out_blocks(v, l);
     if (!is_loss) {
-        l = min(q / ((v.width + 3) / 4), v.depth);
-        const int oo = l < v.depth ? o : 4 * (q - v.depth * ((v.width + 3) / 4)), no = out_blocks(v, l);
-        const float *dz = a.Dz + d_off(v, l, a.max_tiles) + (size_t)(oo / 16) * kGradBlock +
-                          4 * ((t & 15) + 16 * (oo % 16 / 4));
-#pragma unroll 8
-        for (int b = t >> 4; b < tiles; b += 16) s += *(const floatx4 *)(dz + (size_t)b * no * kGradBlock);
+        // share m: rows m, m + 256, ...
+        const float *dz = a.Dz + d_off(v, l, a.max_tiles) + (size_t)(o / 16) * kGradBlock +
+                          4 * ((lane & 15) + 16 * (o % 16 / 4));
+        for (int b0 = 0; b0 < tiles; b0 += 64) {
+            floatx4 x[16];
+#pragma unroll
+            for (int k = 0; k < 16; k++) {
+                const int b = min(b0 + 4 * k + (lane >> 4), tiles - 1);
+                x[k] = *(const floatx4 *)(dz + (size_t)b * no * kGradBlock);
+            }
+#pragma unroll
+            for (int k = 0; k < 16; k++)
+                if (b0 + 4 * k + (lane >> 4) < tiles) s[k & 3] += x[k];
+        }
     } else {
         const int count = a.B * v.n_out;
-#pragma unroll 8
-        for (int i = t; i < count; i += 256) s[0] += a.dev[i] * a.dev[i];
+        for (int i0 = 0; i0 < count; i0 += 2048) {
+            float x[32];
+#pragma unroll
+            for (int k = 0; k < 32; k++) x[k] = a.dev[min(i0 + 64 * k + lane, count - 1)];
+#pragma unroll
+            for (int k = 0; k < 32; k++)
+                if (i0 + 64 * k + lane < count) s[k & 3][0] += x[k] * x[k];
+        }
     }
-    red[t] = s;
-    __syncthreads();
-    for (int m = 128; m > 0; m >>= 1) {
-        if (t < m) red[t] += red[t + m];
-        __syncthreads();
-    }
+    floatx4 r = (s[0] + s[2]) + (s[1] + s[3]);
+#pragma unroll
+    for (int m = 32; m > 0; m >>= 1)
+#pragma unroll
+        for (int j = 0; j < 4; j++) r[j] += __shfl_down(r[j], m, 64);
     if (is_loss) {
-        if (t == 0) *loss += red[0][0] * a.scale;
+        if (lane == 0) *loss += r[0] * a.scale;
         return;
     }
-    const int c = (l < v.depth ? o : 4 * (q - v.depth * ((v.width + 3) / 4))) + t;
-    if (t < 4 && c < layer_out(v, l)) {
-        const int64_t p = v.n_w + (int64_t)l * v.width + c;
-        const float g = red[0][t];
-        if (G) G[p] = g;
-        else P[p] = adam(P[p], g, Mo, Vo, p, aa);
-    }
+#pragma unroll
+    for (int j = 0; j < 4; j++)
+        if (lane == 0 && o + j < layer_out(v, l)) {
+            const int64_t p = v.n_w + (int64_t)l * v.width + o + j;
+            if (G) G[p] = r[j];
+            else P[p] = adam(P[p], r[j], Mo, Vo, p, aa);
+        }
 }
 
 }  // namespace
