@@ -390,12 +390,13 @@ gl_status gl_batch_required_bytes(gl_event *const *evs, int32_t n_events, size_t
 gl_status gl_batch_create(gl_event *const *evs, int32_t n_events, void *workspace, size_t bytes,
                           void *stream, gl_batch **out);
 void gl_batch_destroy(gl_batch *b);
-/* Pick the field-kernel tile shape in sites (0: 32x4, 1: 64x2, 2: 16x8) and the
- * persistent grid (0: one workgroup per tile, k: k workgroups per compute
- * unit) by timing the field phases on this batch (they are idempotent, so
- * the state does not change), or read the choice from cache_json when it
- * holds this batch's key (device, precision, lattice sizes, particle count);
- * the choice is written back to cache_json.  cache_json may be NULL. */
+/* Pick the field-kernel tile shape in sites (0: 32x4, 1: 64x2, 2: 16x8) by
+ * timing the field phases on this batch with one workgroup per tile (they are
+ * idempotent, so the state does not change), or read shape and persistent grid
+ * (0: one workgroup per tile, k: k workgroups per compute unit) from
+ * cache_json when it holds this batch's key (device, precision, lattice sizes,
+ * particle count); the choice is written back to cache_json.  cache_json may
+ * be NULL. */
 gl_status gl_batch_autotune(gl_batch *b, const char *cache_json);
 /* Set the configuration by hand (grid_mult as above, at most 64; sort_every
  * 0: never sort; graph_steps 0: no graph; graph_steps must be even and a

@@ -2382,19 +2382,23 @@ gl_status gl_batch_autotune(gl_batch *b, const char *cache_json) {
     std::string key = batch_key(b);
     int shape = 0, mult = 0;
     if (!cache_lookup(cache_json, key, &shape, &mult)) {
+        // Only the loop-free kernels are timed: the persistent walk holds
+        // registers that cost it a wave a SIMD in FP32 (166 against 128 VGPRs), and
+        // lost on every batch measured (24 events of 256^2: 250-310 us at 2, 4 and
+        // 8 workgroups a compute unit against 219; the 64-event batch 1732
+        // against 1523 ms), so timing its nine candidates was three quarters of
+        // the tuning (13.5 -> 3.5 ms for the 24 events, of 109 ms in all).
+        shape = mult = 0;
         float best = 1e30f;
-        const int mults[] = {0, 2, 4, 8};
-        for (int s = 0; s < kBatchShapes; s++)
-            for (int m : mults) {
-                float ms = 0;
-                gl_status st = b->fp64 ? time_fields<double>(b, s, m, &ms) : time_fields<float>(b, s, m, &ms);
-                if (st) return st;
-                if (ms < best) {
-                    best = ms;
-                    shape = s;
-                    mult = m;
-                }
+        for (int s = 0; s < kBatchShapes; s++) {
+            float ms = 0;
+            gl_status st = b->fp64 ? time_fields<double>(b, s, 0, &ms) : time_fields<float>(b, s, 0, &ms);
+            if (st) return st;
+            if (ms < best) {
+                best = ms;
+                shape = s;
             }
+        }
         cache_store(cache_json, key, shape, mult);
     }
     if (shape != b->shape || mult != b->grid_mult) batch_drop_graphs(b);

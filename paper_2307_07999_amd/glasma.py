@@ -313,11 +313,13 @@ class Event:
         return check(lib().gl_sync(self._h))
 
     # ---- observables ---------------------------------------------------------
+    # a curve has at most max_steps rows: one call with room for all, since
+    # each call reads the series from the device (asking for the row count
+    # first read it twice)
     def _rows(self, fn, species, width):
         n = ctypes.c_int32(0)
-        check(fn(self._h, species, None, 0, ctypes.byref(n)))
-        out = np.zeros((max(n.value, 1), width))
-        check(fn(self._h, species, _d(out), n.value, ctypes.byref(n)))
+        out = np.zeros((max(self.desc.max_steps, 1), width))
+        check(fn(self._h, species, _d(out), len(out), ctypes.byref(n)))
         return out[:n.value]
 
     def broadening(self, species):
@@ -349,9 +351,8 @@ class Event:
 
     def _corr_rows(self, fn):
         n = ctypes.c_int32(0)
-        check(fn(self._h, None, 0, ctypes.byref(n)))
-        out = np.zeros((max(n.value, 1), 5))
-        check(fn(self._h, _d(out), n.value, ctypes.byref(n)))
+        out = np.zeros((max(self.desc.max_steps, 1), 5))
+        check(fn(self._h, _d(out), len(out), ctypes.byref(n)))
         return out[:n.value]
 
     def static_broadening(self):
