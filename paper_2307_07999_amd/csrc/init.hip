@@ -31,6 +31,7 @@ namespace gl {
 // colours 2j, 2j + 1 of the charge of one sheet at site x: one counter-based
 // draw, two normal deviates, scaled by sigma
 __device__ __forceinline__ double2 mv_charge_pair(const MvDraw &mv, int nucleus, int sheet, int j, size_t x) {
+#pragma clang fp contract(off)   // the charge itself, also where the transform's sums follow
     U4 w = draw(mv.seed, (uint32_t)x, (uint32_t)(4 * sheet + j), (uint32_t)nucleus);
     double g0, g1;
     box_muller(w, g0, g1);
@@ -78,26 +79,31 @@ k_unpack(int N, const double2 *planes, double *rho) {
 // ---- 2. FFT ------------------------------------------------------------------
 constexpr int kFftThreads = 256;
 constexpr int kFftMaxN = 1024;
+constexpr int kFftStaged = kFftMaxN + kFftMaxN / 2;   // stages' twiddles, after tw and s2 in the table
 constexpr int kFftElems = 2048;   // complex values per workgroup: C lines of N
 
 __device__ __forceinline__ double2 cmul(double2 a, double2 b) {
-    return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
+#pragma clang fp contract(off)   // this order whatever the compiler knows of b's sign
+    return make_double2(__builtin_fma(a.x, b.x, -(a.y * b.y)), __builtin_fma(a.y, b.x, a.x * b.y));
 }
 
 // One stage of the transform of N: radix, butterflies per line, values per
-// transform before it and twiddle step, with what divides an index below
-// kFftElems by nb and Ns: a shift (N a power of two), or the multiplier m of
-// t / d = t m >> 21, m = ceil(2^21 / d), exact for t < 2048 and d <= 1024.
+// transform before it and where its twiddles start in the table, with what
+// divides an index below kFftElems by nb and Ns: a shift (N a power of two), or
+// the multiplier m of t / d = t m >> 21, m = ceil(2^21 / d), exact for t < 2048
+// and d <= 1024.
 struct FftStage {
-    int R, nb, Ns, step;
+    int R, nb, Ns, tw;
     uint32_t nb_m, Ns_m;
 };
 constexpr int kFftMaxStages = 8;
 
 // The transform of N = 2^a 3^b: radix-8 stages, then at most one radix-4 or
-// radix-2, then radix-3.  2^log_c lines a workgroup, ls LDS elements apart.
+// radix-2, then radix-9 (two radix-3 stages in registers) and at most one
+// radix-3.  2^log_c lines a workgroup, ls LDS elements apart.
 struct FftPlan {
     int stages, log_c, ls;
+    int n_tw;                     // twiddles of all stages, < N
     uint32_t n_m;                 // divides by N
     bool p2;                      // N is a power of two
     FftStage st[kFftMaxStages];
@@ -116,11 +122,14 @@ static bool fft_plan(int N, FftPlan &p) {
         return s;
     };
     p.stages = 0;
+    p.n_tw = 0;
     int m = N, Ns = 1;
-    for (int R : {8, 4, 2, 3})
+    for (int R : {8, 4, 2, 9, 3})
         while (m % R == 0) {
             if (p.stages == kFftMaxStages) return false;
-            p.st[p.stages++] = FftStage{R, N / R, Ns, N / (Ns * R), divider(N / R), divider(Ns)};
+            p.st[p.stages++] = FftStage{R, N / R, Ns, p.n_tw, divider(N / R), divider(Ns)};
+            // none in the first stage; radix 9: those of both radix-3 stages
+            p.n_tw += R == 9 ? (Ns > 1 ? 8 * Ns : 6 * Ns) : Ns > 1 ? (R - 1) * Ns : 0;
             m /= R;
             Ns *= R;
         }
@@ -181,154 +190,282 @@ __device__ __forceinline__ void butterfly(const double2 *v, double2 *o, int sign
         double2 t = make_double2(v[1].x + v[2].x, v[1].y + v[2].y);
         double2 u = make_double2(v[1].x - v[2].x, v[1].y - v[2].y);
         o[0] = make_double2(v[0].x + t.x, v[0].y + t.y);
-        double2 m = make_double2(v[0].x + c3 * t.x, v[0].y + c3 * t.y);
-        double2 iu = make_double2(-s3 * u.y, s3 * u.x);   // s3 * i * u
-        o[1] = make_double2(m.x + iu.x, m.y + iu.y);
-        o[2] = make_double2(m.x - iu.x, m.y - iu.y);
+        // fused by hand: which product joins a sum is otherwise the compiler's
+        // choice, and differs between the stages this is inlined in
+        const double2 m = make_double2(__builtin_fma(c3, t.x, v[0].x), __builtin_fma(c3, t.y, v[0].y));
+        o[1] = make_double2(__builtin_fma(-s3, u.y, m.x), __builtin_fma(s3, u.x, m.y));
+        o[2] = make_double2(__builtin_fma(s3, u.y, m.x), __builtin_fma(-s3, u.x, m.y));
     }
 }
 
-// One Stockham stage of radix R on the C lines of N values in buf (in place:
-// every thread reads its butterflies into registers, the workgroup
-// synchronises, then the results are written).  Twiddle of (r, k) is
-// tw[r k N / (Ns R)]; in the first stage (Ns = 1) all are 1.
-template <int R, bool P2>
-__device__ __forceinline__ void fft_stage(double2 *buf, const double2 *tw, int C, int ls, const FftStage &s, int sign) {
-    // tw holds exp(-2 pi i j / N); the inverse uses its conjugate
+// Radix-R butterfly of a stage with its twiddles, tw[(r - 1) Ns + k] that of
+// (r, k): consecutive lanes read consecutive values, where the table
+// exp(-2 pi i j / N) itself was read at strides that met the same banks.  The
+// first stage's (Ns = 1) are all 1.  tw holds the forward transform's; the
+// inverse uses their conjugates.  Radix 9 is a radix-3 stage and the next one,
+// the second's inputs taken from registers: the same operations as the two.
+template <int R, bool FIRST>
+__device__ __forceinline__ void twiddled(double2 *v, double2 *o, const double2 *tw, int Ns, int k, int sign) {
+    auto turn = [&](double2 &x, int at) {
+        double2 w = tw[at];
+        if (sign > 0) w.y = -w.y;
+        x = cmul(x, w);
+    };
+    if constexpr (R == 9) {
+        double2 z[3][3];
+#pragma unroll
+        for (int m = 0; m < 3; m++) {
+            double2 a[3] = {v[m], v[m + 3], v[m + 6]}, b[3];
+            if constexpr (!FIRST) {
+                turn(a[1], k);
+                turn(a[2], Ns + k);
+            }
+            butterfly<3>(a, b, sign);
+#pragma unroll
+            for (int r = 0; r < 3; r++) z[r][m] = b[r];
+        }
+        const double2 *tw2 = FIRST ? tw : tw + 2 * Ns;
+        auto turn2 = [&](double2 &x, int at) {
+            double2 w = tw2[at];
+            if (sign > 0) w.y = -w.y;
+            x = cmul(x, w);
+        };
+#pragma unroll
+        for (int r = 0; r < 3; r++) {
+            double2 b[3];
+            turn2(z[r][1], k + r * Ns);
+            turn2(z[r][2], 3 * Ns + k + r * Ns);
+            butterfly<3>(z[r], b, sign);
+#pragma unroll
+            for (int q = 0; q < 3; q++) o[r + 3 * q] = b[q];
+        }
+    } else {
+        if constexpr (!FIRST)
+#pragma unroll
+            for (int r = 1; r < R; r++) turn(v[r], (r - 1) * Ns + k);
+        butterfly<R>(v, o, sign);
+    }
+}
+
+// What a stage's values come from and go to: in(line, i) and out(line, i, v).
+// SYNC: both are the LDS lines, so the workgroup synchronises between.  FAST:
+// lanes run over the lines first (global columns) instead of along a line.
+template <int R, bool FIRST, bool FAST, bool SYNC, bool P2, class In, class Out>
+__device__ __forceinline__ void fft_stage(const double2 *tw, int C, const FftPlan &p, const FftStage &s, int sign,
+                                          In in, Out out) {
     constexpr int B = (kFftElems / R + kFftThreads - 1) / kFftThreads;   // butterflies per thread
-    const int total = C * s.nb;
-    double2 o[B][R];
-    int at[B];
+    double2 v[B][R];
+    int line[B], j[B];
 #pragma unroll
     for (int b = 0; b < B; b++) {
         const int t = threadIdx.x + b * kFftThreads;
-        at[b] = -1;
-        if (t < total) {
-            const int line = fft_div<P2>(t, s.nb_m), j = t - line * s.nb;
-            const double2 *in = buf + line * ls;
-            double2 v[R];
+        if constexpr (FAST) {
+            line[b] = t & ((1 << p.log_c) - 1);
+            j[b] = t >> p.log_c;
+            if (line[b] >= C || j[b] >= s.nb) line[b] = -1;
+        } else {
+            line[b] = fft_div<P2>(t, s.nb_m);
+            j[b] = t - line[b] * s.nb;
+            if (line[b] >= C) line[b] = -1;
+        }
+        if (line[b] >= 0)
 #pragma unroll
-            for (int r = 0; r < R; r++) v[r] = in[fft_pad(j + r * s.nb)];
-            int q = j, k = 0;
-            if (s.Ns > 1) {
-                q = fft_div<P2>(j, s.Ns_m);
-                k = j - q * s.Ns;
+            for (int r = 0; r < R; r++) v[b][r] = in(line[b], j[b] + r * s.nb);
+    }
+    // radix 9 has twiddles in the first stage too: the table must have arrived
+    if constexpr (SYNC || (FIRST && R == 9)) __syncthreads();
 #pragma unroll
-                for (int r = 1; r < R; r++) {
-                    double2 w = tw[r * k * s.step];
-                    if (sign > 0) w.y = -w.y;
-                    v[r] = cmul(v[r], w);
-                }
-            }
-            butterfly<R>(v, o[b], sign);
-            at[b] = line * ls * 2048 + q * s.Ns * R + k;   // line start and place in the line
+    for (int b = 0; b < B; b++)
+        if (line[b] >= 0) {
+            const int q = FIRST ? j[b] : fft_div<P2>(j[b], s.Ns_m), k = FIRST ? 0 : j[b] - q * s.Ns;
+            double2 o[R];
+            twiddled<R, FIRST>(v[b], o, tw + s.tw, s.Ns, k, sign);
+#pragma unroll
+            for (int r = 0; r < R; r++) out(line[b], q * s.Ns * R + k + r * s.Ns, o[r]);
+        }
+}
+
+template <bool FIRST, bool FAST, bool SYNC, bool P2, class In, class Out>
+__device__ __forceinline__ void fft_stage_any(const double2 *tw, int C, const FftPlan &p, int s, int sign, In in,
+                                              Out out) {
+    const FftStage &st = p.st[s];
+    if (st.R == 8) fft_stage<8, FIRST, FAST, SYNC, P2>(tw, C, p, st, sign, in, out);
+    else if (st.R == 4) fft_stage<4, FIRST, FAST, SYNC, P2>(tw, C, p, st, sign, in, out);
+    else if (P2 || st.R == 2) fft_stage<2, FIRST, FAST, SYNC, P2>(tw, C, p, st, sign, in, out);
+    else if constexpr (!P2) {
+        if (st.R == 9) fft_stage<9, FIRST, FAST, SYNC, P2>(tw, C, p, st, sign, in, out);
+        else fft_stage<3, FIRST, FAST, SYNC, P2>(tw, C, p, st, sign, in, out);
+    }
+}
+
+// The last stage of the forward transform, f(line, i, v) on its results and the
+// first stage of the inverse, for a plan whose first and last radix are the
+// same: a butterfly's results are then the inputs of the inverse's butterfly
+// of the same index, and stay in registers.
+template <int R, bool P2, class F>
+__device__ __forceinline__ void fft_turn(double2 *buf, const double2 *tw, int C, const FftPlan &p, F f) {
+    constexpr int B = (kFftElems / R + kFftThreads - 1) / kFftThreads;
+    const FftStage &s = p.st[p.stages - 1];              // Ns = nb: q = 0, k = j
+    double2 o[B][R];
+    int line[B], j[B];
+#pragma unroll
+    for (int b = 0; b < B; b++) {
+        const int t = threadIdx.x + b * kFftThreads;
+        line[b] = fft_div<P2>(t, s.nb_m);
+        j[b] = t - line[b] * s.nb;
+        if (line[b] >= C) line[b] = -1;
+        if (line[b] >= 0) {
+            double2 v[R], u[R];
+#pragma unroll
+            for (int r = 0; r < R; r++) v[r] = buf[line[b] * p.ls + fft_pad(j[b] + r * s.nb)];
+            twiddled<R, false>(v, u, tw + s.tw, s.Ns, j[b], -1);
+#pragma unroll
+            for (int r = 0; r < R; r++) u[r] = f(line[b], j[b] + r * s.nb, u[r]);
+            twiddled<R, true>(u, o[b], tw + p.st[0].tw, 1, 0, +1);
         }
     }
     __syncthreads();
 #pragma unroll
     for (int b = 0; b < B; b++)
-        if (at[b] >= 0) {
-            double2 *out = buf + (at[b] >> 11);
-            const int i = at[b] & 2047;
+        if (line[b] >= 0)
 #pragma unroll
-            for (int r = 0; r < R; r++) out[fft_pad(i + r * s.Ns)] = o[b][r];
-        }
+            for (int r = 0; r < R; r++) buf[line[b] * p.ls + fft_pad(j[b] * R + r)] = o[b][r];
     __syncthreads();
 }
 
+// stages first .. end - 1 (not the first of the transform) on the LDS lines
 template <bool P2>
-__device__ __forceinline__ void fft_stages(double2 *buf, const double2 *tw, int C, int sign, const FftPlan &p) {
-    for (int s = 0; s < p.stages; s++) {
-        const FftStage &st = p.st[s];
-        if (st.R == 8) fft_stage<8, P2>(buf, tw, C, p.ls, st, sign);
-        else if (st.R == 4) fft_stage<4, P2>(buf, tw, C, p.ls, st, sign);
-        else if (st.R == 2) fft_stage<2, P2>(buf, tw, C, p.ls, st, sign);
-        else fft_stage<3, P2>(buf, tw, C, p.ls, st, sign);
+__device__ __forceinline__ void fft_stages(double2 *buf, const double2 *tw, int C, int sign, const FftPlan &p,
+                                           int first, int end) {
+    auto in = [&](int line, int i) { return buf[line * p.ls + fft_pad(i)]; };
+    auto out = [&](int line, int i, double2 v) { buf[line * p.ls + fft_pad(i)] = v; };
+    for (int s = first; s < end; s++) {
+        fft_stage_any<false, false, true, P2>(tw, C, p, s, sign, in, out);
+        __syncthreads();
     }
 }
 
 // Tables of one solve, filled once: tw[j] = exp(-2 pi i j / N) and
-// s2[j] = 4 sin^2(pi j / N), j < N.
-__global__ void __launch_bounds__(256)
-k_fft_tables(int N, double2 *__restrict__ tw, double *__restrict__ s2) {
-    const int j = blockIdx.x * 256 + threadIdx.x;
-    if (j >= N) return;
+// s2[j] = 4 sin^2(pi j / N), j < N, and the stages' twiddles in their own order.
+__device__ __forceinline__ double2 unit_root(int j, int N) {
     double sn, cs;
     sincospi(2.0 * (double)j / (double)N, &sn, &cs);
-    tw[j] = make_double2(cs, -sn);
+    return make_double2(cs, -sn);
+}
+__global__ void __launch_bounds__(256)
+k_fft_tables(int N, FftPlan p, double2 *__restrict__ tw, double *__restrict__ s2, double2 *__restrict__ staged) {
+    const int j = blockIdx.x * 256 + threadIdx.x;
+    if (j >= N) return;
+    tw[j] = unit_root(j, N);
     const double h = sinpi((double)j / (double)N);
     s2[j] = 4.0 * h * h;
+    if (j >= p.n_tw) return;
+    int s = p.stages - 1;
+    while (p.st[s].tw > j) s--;
+    int R = p.st[s].R, Ns = p.st[s].Ns, e = j - p.st[s].tw;
+    if (R == 9) {
+        const int n1 = Ns > 1 ? 2 * Ns : 0;              // the first of its radix-3 stages, then the second
+        R = 3;
+        if (e >= n1) {
+            e -= n1;
+            Ns *= 3;
+        }
+    }
+    staged[j] = unit_root((e / Ns + 1) * (e % Ns) * (N / (Ns * R)), N);
 }
 
 // In-place transforms of the N x N planes: each workgroup transforms C
-// adjacent lines of one plane (rows if cols == 0, columns otherwise), with
-// the twiddles exp(-2 pi i j / N) copied from the solve's table into LDS.  Loads
-// and stores walk the C lines together, so a column workgroup reads C
-// consecutive values of each row.  sign = -1 forward, +1 inverse
-// (unnormalised).  MODE kFftPoisson (columns only, after the forward row
-// pass): the forward column transform, the multiplication of mode (kx, ky)
-// by 1 / (N^2 (4 sin^2(pi kx/N) + 4 sin^2(pi ky/N) + m2)) (zero above
-// uv2 > 0) and the inverse column transform, in one pass.  MODE kFftDraw
-// (forward rows): the input lines are the MV charges, drawn here instead of
-// being written to the planes by a pass of their own and read back.  Planes
-// are [nucleus][sheet][4], mv.sheets sheets of each nucleus.
+// adjacent lines of one plane (rows, or columns in MODE kFftPoisson), the
+// twiddles copied from the solve's table into LDS.  The first stage takes its
+// values from global memory (rows along the lines; columns C consecutive values
+// of each row) and the last writes its results there, so LDS holds them only
+// between stages.  sign = -1 forward, +1 inverse (unnormalised).  MODE
+// kFftPoisson (after the forward row pass): the forward column transform, the
+// multiplication of mode (kx, ky) by 1 / (N^2 (4 sin^2(pi kx/N) + 4 sin^2(pi
+// ky/N) + m2)) (zero above uv2 > 0) and the inverse column transform, in one
+// pass.  MODE kFftDraw (forward rows): the input lines are the MV charges, drawn
+// here instead of being written to the planes by a pass of their own and read
+// back.  Planes are [nucleus][sheet][4], mv.sheets sheets of each nucleus.
+//
+// Bound: by LDS and its latency (values in and out at every stage, and their
+// twiddles); the inverse row pass is at 7 TB/s with what it reads and writes.
+// Of 16 LDS passes of a column of 512 values (in, three stages forward, product,
+// three back, out) the direct ends, and the last stage forward, the product and
+// the first back in registers, leave 8; and the staged twiddles meet no bank
+// twice.  Eight sheets of 512^2, 134 MB of planes: columns 84 -> 57 us, inverse
+// rows 48 -> 38, forward rows with the draw 85 -> 78 (bound by the draw's
+// arithmetic: 172 FP64 instructions a pair, most of them the logarithm's and the
+// sine's).  3^5, both nuclei and 17 sheets: columns 136 -> 83.
 constexpr int kFftLines = 0, kFftPoisson = 1, kFftDraw = 2;
 template <int MODE, bool P2>
 __global__ void __launch_bounds__(kFftThreads)
-k_fft_lines(double2 *data, int N, int cols, int groups_per_plane, int sign, FftPlan fp, double m2, double uv2,
+k_fft_lines(double2 *data, int N, int groups_per_plane, int sign, FftPlan fp, double m2, double uv2,
             const double2 *__restrict__ tw_tab, const double *__restrict__ s2_tab, MvDraw mv) {
     constexpr bool POISSON = MODE == kFftPoisson;
-    // dynamic LDS sized for this N: the lines, then tw[N], then (POISSON) s2[N]
+    // dynamic LDS sized for this N: the lines, then tw, then (POISSON) s2[N]
     extern __shared__ double2 lds[];
     double2 *buf = lds, *tw = lds + (fp.ls << fp.log_c);
-    double *s2 = (double *)(tw + N);
+    double *s2 = (double *)(tw + fp.n_tw);
     // contiguous runs of groups per XCD: the C-wide column segments of
     // neighbouring groups share cache lines, which then meet in one L2
     const int bid = (int)xcd_remap(blockIdx.x, gridDim.x);
     const int plane = bid / groups_per_plane, l0 = (bid - plane * groups_per_plane) << fp.log_c;
-    const int C = min(1 << fp.log_c, N - l0);
+    const int C = min(1 << fp.log_c, N - l0), last = fp.stages - 1;
     double2 *base = data + (size_t)plane * N * N;
-    for (int j = threadIdx.x; j < N; j += kFftThreads) {
-        tw[j] = tw_tab[j];
-        if (POISSON) s2[j] = s2_tab[j];
-    }
-    // calls f(LDS element, address) for the thread's values of the C lines
-    auto walk = [&](auto f) {
-        if (cols) {
-            for (int i = threadIdx.x; i < N << fp.log_c; i += kFftThreads) {
-                const int line = i & ((1 << fp.log_c) - 1), k = i >> fp.log_c;
-                if (line < C) f(line * fp.ls + fft_pad(k), (size_t)k * N + (l0 + line));
-            }
-        } else {
-            for (int i = threadIdx.x; i < C * N; i += kFftThreads) {
-                const int line = fft_div<P2>(i, fp.n_m), k = i - line * N;
-                f(line * fp.ls + fft_pad(k), (size_t)l0 * N + i);
-            }
-        }
+    for (int j = threadIdx.x; j < fp.n_tw; j += kFftThreads) tw[j] = tw_tab[j];
+    if constexpr (POISSON)
+        for (int j = threadIdx.x; j < N; j += kFftThreads) s2[j] = s2_tab[j];
+    auto from_lds = [&](int line, int i) { return buf[line * fp.ls + fft_pad(i)]; };
+    auto to_lds = [&](int line, int i, double2 v) { buf[line * fp.ls + fft_pad(i)] = v; };
+    auto place = [&](int line, int i) {
+        return POISSON ? (uint32_t)(i * N + (l0 + line)) : (uint32_t)((l0 + line) * N + i);
     };
     const int sheet = plane / 4;
-    walk([&](int at, size_t addr) {
+    auto input = [&](int line, int i) {
         if constexpr (MODE == kFftDraw)
-            buf[at] = mv_charge_pair(mv, mv.nucleus + sheet / mv.sheets, mv.sheet0 + sheet % mv.sheets, plane % 4, addr);
-        else buf[at] = base[addr];
-    });
-    __syncthreads();
-    if (POISSON) {
-        fft_stages<P2>(buf, tw, C, -1, fp);
+            return mv_charge_pair(mv, mv.nucleus + sheet / mv.sheets, mv.sheet0 + sheet % mv.sheets, plane % 4,
+                                  place(line, i));
+        else return base[place(line, i)];
+    };
+    auto output = [&](int line, int i, double2 v) { base[place(line, i)] = v; };
+    if constexpr (POISSON) {
         const double nn = (double)N * (double)N;
-        for (int i = threadIdx.x; i < C * N; i += kFftThreads) {
-            const int line = fft_div<P2>(i, fp.n_m), k = i - line * N;   // kx = l0 + line, ky = k
-            const double k2 = s2[l0 + line] + s2[k];
+        auto poisson = [&](int line, int i, double2 v) {                 // kx = l0 + line, ky = i
+#pragma clang fp contract(off)                                           // a product of its own, also before a sum
+            const double k2 = s2[l0 + line] + s2[i];
             const double gk = (uv2 > 0.0 && k2 > uv2) ? 0.0 : 1.0 / (nn * (k2 + m2));
-            double2 &v = buf[line * fp.ls + fft_pad(k)];
-            v = make_double2(v.x * gk, v.y * gk);
-        }
+            return make_double2(v.x * gk, v.y * gk);
+        };
+        auto scaled = [&](int line, int i, double2 v) { to_lds(line, i, poisson(line, i, v)); };
+        fft_stage_any<true, true, false, P2>(tw, C, fp, 0, -1, input, to_lds);
         __syncthreads();
-        fft_stages<P2>(buf, tw, C, +1, fp);
+        fft_stages<P2>(buf, tw, C, -1, fp, 1, last);
+        const bool same = last > 0 && fp.st[last].R == fp.st[0].R;
+        if (same && fp.st[0].R == 8) fft_turn<8, P2>(buf, tw, C, fp, poisson);
+        else if (!P2 && same && fp.st[0].R == 9) fft_turn<9, P2>(buf, tw, C, fp, poisson);
+        else {
+            // the results to LDS, scaled, and back for the inverse's first stage
+            if (last > 0) fft_stage_any<false, false, true, P2>(tw, C, fp, last, -1, from_lds, scaled);
+            else
+                for (int t = threadIdx.x; t < C * N; t += kFftThreads) {
+                    const int line = fft_div<P2>(t, fp.n_m), i = t - line * N;
+                    scaled(line, i, from_lds(line, i));
+                }
+            __syncthreads();
+            if (last > 0) fft_stage_any<true, false, true, P2>(tw, C, fp, 0, +1, from_lds, to_lds);
+            else fft_stage_any<true, true, false, P2>(tw, C, fp, 0, +1, from_lds, output);
+            __syncthreads();
+        }
+        fft_stages<P2>(buf, tw, C, +1, fp, 1, last);
+        if (last > 0) fft_stage_any<false, true, false, P2>(tw, C, fp, last, +1, from_lds, output);
+    } else if (last == 0) {
+        fft_stage_any<true, false, false, P2>(tw, C, fp, 0, sign, input, output);
     } else {
-        fft_stages<P2>(buf, tw, C, sign, fp);
+        fft_stage_any<true, false, false, P2>(tw, C, fp, 0, sign, input, to_lds);
+        __syncthreads();
+        fft_stages<P2>(buf, tw, C, sign, fp, 1, last);
+        fft_stage_any<false, false, false, P2>(tw, C, fp, last, sign, from_lds, output);
     }
-    walk([&](int at, size_t addr) { base[addr] = buf[at]; });
 }
 
 // ---- 3. Wilson lines --------------------------------------------------------
@@ -392,21 +529,17 @@ k_dipole_lines(const double *__restrict__ V, int N, FftPlan fp, const double2 *_
     const int entry = blockIdx.y % 9, l0 = blockIdx.x << fp.log_c, C = min(1 << fp.log_c, N - l0);
     const bool cols = blockIdx.y >= 9;
     const double *re = V + (size_t)(2 * entry) * n2, *im = re + n2;
-    for (int j = threadIdx.x; j < N; j += kFftThreads) tw[j] = tw_tab[j];
-    for (int i = threadIdx.x; i < N << fp.log_c; i += kFftThreads) {
-        int line, k;
-        if (cols) {
-            line = i & ((1 << fp.log_c) - 1);
-            k = i >> fp.log_c;
-        } else {
-            line = fft_div<P2>(i, fp.n_m);
-            k = i - line * N;
-        }
-        const size_t addr = cols ? (size_t)k * N + (l0 + line) : (size_t)l0 * N + i;
-        if (line < C) buf[line * fp.ls + fft_pad(k)] = make_double2(re[addr], im[addr]);
-    }
+    for (int j = threadIdx.x; j < fp.n_tw; j += kFftThreads) tw[j] = tw_tab[j];
+    auto to_lds = [&](int line, int i, double2 v) { buf[line * fp.ls + fft_pad(i)] = v; };
+    auto entry_at = [&](size_t at) { return make_double2(re[at], im[at]); };
+    if (cols)
+        fft_stage_any<true, true, false, P2>(
+            tw, C, fp, 0, -1, [&](int line, int i) { return entry_at((size_t)i * N + (l0 + line)); }, to_lds);
+    else
+        fft_stage_any<true, false, false, P2>(
+            tw, C, fp, 0, -1, [&](int line, int i) { return entry_at((size_t)(l0 + line) * N + i); }, to_lds);
     __syncthreads();
-    fft_stages<P2>(buf, tw, C, -1, fp);
+    fft_stages<P2>(buf, tw, C, -1, fp, 1, fp.stages);
     double *out = part + ((size_t)blockIdx.y * gridDim.x + blockIdx.x) * N;
     for (int k = threadIdx.x; k < N; k += kFftThreads) {
         double s = 0.0;
@@ -730,8 +863,10 @@ hipError_t launch_planes_to_charges(hipStream_t st, int N, const double2 *planes
 }
 
 hipError_t launch_fft_tables(hipStream_t st, int N, double2 *tab) {
-    if (N > kFftMaxN) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_fft_tables, dim3((N + 255) / 256), dim3(256), 0, st, N, tab, (double *)(tab + kFftMaxN));
+    FftPlan fp;
+    if (N > kFftMaxN || !fft_plan(N, fp)) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_fft_tables, dim3((N + 255) / 256), dim3(256), 0, st, N, fp, tab, (double *)(tab + kFftMaxN),
+                       tab + kFftStaged);
     return hipGetLastError();
 }
 
@@ -744,20 +879,21 @@ static void poisson_passes(hipStream_t st, int N, double m2, double uv2, double2
                            const double2 *tab, const MvDraw *draw, const FftPlan &fp) {
     const int groups = (N + (1 << fp.log_c) - 1) >> fp.log_c;
     const double *s2 = (const double *)(tab + kFftMaxN);
-    const size_t lds_lines = ((size_t)(fp.ls << fp.log_c) + N) * sizeof(double2);
+    const double2 *tw = tab + kFftStaged;
+    const size_t lds_lines = ((size_t)(fp.ls << fp.log_c) + fp.n_tw) * sizeof(double2);
     const size_t lds_poisson = lds_lines + N * sizeof(double);
     const MvDraw mv = draw ? *draw : MvDraw{0.0, 0, 0, 0, 1};
     const dim3 grid(n_planes * groups), wg(kFftThreads);
     if (draw)
-        hipLaunchKernelGGL((k_fft_lines<kFftDraw, P2>), grid, wg, lds_lines, st, planes, N, 0, groups, -1, fp, m2,
-                           uv2, tab, s2, mv);
+        hipLaunchKernelGGL((k_fft_lines<kFftDraw, P2>), grid, wg, lds_lines, st, planes, N, groups, -1, fp, m2,
+                           uv2, tw, s2, mv);
     else
-        hipLaunchKernelGGL((k_fft_lines<kFftLines, P2>), grid, wg, lds_lines, st, planes, N, 0, groups, -1, fp, m2,
-                           uv2, tab, s2, mv);
-    hipLaunchKernelGGL((k_fft_lines<kFftPoisson, P2>), grid, wg, lds_poisson, st, planes, N, 1, groups, -1, fp, m2,
-                       uv2, tab, s2, mv);
-    hipLaunchKernelGGL((k_fft_lines<kFftLines, P2>), grid, wg, lds_lines, st, planes, N, 0, groups, +1, fp, m2, uv2,
-                       tab, s2, mv);
+        hipLaunchKernelGGL((k_fft_lines<kFftLines, P2>), grid, wg, lds_lines, st, planes, N, groups, -1, fp, m2,
+                           uv2, tw, s2, mv);
+    hipLaunchKernelGGL((k_fft_lines<kFftPoisson, P2>), grid, wg, lds_poisson, st, planes, N, groups, -1, fp, m2,
+                       uv2, tw, s2, mv);
+    hipLaunchKernelGGL((k_fft_lines<kFftLines, P2>), grid, wg, lds_lines, st, planes, N, groups, +1, fp, m2, uv2,
+                       tw, s2, mv);
 }
 
 hipError_t launch_poisson(hipStream_t st, int N, double m2, double uv2, double2 *planes, int n_planes,
@@ -782,11 +918,13 @@ hipError_t launch_dipole(hipStream_t st, int N, const double *V, int rmax, const
     if (N > kFftMaxN || !fft_plan(N, fp)) return hipErrorInvalidValue;
     const int groups = (N + (1 << fp.log_c) - 1) >> fp.log_c;
     double *S = scratch, *part = scratch + N;
-    const size_t lds = ((size_t)(fp.ls << fp.log_c) + N) * sizeof(double2);
+    const size_t lds = ((size_t)(fp.ls << fp.log_c) + fp.n_tw) * sizeof(double2);
     if (fp.p2)
-        hipLaunchKernelGGL(k_dipole_lines<true>, dim3(groups, 18), dim3(kFftThreads), lds, st, V, N, fp, tab, part);
+        hipLaunchKernelGGL(k_dipole_lines<true>, dim3(groups, 18), dim3(kFftThreads), lds, st, V, N, fp, tab + kFftStaged,
+                           part);
     else
-        hipLaunchKernelGGL(k_dipole_lines<false>, dim3(groups, 18), dim3(kFftThreads), lds, st, V, N, fp, tab, part);
+        hipLaunchKernelGGL(k_dipole_lines<false>, dim3(groups, 18), dim3(kFftThreads), lds, st, V, N, fp, tab + kFftStaged,
+                           part);
     hipLaunchKernelGGL(k_dipole_sum, dim3((N + 15) / 16), dim3(256), 0, st, N, (const double *)part, 18 * groups, S);
     hipLaunchKernelGGL(k_dipole_curve, dim3(rmax + 1), dim3(256), 0, st, N, (const double *)S, tab, D);
     return hipGetLastError();

@@ -225,7 +225,7 @@ hipError_t launch_charges_to_planes(hipStream_t st, int N, const double *rho /* 
                                     double2 *planes);
 hipError_t launch_planes_to_charges(hipStream_t st, int N, const double2 *planes, double *rho);
 // the twiddle and sin^2 tables of one solve size into tab (kFftTableBytes)
-constexpr size_t kFftTableBytes = 1024 * (sizeof(double2) + sizeof(double));
+constexpr size_t kFftTableBytes = 1024 * (2 * sizeof(double2) + sizeof(double));
 hipError_t launch_fft_tables(hipStream_t st, int N, double2 *tab);
 hipError_t launch_poisson(hipStream_t st, int N, double m2, double uv2, double2 *planes, int n_planes,
                           const double2 *tab, const MvDraw *draw = nullptr);

@@ -105,3 +105,19 @@ def test_device_draw_equals_caller_charges_bitwise(gl):
         assert np.array_equal(x, y)
     for nuc in (0, 1):
         assert np.array_equal(a.wilson_line(nuc), b.wilson_line(nuc))
+
+
+@pytest.mark.parametrize("N", [2, 3, 4, 6, 8, 9, 12, 16, 18, 27, 32, 36, 64, 72, 81, 128, 243, 324, 486])
+def test_wilson_lines_of_every_transform(gl, N):
+    """Every first, middle and last radix of the line transforms, lattices of one
+    stage, and column groups that do not divide the lattice; two sheets, both
+    nuclei, against the oracle.  A transform's error is some 10 eps per stage of
+    entries below one."""
+    from oracle import oracle as orc
+    L, sigma, m2 = _params(N, 2)
+    ev = gl.Event(N, L)
+    ev.init_glasma(G2MU, M_IR, 2, SEED)
+    for nuc in (0, 1):
+        V = orc.wilson_line(N, sigma, m2, 2, SEED, nuc)
+        assert np.abs(ev.wilson_line(nuc) - V.T).max() < 1e-12
+    ev.close()
