@@ -108,7 +108,7 @@ gl_status make_layout(const gl_lattice_desc *d, Layout &L) {
     // the push before it (run_paired)
     const bool paired = L.slots > 0 && pair_lattice(n2, ts);
     for (int b = 0; b < 3; b++) L.field[b] = b < 2 || paired ? take(kStateVals * n2 * ts) : 0;
-    for (int b = 0; b < 2; b++) L.F[b] = b < 1 || paired ? take((size_t)kSiteRec * n2 * ts) : 0;
+    for (int b = 0; b < 2; b++) L.F[b] = b < 1 || paired ? take(site_elems(n2) * ts) : 0;
     for (int b = 0; b < 2; b++) L.part[b] = take((size_t)L.slots * ((part_rec(ts) + 3) * ts + 12));
     for (int b = 0; b < 2; b++) L.id[b] = take((size_t)L.slots * sizeof(int32_t));
     for (int b = 0; b < 2; b++) L.sort_keys[b] = take((size_t)L.slots * sizeof(uint32_t));
@@ -797,11 +797,11 @@ gl_status get_site_fields_t(gl_event *ev, double *F) {
     // planes [6][8][n2]; E_x and E_y add their second halves where those are
     // stored apart (half_stored)
     const size_t n2 = ev->n2;
-    std::vector<T> tmp((size_t)kSiteRec * n2);
+    std::vector<T> tmp(site_elems(n2));
     HIP_TRY(hipMemcpyAsync(tmp.data(), ev->site_fields<T>(), tmp.size() * sizeof(T), hipMemcpyDeviceToHost, ev->stream));
     HIP_TRY(hipStreamSynchronize(ev->stream));
-    // device records in chunked planes
-    auto at = [&](int k, size_t x) { return (double)tmp[chunk_index<T>(n2, k, x)]; };
+    constexpr int NV = 16 / (int)sizeof(T);
+    auto at = [&](int k, size_t x) { return (double)tmp[(size_t)site_chunk<T>(x, k / NV) * NV + k % NV]; };
     for (int k = 0; k < 48; k++)
         for (size_t x = 0; x < n2; x++) F[(size_t)k * n2 + x] = at(k, x);
     for (int k = 0; k < 16; k++)
@@ -1743,6 +1743,8 @@ struct Blob {
     size_t bytes;
 };
 
+constexpr uint64_t kSiteBlob = 2;   // the site fields' tag
+
 std::vector<Blob> ckpt_blobs(gl_event *ev) {
     const size_t ts = ev->fp64() ? 8 : 4, n2 = ev->n2, row = (size_t)kMaxSpecies * 4 * sizeof(double);
     std::vector<Blob> b;
@@ -1750,7 +1752,7 @@ std::vector<Blob> ckpt_blobs(gl_event *ev) {
     if (ev->push_due) {
         // the pending push reads the site fields and the state at tau_n (links
         // for the crossings, phi for the eta rotation), the other buffer
-        b.push_back({2, ev->ws + ev->L.F[ev->fcur], (size_t)kSiteRec * n2 * ts});
+        b.push_back({kSiteBlob, ev->ws + ev->L.F[ev->fcur], (size_t)kSiteRec * n2 * ts});
         b.push_back({11, ev->field_base(1 - ev->cur), (size_t)kStateVals * n2 * ts});
     }
     if (ev->L.slots > 0) {
@@ -1770,6 +1772,16 @@ std::vector<Blob> ckpt_blobs(gl_event *ev) {
     return b;
 }
 
+// The file holds the site fields in chunked planes (chunk c of site x at
+// c n2 + x), the device in groups of records.
+template <typename T>
+void regroup_site_fields(char *file, char *dev, size_t n2, bool to_file) {
+    for (size_t c = 0; c < kSiteRec * sizeof(T) / 16; c++)
+        for (size_t x = 0; x < n2; x++) {
+            char *f = file + 16 * (c * n2 + x), *d = dev + 16 * (size_t)site_chunk<T>(x, (int)c);
+            std::memcpy(to_file ? f : d, to_file ? d : f, 16);
+        }
+}
 struct FileCloser {
     std::FILE *f;
     ~FileCloser() {
@@ -1822,13 +1834,20 @@ gl_status gl_checkpoint(gl_event *ev, const char *path) {
     bool ok = std::fwrite(kCkptMagic, 1, 8, fc.f) == 8 && std::fwrite(head, sizeof(head), 1, fc.f) == 1 &&
               std::fwrite(&ev->desc, sizeof(ev->desc), 1, fc.f) == 1 && std::fwrite(&c, sizeof(c), 1, fc.f) == 1 &&
               (sp.empty() || std::fwrite(sp.data(), sizeof(CkptSpecies), sp.size(), fc.f) == sp.size());
-    std::vector<char> host;
+    std::vector<char> host, dev;
     for (const Blob &b : ckpt_blobs(ev)) {
         if (!ok) break;
+        const bool site = b.tag == kSiteBlob;
+        std::vector<char> &from = site ? dev : host;
         host.resize(b.bytes);
+        from.resize(site ? site_elems(ev->n2) * (ev->fp64() ? 8 : 4) : b.bytes);
         if (b.bytes) {
-            HIP_TRY(hipMemcpyAsync(host.data(), b.dev, b.bytes, hipMemcpyDeviceToHost, ev->stream));
+            HIP_TRY(hipMemcpyAsync(from.data(), b.dev, from.size(), hipMemcpyDeviceToHost, ev->stream));
             HIP_TRY(hipStreamSynchronize(ev->stream));
+        }
+        if (site) {
+            if (ev->fp64()) regroup_site_fields<double>(host.data(), dev.data(), ev->n2, true);
+            else regroup_site_fields<float>(host.data(), dev.data(), ev->n2, true);
         }
         const uint64_t hb[2] = {b.tag, (uint64_t)b.bytes};
         ok = std::fwrite(hb, sizeof(hb), 1, fc.f) == 1 && (b.bytes == 0 || std::fwrite(host.data(), 1, b.bytes, fc.f) == b.bytes);
@@ -1911,7 +1930,7 @@ gl_status gl_restore(gl_event *ev, const char *path) {
     HIP_TRY(hipMemsetAsync(ev->series(), 0, cap_rows * row, ev->stream));
     if (d.static_correlator) HIP_TRY(hipMemsetAsync(ev->stat_series(), 0, cap_rows * row, ev->stream));
     if (d.lightlike_correlator) HIP_TRY(hipMemsetAsync(ev->ll_series(), 0, cap_rows * row, ev->stream));
-    std::vector<char> host;
+    std::vector<char> host, dev;
     for (const Blob &b : ckpt_blobs(ev)) {
         uint64_t hb[2];
         if (std::fread(hb, sizeof(hb), 1, fc.f) != 1 || hb[0] != b.tag || hb[1] != b.bytes)
@@ -1919,7 +1938,13 @@ gl_status gl_restore(gl_event *ev, const char *path) {
         host.resize(b.bytes);
         if (b.bytes == 0) continue;
         if (std::fread(host.data(), 1, b.bytes, fc.f) != b.bytes) return fail(GL_EINVAL, std::string(path) + " is truncated");
-        HIP_TRY(hipMemcpyAsync(b.dev, host.data(), b.bytes, hipMemcpyHostToDevice, ev->stream));
+        if (b.tag == kSiteBlob) {
+            dev.assign(site_elems(ev->n2) * (ev->fp64() ? 8 : 4), 0);
+            if (ev->fp64()) regroup_site_fields<double>(host.data(), dev.data(), ev->n2, false);
+            else regroup_site_fields<float>(host.data(), dev.data(), ev->n2, false);
+            host.swap(dev);
+        }
+        HIP_TRY(hipMemcpyAsync(b.dev, host.data(), host.size(), hipMemcpyHostToDevice, ev->stream));
         HIP_TRY(hipStreamSynchronize(ev->stream));
     }
     ev->ready = true;

@@ -105,9 +105,9 @@ k_correlators(int N, const T *__restrict__ F, const T *__restrict__ U, double *_
         for (int i = 0; i < 3; i++) {
             T re[8], rh[8];
             double e[8];
-            chunk_load_a(F, n2, c, 8 * i, re);
+            site_load<8>(F, c, 8 * i, re);
             const bool half = i < 2 && half_stored(i, ix, iy);
-            if (half) chunk_load_a(F, n2, c, 48 + 8 * i, rh);
+            if (half) site_load<8>(F, c, 48 + 8 * i, rh);
 #pragma unroll
             for (int a = 0; a < 8; a++) e[a] = (double)re[a] + (half ? (double)rh[a] : 0.0);
             if constexpr (STAT) {
@@ -124,7 +124,7 @@ k_correlators(int N, const T *__restrict__ F, const T *__restrict__ U, double *_
                 double t[8];
                 if (i > 0) {
                     T rb[8];   // B_z for F_y, B_y for F_z
-                    chunk_load_a(F, n2, c, i == 1 ? 40 : 32, rb);
+                    site_load<8>(F, c, i == 1 ? 40 : 32, rb);
 #pragma unroll
                     for (int a = 0; a < 8; a++) e[a] += i == 1 ? -(double)rb[a] : (double)rb[a];
                 }

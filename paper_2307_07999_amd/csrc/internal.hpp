@@ -9,9 +9,7 @@ namespace gl {
 
 constexpr int kMaxSpecies = 16;
 constexpr int kPushBlock = 256;   // particles per push workgroup
-// site-field record of kSiteRec reals per site in chunked planes (16-byte
-// chunks of consecutive values, one chunk plane per chunk index over all
-// sites): slots of 8 reals Ex, Ey, Ez, Bx, By, Bz (local frame), then two
+// site-field record of kSiteRec reals per site: slots of 8 reals Ex, Ey, Ez, Bx, By, Bz (local frame), then two
 // slots for the second halves of Ex and Ey.  E_i at a site is the sum of
 // the half from the link U_i(x) and the half transported from U_i(x - i).
 // Where both links fall in one field-step workgroup the step adds them and
@@ -19,9 +17,33 @@ constexpr int kPushBlock = 256;   // particles per push workgroup
 // rule that every tile shape respects) the half from x - i is stored apart
 // in slot 6 + i, and readers add it: E_i = slot i + slot 6 + i there, slot
 // i elsewhere (slot 6 + i is not written).  Either way it is the same sum
-// of the same two halves.  A particle reads its cell's record in 16-byte
-// loads, and the field step's lanes store neighbouring chunks.
+// of the same two halves.
+//
+// The records stand in groups of kSiteGroup consecutive sites, a group's
+// records interleaved in 16-byte chunks, chunk c of the group's sites beside one
+// another.  A record as a whole would suit the push of thinly spread particles,
+// whose gathers otherwise meet a new line per chunk all over the planes; a chunk
+// plane over all sites suits the field step, whose lanes then store whole lines.
+// Four sites are 1 KiB a record group in FP32, and a pair of chunks of them one
+// 128-byte line, which the field step's lane pairs write together.  Push / field
+// step, us, of 24 events of 256^2 with 10^4 particles each, of ten events of
+// 128^2 to 512^2 with up to 10^6, and of 512^2 with 7 10^5 in FP32 and FP64:
+//   planes     92 / 216   231 / 203   36.8 / 34.7   65.8 / 67.2
+//   8 sites    92 / 218   229 / 203   36.3 / 34.8   64.8 / 66.9
+//   4 sites    66 / 220   219 / 204   36.5 / 35.0   63.9 / 68.2
+//   2 sites    56 / 240   211 / 221   37.8 / 35.5   63.5 / 70.9
+//   1 site     51 / 318   244 / --    40.6 / 38.6   66.6 / 78.1
 constexpr int kSiteRec = 64;
+constexpr int kSiteGroup = 4;
+// elements of the records of n2 sites, and where chunk c of site x is, in chunks
+__host__ __device__ __forceinline__ size_t site_elems(size_t n2) {
+    return (size_t)kSiteRec * ((n2 + kSiteGroup - 1) / kSiteGroup * kSiteGroup);
+}
+template <typename T>
+__host__ __device__ __forceinline__ uint32_t site_chunk(size_t x, int c) {
+    constexpr uint32_t chunks = kSiteRec * sizeof(T) / 16, g = kSiteGroup;
+    return ((uint32_t)x / g) * (chunks * g) + (uint32_t)c * g + (uint32_t)x % g;
+}
 constexpr int kHalfX = 16, kHalfY = 2;   // tile widths and heights are multiples of these
 // whether site (ix, iy) keeps the half of E_{d+1} from x - (d+1) apart
 __host__ __device__ __forceinline__ bool half_stored(int d, int ix, int iy) {

@@ -54,26 +54,22 @@ __device__ __forceinline__ int push_particle(int N, const PartPtrs<T> &P, int64_
         // so that at most a third of it is live: the FP32 push then fits 79
         // VGPRs, six waves per SIMD (FP32 push 42.8 -> 41.4 us, FP64 73.2 ->
         // 71.3 us, FP32 64-event batch 0.937 -> 0.921 s)
-        constexpr int NV = 16 / (int)sizeof(T);
         T e[3], b[3], ph[8];
 #pragma unroll
         for (int k = 0; k < 2; k++) {
             // E_x or E_y and its second half where it is stored apart
             T re[8], rh[8];
-#pragma unroll
-            for (int j = 0; j < 8; j += NV) chunk_ld16(F, n2, x, 8 * k + j, re + j);
+            site_load<8>(F, x, 8 * k, re);
             const bool stored = half_stored(k, cx, cy);
             if constexpr (ST) {
                 if (stored) {
-#pragma unroll
-                    for (int j = 0; j < 8; j += NV) chunk_ld16(F, n2, x, 48 + 8 * k + j, rh + j);
+                    site_load<8>(F, x, 48 + 8 * k, rh);
                 } else {
 #pragma unroll
                     for (int j = 0; j < 8; j++) rh[j] = T(0);
                 }
             } else {
-#pragma unroll
-                for (int j = 0; j < 8; j += NV) chunk_ld16(F, n2, x, 48 + 8 * k + j, rh + j);
+                site_load<8>(F, x, 48 + 8 * k, rh);
 #pragma unroll
                 for (int j = 0; j < 8; j++) rh[j] = stored ? rh[j] : T(0);
             }
@@ -86,8 +82,7 @@ __device__ __forceinline__ int push_particle(int N, const PartPtrs<T> &P, int64_
         {
             // E_z (slots 16..23), B_x, B_y, B_z (24..47) and phi
             T rb[32];
-#pragma unroll
-            for (int j = 0; j < 32; j += NV) chunk_ld16(F, n2, x, 16 + j, rb + j);
+            site_load<32>(F, x, 16, rb);
             chunk_load_a(f.phi, n2, x, 0, ph);
             T se = T(0);
 #pragma unroll

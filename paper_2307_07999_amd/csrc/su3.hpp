@@ -722,6 +722,62 @@ __device__ __forceinline__ void chunk_store_link_l(T *p, size_t n2, size_t x, in
     chunk_store_n_l<kLinkVals, CP>(p, n2, x, kLinkVals * d, v);
 }
 
+// Site-field records (site_chunk): n values k0 .. of site x, k0 and n multiples
+// of 16 / sizeof(T), k0 the lane's own.
+template <int n, typename T>
+__device__ __forceinline__ void site_load(const T *p, size_t x, int k0, T *v) {
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    struct V { T v[16 / sizeof(T)]; };
+    constexpr int NV = 16 / (int)sizeof(T);
+    const uint32_t at = site_chunk<T>(x, k0 / NV) * 16;
+#pragma unroll
+    for (int k = 0; k < n; k += NV) {
+        const V r = __builtin_bit_cast(
+            V, __builtin_amdgcn_raw_buffer_load_b128(buf(p), at + (uint32_t)(k / NV * kSiteGroup * 16), 0u, 0));
+#pragma unroll
+        for (int i = 0; i < NV; i++) v[k + i] = r.v[i];
+    }
+}
+// n values of each lane of a pair (d = 0, 1), lane 0's to k0 .. and lane 1's to
+// k1 .. of site x's record: the lanes trade chunks so that each store writes two
+// neighbouring chunks of the site, and with kSiteGroup = 4 whole cache lines.
+template <int n, typename T>
+__device__ __forceinline__ void site_store_pair(T *p, size_t x, int k0, int k1, const T *v, int d) {
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    struct V { T v[16 / sizeof(T)]; };
+    constexpr int NV = 16 / (int)sizeof(T);
+    static_assert(n % (2 * NV) == 0, "whole pairs of chunks");
+    const uint32_t at0 = site_chunk<T>(x, k0 / NV + d) * 16, at1 = site_chunk<T>(x, k1 / NV + d) * 16;
+#pragma unroll
+    for (int k = 0; k < n; k += 2 * NV) {
+        V a, b;   // chunks k / NV + d of lane 0's and of lane 1's values
+#pragma unroll
+        for (int i = 0; i < NV; i++) {
+            const T even = dpp<kDppSwap1>(v[k + i]), odd = dpp<kDppSwap1>(v[k + NV + i]);
+            a.v[i] = d ? odd : v[k + i];
+            b.v[i] = d ? v[k + NV + i] : even;
+        }
+        const uint32_t step = (uint32_t)(k / NV * kSiteGroup * 16);
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, a), buf(p), at0 + step, 0u, 0);
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, b), buf(p), at1 + step, 0u, 0);
+    }
+}
+template <int n, typename T>
+__device__ __forceinline__ void site_store(T *p, size_t x, int k0, const T *v) {
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    struct V { T v[16 / sizeof(T)]; };
+    constexpr int NV = 16 / (int)sizeof(T);
+    const uint32_t at = site_chunk<T>(x, k0 / NV) * 16;
+#pragma unroll
+    for (int k = 0; k < n; k += NV) {
+        V r;
+#pragma unroll
+        for (int i = 0; i < NV; i++) r.v[i] = v[k + i];
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, r), buf(p),
+                                               at + (uint32_t)(k / NV * kSiteGroup * 16), 0u, 0);
+    }
+}
+
 // A link plane set: 18 planes of n2 values, entry (i,j) real at plane 2(3i+j).
 template <typename T>
 __device__ __forceinline__ M3<T> load_m(const T *__restrict__ base, size_t n2, size_t x) {
