@@ -13,9 +13,9 @@ struct BatchEv {
     int n_species;
     int max_steps;
     int64_t n_slots, n_particles;   // used slots, the valid ones first
-    FieldPtrs<T> f[2];     // f[p] and f[p ^ 1]: state at step n and at n + 1 for parity p
+    FieldPtrs<T> f[3];     // the event's two field states, and the spare one of a batch that pairs its launches
     PartPtrs<T> P[2];      // particle buffers; the current one alternates at each sort
-    T *F;                  // site-field records (chunked planes), written by the field phase when n_species > 0
+    T *F[2];               // site-field records, written by the field phase when n_species > 0; the second as f[2]
     double *partials;      // [n_slots / kPushBlock][n_species][4]
     const double *p0sum;   // [kMaxSpecies][4]: sums of the squared momenta at formation
     double *series;        // [max_steps][kMaxSpecies][4]
@@ -31,6 +31,13 @@ constexpr int64_t kCheckChunk = 65536;       // state values per entry of the ba
 
 struct BatchCtl {
     int64_t n;             // common step index of all events
+};
+
+// A step of a launch: its place after the control block's step, the field
+// states it reads and writes (a push: the state of its own time in `in`) and
+// its site-field record.
+struct BatchAt {
+    int off, in, out, F;
 };
 
 constexpr int kBatchShapes = 3;   // field-kernel site tiles 32x4, 64x2, 16x8 (two lanes per site)
@@ -58,7 +65,7 @@ __device__ __forceinline__ void permute_one(const PartPtrs<T> &src, const PartPt
 
 template <typename T>
 hipError_t launch_batch_fields(hipStream_t st, int shape, const BatchEv<T> *evs, const int2 *tiles, int64_t total,
-                               int fpar, const BatchCtl *ctl, double dtau, int grid);
+                               const BatchAt &at, const BatchCtl *ctl, double dtau, int grid);
 // the particle sort of every event, one launch per phase; pblocks (event,
 // particle block) and stiles (event, sort tile) cover each event's used
 // slots.  The sorted order of buffer parity ppar goes to each event's sort
@@ -76,8 +83,18 @@ hipError_t launch_batch_permute(hipStream_t st, const BatchEv<T> *evs, const int
 // particles go to parity ppar ^ 1 (a masked event's particles are moved
 // without a push)
 template <typename T>
-hipError_t launch_batch_push(hipStream_t st, const BatchEv<T> *evs, const int2 *blocks, int64_t total, int fpar,
-                             int ppar, const BatchCtl *ctl, double dtau, int grid, int n_events, bool permuted);
+hipError_t launch_batch_push(hipStream_t st, const BatchEv<T> *evs, const int2 *blocks, int64_t total,
+                             const BatchAt &at, int ppar, const BatchCtl *ctl, double dtau, int grid, bool permuted);
+// the field step `at` and the push of the step before it in one launch
+template <typename T>
+hipError_t launch_batch_pair(hipStream_t st, int shape, const BatchEv<T> *evs, const int2 *tiles, int64_t n_tiles,
+                             const BatchAt &at, const int2 *blocks, int64_t n_blocks, const BatchAt &push, int ppar,
+                             const BatchCtl *ctl, double dtau, bool permuted);
+// the series rows of the push at step off
+template <typename T>
+hipError_t launch_batch_reduce(hipStream_t st, const BatchEv<T> *evs, int n_events, int off, const BatchCtl *ctl);
+// the control block moves on by `steps`
+hipError_t launch_batch_advance(hipStream_t st, BatchCtl *ctl, int steps);
 // every event's field state at parity fpar checked for NaN/Inf in chunks of
 // kCheckChunk values ((event, chunk) entries); a failing event's fail slot
 // is lowered to the current step

@@ -30,36 +30,36 @@ __device__ __forceinline__ int64_t xcd_first(int64_t total, int64_t &stride, int
 
 // one tile of an event: stage its links and phi, then the step of its sites
 template <typename T, int TX, int TY>
-__device__ __forceinline__ void batch_field_tile(LinkTile<T, TX, TY> &tile, const BatchEv<T> &e, int2 w, int fpar,
-                                                 int64_t n, T tau, T dtau, T tau_h) {
-    const int lx = threadIdx.x >> 1, ly = threadIdx.y;
+__device__ __forceinline__ void batch_field_tile(LinkTile<T, TX, TY> &tile, const BatchEv<T> &e, int2 w,
+                                                 const BatchAt &at, int tid, int64_t n, T tau, T dtau, T tau_h) {
+    const int lx = (tid % (2 * TX)) >> 1, ly = tid / (2 * TX);
     const int tx = (e.N + TX - 1) / TX;
     const int x0 = (w.y % tx) * TX, y0 = (w.y / tx) * TY;
-    const int tid = threadIdx.x + 2 * TX * threadIdx.y;
-    stage_tile(tile, e.N, e.f[fpar], x0, y0, tid, 2 * TX * TY);
+    stage_tile(tile, e.N, e.f[at.in], x0, y0, tid, 2 * TX * TY);
     __syncthreads();
     // every thread takes part (the step synchronises the workgroup)
     const bool active = x0 + lx < e.N && y0 + ly < e.N;
     const int reunit = e.reunit_every > 0 && (n % e.reunit_every) == e.reunit_every - 1;
     // a batch's working set overflows the last-level cache in either
     // precision: its streamed arrays take the non-temporal hint
-    field_step_link<T, TX, TY, true>(tile, e.N, e.f[fpar], e.f[fpar ^ 1], e.n_species > 0 ? e.F : nullptr, x0, y0,
-                                     lx, ly, threadIdx.x & 1, tid, active, tau, dtau, tau_h, reunit);
+    field_step_link<T, TX, TY, true>(tile, e.N, e.f[at.in], e.f[at.out], e.n_species > 0 ? e.F[at.F] : nullptr, x0,
+                                     y0, lx, ly, tid & 1, tid, active, tau, dtau, tau_h, reunit);
 }
 
 template <typename T, int TX, int TY>
 __global__ void __launch_bounds__(2 * TX *TY)
-k_batch_field(const BatchEv<T> *__restrict__ evs, const int2 *__restrict__ tiles, int64_t total, int fpar,
+k_batch_field(const BatchEv<T> *__restrict__ evs, const int2 *__restrict__ tiles, int64_t total, BatchAt at,
               const BatchCtl *__restrict__ ctl, T dtau) {
     __shared__ LinkTile<T, TX, TY> tile;
-    const int64_t n = ctl->n;
+    const int tid = threadIdx.x + 2 * TX * threadIdx.y;
+    const int64_t n = ctl->n + at.off;
     const T tau = dtau * (T)n, tau_h = dtau * ((T)n + T(0.5));
     int64_t stride, end;
     for (int64_t t = xcd_first(total, stride, end); t < end; t += stride) {
         const int2 w = tiles[t];
         if (*evs[w.x].fail != kNotFailed) continue;   // a failed event is masked (uniform per workgroup)
         __syncthreads();   // the previous tile's reads are done
-        batch_field_tile(tile, evs[w.x], w, fpar, n, tau, dtau, tau_h);
+        batch_field_tile(tile, evs[w.x], w, at, tid, n, tau, dtau, tau_h);
     }
 }
 
@@ -68,14 +68,15 @@ k_batch_field(const BatchEv<T> *__restrict__ evs, const int2 *__restrict__ tiles
 // without its loop, which holds registers the step can use.
 template <typename T, int TX, int TY>
 __global__ void __launch_bounds__(2 * TX *TY) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 ? 2 : 4, 8)))
-k_batch_field_flat(const BatchEv<T> *__restrict__ evs, const int2 *__restrict__ tiles, int64_t total, int fpar,
+k_batch_field_flat(const BatchEv<T> *__restrict__ evs, const int2 *__restrict__ tiles, int64_t total, BatchAt at,
                    const BatchCtl *__restrict__ ctl, T dtau) {
     __shared__ LinkTile<T, TX, TY> tile;
-    const int64_t n = ctl->n;
+    const int tid = threadIdx.x + 2 * TX * threadIdx.y;
+    const int64_t n = ctl->n + at.off;
     const T tau = dtau * (T)n, tau_h = dtau * ((T)n + T(0.5));
     const int2 w = tiles[xcd_remap(blockIdx.x, gridDim.x)];
     if (*evs[w.x].fail != kNotFailed) return;   // a failed event is masked (uniform per workgroup)
-    batch_field_tile(tile, evs[w.x], w, fpar, n, tau, dtau, tau_h);
+    batch_field_tile(tile, evs[w.x], w, at, tid, n, tau, dtau, tau_h);
 }
 
 // one block of an event's particles; with PERM, position i takes the particle
@@ -83,7 +84,8 @@ k_batch_field_flat(const BatchEv<T> *__restrict__ evs, const int2 *__restrict__ 
 // particle goes, with its species, momenta at formation and id, to slot i of
 // parity ppar ^ 1, as the single-event push that applies a sort does
 template <typename T, bool PERM>
-__device__ __forceinline__ void batch_push_block(const BatchEv<T> &e, int2 w, int fpar, int ppar, int n, T dtau) {
+__device__ __forceinline__ void batch_push_block(SpeciesReduce &red, const BatchEv<T> &e, int2 w, const BatchAt &at,
+                                                 int ppar, int n, T dtau) {
     const int64_t i = (int64_t)w.y * kPushBlock + threadIdx.x;
     double acc[4] = {0.0, 0.0, 0.0, 0.0};
     int s = -1;
@@ -99,12 +101,13 @@ __device__ __forceinline__ void batch_push_block(const BatchEv<T> &e, int2 w, in
             W.pz0[i] = P.pz0[src];
             e.ids[ppar ^ 1][i] = e.ids[ppar][src];
             __builtin_amdgcn_sched_barrier(0);
-            s = push_particle<T, true, true>(e.N, P, src, W, i, e.f[fpar], e.F, e.tab, n, dtau, acc);
+            s = push_particle<T, true, true>(e.N, P, src, W, i, e.f[at.in], e.F[at.F], e.tab, n, dtau, acc);
         } else {
-            s = push_particle<T, false, true>(e.N, e.P[ppar], i, e.P[ppar], i, e.f[fpar], e.F, e.tab, n, dtau, acc);
+            s = push_particle<T, false, true>(e.N, e.P[ppar], i, e.P[ppar], i, e.f[at.in], e.F[at.F], e.tab, n, dtau,
+                                              acc);
         }
     }
-    block_species_reduce(s, acc, e.n_species, e.partials + (size_t)w.y * e.n_species * 4);
+    block_species_reduce(red, s, acc, e.n_species, e.partials + (size_t)w.y * e.n_species * 4);
 }
 
 // a masked (failed) event is not pushed, but a pending sort still moves its
@@ -119,9 +122,10 @@ __device__ __forceinline__ void batch_masked_block(const BatchEv<T> &e, int2 w, 
 
 template <typename T, bool PERM>
 __global__ void __launch_bounds__(kPushBlock)
-k_batch_push(const BatchEv<T> *__restrict__ evs, const int2 *__restrict__ blocks, int64_t total, int fpar,
+k_batch_push(const BatchEv<T> *__restrict__ evs, const int2 *__restrict__ blocks, int64_t total, BatchAt at,
              int ppar, const BatchCtl *__restrict__ ctl, T dtau) {
-    const int n = (int)ctl->n;
+    __shared__ SpeciesReduce red;
+    const int n = (int)(ctl->n + at.off);
     int64_t stride, end;
     for (int64_t t = xcd_first(total, stride, end); t < end; t += stride) {
         const int2 w = blocks[t];
@@ -129,36 +133,82 @@ k_batch_push(const BatchEv<T> *__restrict__ evs, const int2 *__restrict__ blocks
             batch_masked_block<T, PERM>(evs[w.x], w, ppar);
             continue;
         }
-        batch_push_block<T, PERM>(evs[w.x], w, fpar, ppar, n, dtau);
+        batch_push_block<T, PERM>(red, evs[w.x], w, at, ppar, n, dtau);
     }
 }
 
 template <typename T, bool PERM>
 __global__ void __launch_bounds__(kPushBlock)
-k_batch_push_flat(const BatchEv<T> *__restrict__ evs, const int2 *__restrict__ blocks, int64_t total, int fpar,
+k_batch_push_flat(const BatchEv<T> *__restrict__ evs, const int2 *__restrict__ blocks, int64_t total, BatchAt at,
                   int ppar, const BatchCtl *__restrict__ ctl, T dtau) {
+    __shared__ SpeciesReduce red;
     const int2 w = blocks[xcd_remap(blockIdx.x, gridDim.x)];
     if (*evs[w.x].fail != kNotFailed) {
         batch_masked_block<T, PERM>(evs[w.x], w, ppar);
         return;
     }
-    batch_push_block<T, PERM>(evs[w.x], w, fpar, ppar, (int)ctl->n, dtau);
+    batch_push_block<T, PERM>(red, evs[w.x], w, at, ppar, (int)(ctl->n + at.off), dtau);
+}
+
+// The field step of one time and the push of the time before it, which with a
+// third field state and a second record do not wait for each other: for batches
+// that fill the chip no more than a round or two (the rule of one event,
+// pairs in event.hip), where each launch is bound by its own chain of
+// dependent instructions.  Rows of FP32 runs, ms: 4 of 64^2 with 1000 particles
+// 14.2 -> 9.4, 5 of 128^2 with 3000 20.0 -> 14.7, 10 of 128^2 with 10^4 28.3 ->
+// 24.0, 2 of 256^2 with 10^4 12.1 -> 10.9.  Larger batches gain nothing: the
+// field step then fills all waves of a SIMD and is near its issue rate, and a
+// push workgroup beside it only holds the registers of another (24 of 256^2 296
+// -> 288 us a step, ten of 128^2 to 512^2 424 -> 447).
+template <typename T, int TX, int TY, bool PERM>
+__global__ void __launch_bounds__(kPushBlock) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 ? 2 : 4, 8)))
+k_batch_field_push(const BatchEv<T> *__restrict__ evs, const int2 *__restrict__ tiles, int64_t n_tiles,
+                   const int2 *__restrict__ blocks, int64_t n_blocks, BatchAt at, BatchAt push, int ppar,
+                   const BatchCtl *__restrict__ ctl, T dtau) {
+    static_assert(2 * TX * TY == kPushBlock, "a field tile and a push block share the workgroup size");
+    union Lds {
+        LinkTile<T, TX, TY> tile;
+        SpeciesReduce red;
+    };
+    __shared__ __align__(16) unsigned char lds[sizeof(Lds)];
+    // XCD x owns one run of the tiles and one of the push blocks; its
+    // workgroups j take them in turn, the push blocks spread evenly
+    const int64_t x = blockIdx.x & 7, j = blockIdx.x >> 3;
+    const int64_t tq = n_tiles >> 3, tr = n_tiles & 7, pq = n_blocks >> 3, pr = n_blocks & 7;
+    const int64_t mine_t = tq + (x < tr), mine_p = pq + (x < pr), all = mine_t + mine_p;
+    if (j >= all) return;
+    const int64_t p = j * mine_p / all;
+    if ((j + 1) * mine_p / all > p) {
+        const int2 w = blocks[x * pq + (x < pr ? x : pr) + p];
+        if (*evs[w.x].fail != kNotFailed) {
+            batch_masked_block<T, PERM>(evs[w.x], w, ppar);
+            return;
+        }
+        batch_push_block<T, PERM>(*reinterpret_cast<SpeciesReduce *>(lds), evs[w.x], w, push, ppar,
+                                  (int)(ctl->n + push.off), dtau);
+        return;
+    }
+    const int2 w = tiles[x * tq + (x < tr ? x : tr) + (j - p)];
+    if (*evs[w.x].fail != kNotFailed) return;
+    const int64_t n = ctl->n + at.off;
+    batch_field_tile(*reinterpret_cast<LinkTile<T, TX, TY> *>(lds), evs[w.x], w, at, (int)threadIdx.x, n, dtau * (T)n,
+                     dtau, dtau * ((T)n + T(0.5)));
 }
 
 // one workgroup per (event, species): fixed-order sum of the event's partial
 // rows into its series row n - 1, n taken from the control block
 template <typename T>
 __global__ void __launch_bounds__(256)
-k_batch_reduce(const BatchEv<T> *__restrict__ evs, const BatchCtl *__restrict__ ctl) {
+k_batch_reduce(const BatchEv<T> *__restrict__ evs, int off, const BatchCtl *__restrict__ ctl) {
     const BatchEv<T> &e = evs[blockIdx.x];
     const int s = blockIdx.y;
     if (s >= e.n_species) return;
-    const int64_t row = ctl->n - 1;
+    const int64_t n = ctl->n + off, row = n - 1;
     if (row < 0 || row >= e.max_steps) return;
     // masked since an earlier step: that push skipped the event, its partial
     // rows are stale.  Blocks of this launch lower fail to n + 1 at most, so
     // the test reads the same for every thread of the workgroup.
-    if (*e.fail <= ctl->n) return;
+    if (*e.fail <= n) return;
     const int nb = (int)(e.n_slots / kPushBlock);
     __shared__ double red[256][4];
     double acc[4] = {0, 0, 0, 0};
@@ -179,7 +229,7 @@ k_batch_reduce(const BatchEv<T> *__restrict__ evs, const BatchCtl *__restrict__ 
         if (threadIdx.x < 3 && red[0][3] > 0.0) v -= e.p0sum[s * 4 + threadIdx.x];
         e.series[((size_t)row * kMaxSpecies + s) * 4 + threadIdx.x] = v;
         // a non-finite sum fails the event at the step this push reached (n + 1)
-        if (!isfinite(v)) atomicMin(e.fail, (int32_t)(ctl->n + 1 < kNotFailed ? ctl->n + 1 : kNotFailed - 1));
+        if (!isfinite(v)) atomicMin(e.fail, (int32_t)(n + 1 < kNotFailed ? n + 1 : kNotFailed - 1));
     }
 }
 
@@ -199,23 +249,23 @@ k_batch_check(const BatchEv<T> *__restrict__ evs, const int2 *__restrict__ entri
     if (bad) atomicMin(e.fail, (int32_t)(ctl->n < kNotFailed ? ctl->n : kNotFailed - 1));
 }
 
-__global__ void k_batch_advance(BatchCtl *ctl) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) ctl->n = ctl->n + 1;
+__global__ void k_batch_advance(BatchCtl *ctl, int steps) {
+    if (threadIdx.x == 0 && blockIdx.x == 0) ctl->n = ctl->n + steps;
 }
 
 template <typename T>
 hipError_t launch_batch_fields(hipStream_t st, int shape, const BatchEv<T> *evs, const int2 *tiles, int64_t total,
-                               int fpar, const BatchCtl *ctl, double dtau, int grid) {
+                               const BatchAt &at, const BatchCtl *ctl, double dtau, int grid) {
     if (total <= 0) return hipSuccess;
     unsigned g = (unsigned)(grid > 0 && grid < total ? grid : total);
 #define GL_SHAPE(TXv, TYv)                                                                                    \
     {                                                                                                         \
         if (g == total)                                                                                       \
             hipLaunchKernelGGL((k_batch_field_flat<T, TXv, TYv>), dim3(g), dim3(2 * TXv, TYv), 0, st, evs,    \
-                               tiles, total, fpar, ctl, (T)dtau);                                             \
+                               tiles, total, at, ctl, (T)dtau);                                               \
         else                                                                                                  \
             hipLaunchKernelGGL((k_batch_field<T, TXv, TYv>), dim3(g), dim3(2 * TXv, TYv), 0, st, evs, tiles,  \
-                               total, fpar, ctl, (T)dtau);                                                    \
+                               total, at, ctl, (T)dtau);                                                      \
     }
     switch (shape) {
         case 0: GL_SHAPE(32, 4) break;
@@ -228,27 +278,62 @@ hipError_t launch_batch_fields(hipStream_t st, int shape, const BatchEv<T> *evs,
 }
 
 template <typename T>
-hipError_t launch_batch_push(hipStream_t st, const BatchEv<T> *evs, const int2 *blocks, int64_t total, int fpar,
-                             int ppar, const BatchCtl *ctl, double dtau, int grid, int n_events, bool permuted) {
+hipError_t launch_batch_push(hipStream_t st, const BatchEv<T> *evs, const int2 *blocks, int64_t total,
+                             const BatchAt &at, int ppar, const BatchCtl *ctl, double dtau, int grid, bool permuted) {
     if (total > 0) {
         unsigned g = (unsigned)(grid > 0 && grid < total ? grid : total);
 #define GL_PUSH(PERM)                                                                                          \
     {                                                                                                          \
         if (g == total)                                                                                        \
             hipLaunchKernelGGL((k_batch_push_flat<T, PERM>), dim3(g), dim3(kPushBlock), 0, st, evs, blocks, total, \
-                               fpar, ppar, ctl, (T)dtau);                                                      \
+                               at, ppar, ctl, (T)dtau);                                                        \
         else                                                                                                   \
             hipLaunchKernelGGL((k_batch_push<T, PERM>), dim3(g), dim3(kPushBlock), 0, st, evs, blocks, total,   \
-                               fpar, ppar, ctl, (T)dtau);                                                      \
+                               at, ppar, ctl, (T)dtau);                                                        \
     }
         if (permuted)
             GL_PUSH(true)
         else
             GL_PUSH(false)
 #undef GL_PUSH
-        hipLaunchKernelGGL(k_batch_reduce<T>, dim3(n_events, kMaxSpecies), dim3(256), 0, st, evs, ctl);
     }
-    hipLaunchKernelGGL(k_batch_advance, dim3(1), dim3(64), 0, st, (BatchCtl *)ctl);
+    return hipGetLastError();
+}
+
+template <typename T>
+hipError_t launch_batch_pair(hipStream_t st, int shape, const BatchEv<T> *evs, const int2 *tiles, int64_t n_tiles,
+                             const BatchAt &at, const int2 *blocks, int64_t n_blocks, const BatchAt &push, int ppar,
+                             const BatchCtl *ctl, double dtau, bool permuted) {
+    if (n_tiles <= 0 || n_blocks <= 0) return hipErrorInvalidValue;
+    // as many workgroups an XCD as the fullest one has work for
+    const unsigned g = (unsigned)(8 * ((n_tiles + 7) / 8 + (n_blocks + 7) / 8));
+#define GL_SHAPE(TXv, TYv)                                                                                     \
+    {                                                                                                          \
+        if (permuted)                                                                                          \
+            hipLaunchKernelGGL((k_batch_field_push<T, TXv, TYv, true>), dim3(g), dim3(kPushBlock), 0, st, evs, \
+                               tiles, n_tiles, blocks, n_blocks, at, push, ppar, ctl, (T)dtau);                \
+        else                                                                                                   \
+            hipLaunchKernelGGL((k_batch_field_push<T, TXv, TYv, false>), dim3(g), dim3(kPushBlock), 0, st, evs, \
+                               tiles, n_tiles, blocks, n_blocks, at, push, ppar, ctl, (T)dtau);                \
+    }
+    switch (shape) {
+        case 0: GL_SHAPE(32, 4) break;
+        case 1: GL_SHAPE(64, 2) break;
+        case 2: GL_SHAPE(16, 8) break;
+        default: return hipErrorInvalidValue;
+    }
+#undef GL_SHAPE
+    return hipGetLastError();
+}
+
+template <typename T>
+hipError_t launch_batch_reduce(hipStream_t st, const BatchEv<T> *evs, int n_events, int off, const BatchCtl *ctl) {
+    hipLaunchKernelGGL(k_batch_reduce<T>, dim3(n_events, kMaxSpecies), dim3(256), 0, st, evs, off, ctl);
+    return hipGetLastError();
+}
+
+hipError_t launch_batch_advance(hipStream_t st, BatchCtl *ctl, int steps) {
+    hipLaunchKernelGGL(k_batch_advance, dim3(1), dim3(64), 0, st, ctl, steps);
     return hipGetLastError();
 }
 
@@ -263,10 +348,14 @@ hipError_t launch_batch_check(hipStream_t st, const BatchEv<T> *evs, const int2 
 #define GL_INST(T)                                                                                          \
     template hipError_t launch_batch_check<T>(hipStream_t, const BatchEv<T> *, const int2 *, int64_t, int,      \
                                               const BatchCtl *);                                             \
-    template hipError_t launch_batch_fields<T>(hipStream_t, int, const BatchEv<T> *, const int2 *, int64_t, int, \
-                                               const BatchCtl *, double, int);                               \
-    template hipError_t launch_batch_push<T>(hipStream_t, const BatchEv<T> *, const int2 *, int64_t, int, int,  \
-                                             const BatchCtl *, double, int, int, bool);
+    template hipError_t launch_batch_fields<T>(hipStream_t, int, const BatchEv<T> *, const int2 *, int64_t,      \
+                                               const BatchAt &, const BatchCtl *, double, int);              \
+    template hipError_t launch_batch_push<T>(hipStream_t, const BatchEv<T> *, const int2 *, int64_t,            \
+                                             const BatchAt &, int, const BatchCtl *, double, int, bool);     \
+    template hipError_t launch_batch_pair<T>(hipStream_t, int, const BatchEv<T> *, const int2 *, int64_t,       \
+                                             const BatchAt &, const int2 *, int64_t, const BatchAt &, int,   \
+                                             const BatchCtl *, double, bool);                                \
+    template hipError_t launch_batch_reduce<T>(hipStream_t, const BatchEv<T> *, int, int, const BatchCtl *);
 GL_INST(double)
 GL_INST(float)
 #undef GL_INST

@@ -1973,6 +1973,7 @@ struct gl_batch {
     int64_t total_tiles[kBatchShapes] = {0, 0, 0}, total_pblocks = 0, total_stiles = 0, total_checks = 0;
     int shape = 0, grid_mult = 4, cus = 256;
     int fpar = 0, ppar = 0;
+    bool paired = false;              // each field step runs beside the push before it
     int64_t since_sort = 0;
     bool sort_pending = false;        // a sorted order waits in the events' scratch; the next push applies it
     int sort_every = 16;
@@ -2002,6 +2003,19 @@ struct BatchSizes {
 int64_t check_chunks(const gl_event *ev) { return ((int64_t)kStateVals * ev->n2 + kCheckChunk - 1) / kCheckChunk; }
 
 const int kShapeTX[kBatchShapes] = {32, 64, 16}, kShapeTY[kBatchShapes] = {4, 2, 8};
+
+// whether a batch of these events pairs each field step with the push before it:
+// as one event does (pairs), each having the buffers and all of them together
+// within the limits
+bool pairs(const gl_batch *b) {
+    size_t bytes = 0;
+    for (const gl_event *ev : b->evs) {
+        const size_t ts = ev->fp64() ? 8 : 4;
+        if (ev->L.slots == 0 || !pair_lattice(ev->n2, ts)) return false;
+        bytes += (3 * kStateVals + 2 * (size_t)kSiteRec) * ts * ev->n2;
+    }
+    return bytes <= kPairBytes && b->total_pblocks > 0 && b->total_pblocks <= pair_blocks(b->fp64);
+}
 
 gl_status batch_sizes(gl_event *const *evs, int n, BatchSizes &z) {
     if (!evs || n < 1) return fail(GL_EINVAL, "empty batch");
@@ -2049,7 +2063,9 @@ BatchEv<T> batch_desc(const gl_batch *b, int e) {
     d.f[1] = ev->fields<T>(1 - b->cur0[e]);
     d.P[0] = ev->parts<T>(b->pbuf0[e]);
     d.P[1] = ev->parts<T>(1 - b->pbuf0[e]);
-    d.F = ev->site_fields<T>();
+    d.F[0] = ev->site_fields<T>();
+    d.f[2] = b->paired ? ev->fields<T>(2) : d.f[1];
+    d.F[1] = b->paired ? (T *)(ev->ws + ev->L.F[1 - ev->fcur]) : d.F[0];
     d.partials = ev->partials();
     d.p0sum = ev->p0sum();
     d.series = ev->series();
@@ -2070,28 +2086,56 @@ int batch_sort_passes(const gl_batch *b) {
     return p;
 }
 
+// `steps` steps from the control block's.  A paired batch launches each field
+// step with the push of the step before it, the states going round the event's
+// two and the spare one and the records alternating so that the last state and
+// the last record are the event's own; else the phases follow one another
+// (a persistent walk, grid_mult > 0, is not paired).
 template <typename T>
-gl_status batch_step(gl_batch *b) {
+gl_status batch_steps(gl_batch *b, int steps) {
     const int grid = b->grid_mult > 0 ? b->grid_mult * b->cus : 0;
     const BatchEv<T> *d = (const BatchEv<T> *)(b->ws + b->desc);
     const BatchCtl *ctl = (const BatchCtl *)(b->ws + b->ctl);
-    HIP_TRY(launch_batch_fields<T>(b->stream, b->shape, d, (const int2 *)(b->ws + b->tiles[b->shape]),
-                                   b->total_tiles[b->shape], b->fpar, ctl, b->dtau, grid));
-    // a pending sort is applied by this push, which moves the particles to the other buffer
-    HIP_TRY(launch_batch_push<T>(b->stream, d, (const int2 *)(b->ws + b->pblocks), b->total_pblocks, b->fpar,
-                                 b->ppar, ctl, b->dtau, grid, (int)b->evs.size(), b->sort_pending));
-    if (b->sort_pending) b->ppar ^= 1;
-    b->sort_pending = false;
-    b->fpar ^= 1;
-    b->since_sort++;
-    if (b->any_particles && b->sort_every > 0 && b->since_sort >= b->sort_every) {
-        HIP_TRY(launch_batch_sort<T>(b->stream, d, (int)b->evs.size(), batch_sort_passes(b),
-                                     (const int2 *)(b->ws + b->pblocks),
-                                     b->total_pblocks, (const int2 *)(b->ws + b->stiles), b->total_stiles, b->ppar,
-                                     false));
-        b->sort_pending = true;
-        b->since_sort = 0;
+    const int2 *tiles = (const int2 *)(b->ws + b->tiles[b->shape]), *blocks = (const int2 *)(b->ws + b->pblocks);
+    const int64_t n_tiles = b->total_tiles[b->shape];
+    const bool pair = b->paired && grid == 0 && b->total_pblocks > 0;
+    const int own = b->fpar, other = own ^ 1;
+    auto state = [&](int i) {
+        if (!pair) return i & 1 ? other : own;
+        return i % 3 == 0 ? own : (i % 3 == 1) == (steps % 3 != 2) ? other : 2;
+    };
+    auto at = [&](int i) { return BatchAt{i, state(i), state(i + 1), pair ? (steps - 1 - i) & 1 : 0}; };
+    auto pushed = [&](int i) -> gl_status {
+        if (b->total_pblocks > 0) HIP_TRY(launch_batch_reduce<T>(b->stream, d, (int)b->evs.size(), i, ctl));
+        // a pending sort was applied by this push, which moved the particles to the other buffer
+        if (b->sort_pending) b->ppar ^= 1;
+        b->sort_pending = false;
+        b->since_sort++;
+        if (b->any_particles && b->sort_every > 0 && b->since_sort >= b->sort_every) {
+            HIP_TRY(launch_batch_sort<T>(b->stream, d, (int)b->evs.size(), batch_sort_passes(b), blocks,
+                                         b->total_pblocks, (const int2 *)(b->ws + b->stiles), b->total_stiles,
+                                         b->ppar, false));
+            b->sort_pending = true;
+            b->since_sort = 0;
+        }
+        return GL_OK;
+    };
+    for (int i = 0; i < steps; i++) {
+        if (pair && i > 0) {
+            HIP_TRY(launch_batch_pair<T>(b->stream, b->shape, d, tiles, n_tiles, at(i), blocks, b->total_pblocks,
+                                         at(i - 1), b->ppar, ctl, b->dtau, b->sort_pending));
+            if (gl_status s = pushed(i - 1)) return s;
+        } else {
+            HIP_TRY(launch_batch_fields<T>(b->stream, b->shape, d, tiles, n_tiles, at(i), ctl, b->dtau, grid));
+        }
+        if (!pair || i == steps - 1) {
+            HIP_TRY(launch_batch_push<T>(b->stream, d, blocks, b->total_pblocks, at(i), b->ppar, ctl, b->dtau, grid,
+                                         b->sort_pending));
+            if (gl_status s = pushed(i)) return s;
+        }
     }
+    HIP_TRY(launch_batch_advance(b->stream, (BatchCtl *)ctl, steps));
+    b->fpar = state(steps);
     return GL_OK;
 }
 
@@ -2107,7 +2151,9 @@ gl_status batch_apply_pending(gl_batch *b) {
     return GL_OK;
 }
 
-gl_status batch_step_any(gl_batch *b) { return b->fp64 ? batch_step<double>(b) : batch_step<float>(b); }
+gl_status batch_steps_any(gl_batch *b, int steps) {
+    return b->fp64 ? batch_steps<double>(b, steps) : batch_steps<float>(b, steps);
+}
 
 // the batch's graphs, after the stream has finished with them (a launch may
 // still be in flight when the batch is reconfigured or destroyed)
@@ -2133,8 +2179,7 @@ gl_status batch_graph(gl_batch *b, const gl_batch::Graph **out) {
     const int64_t s0 = b->since_sort;
     const bool q0 = b->sort_pending;
     HIP_TRY(hipStreamBeginCapture(b->stream, hipStreamCaptureModeRelaxed));
-    gl_status st = GL_OK;
-    for (int k = 0; k < b->graph_steps && st == GL_OK; k++) st = batch_step_any(b);
+    gl_status st = batch_steps_any(b, b->graph_steps);
     hipGraph_t g = nullptr;
     hipError_t e = hipStreamEndCapture(b->stream, &g);
     gl_batch::Graph rec;
@@ -2231,17 +2276,17 @@ gl_status time_fields(gl_batch *b, int shape, int mult, float *ms) {
     const BatchEv<T> *d = (const BatchEv<T> *)(b->ws + b->desc);
     const BatchCtl *ctl = (const BatchCtl *)(b->ws + b->ctl);
     const int2 *tiles = (const int2 *)(b->ws + b->tiles[shape]);
+    const BatchAt at{0, b->fpar, b->fpar ^ 1, 0};
     hipEvent_t e0, e1;
     HIP_TRY(hipEventCreate(&e0));
     HIP_TRY(hipEventCreate(&e1));
     // the field phases read the state at parity fpar and only write the
     // next-step buffer and the site fields: repeating them changes nothing
-    HIP_TRY(launch_batch_fields<T>(b->stream, shape, d, tiles, b->total_tiles[shape], b->fpar, ctl, b->dtau, grid));
+    HIP_TRY(launch_batch_fields<T>(b->stream, shape, d, tiles, b->total_tiles[shape], at, ctl, b->dtau, grid));
     HIP_TRY(hipEventRecord(e0, b->stream));
     const int reps = 3;
     for (int r = 0; r < reps; r++)
-        HIP_TRY(launch_batch_fields<T>(b->stream, shape, d, tiles, b->total_tiles[shape], b->fpar, ctl, b->dtau,
-                                       grid));
+        HIP_TRY(launch_batch_fields<T>(b->stream, shape, d, tiles, b->total_tiles[shape], at, ctl, b->dtau, grid));
     HIP_TRY(hipEventRecord(e1, b->stream));
     HIP_TRY(hipEventSynchronize(e1));
     HIP_TRY(hipEventElapsedTime(ms, e0, e1));
@@ -2333,7 +2378,9 @@ gl_status gl_batch_create(gl_event *const *evs, int32_t n_events, void *workspac
         b->cur0.push_back(ev->cur);
         b->pbuf0.push_back(ev->pbuf);
         b->any_particles |= ev->slots_used > 0;
+        b->total_pblocks += ev->slots_used / kPushBlock;
     }
+    b->paired = pairs(b);
     int dev = 0, cus = 0;
     if (hipGetDevice(&dev) == hipSuccess &&
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && cus > 0)
@@ -2364,7 +2411,6 @@ gl_status gl_batch_create(gl_event *const *evs, int32_t n_events, void *workspac
     std::vector<int2> pb;
     for (int e = 0; e < n_events; e++)
         for (int64_t j = 0; j < evs[e]->slots_used / kPushBlock; j++) pb.push_back(make_int2(e, (int)j));
-    b->total_pblocks = (int64_t)pb.size();
     std::vector<int2> stl;
     for (int e = 0; e < n_events; e++)
         if (evs[e]->slots_used > 0)
@@ -2481,9 +2527,13 @@ gl_status gl_batch_run(gl_batch *b, int32_t n_steps) {
             left -= b->graph_steps;
             continue;
         }
-        gl_status s = batch_step_any(b);
+        // up to where a graph may start
+        int64_t steps = left;
+        if (b->graph_steps > 0 && !aligned && left > b->graph_steps)
+            steps = std::max<int64_t>(1, b->sort_every - b->since_sort);
+        gl_status s = batch_steps_any(b, (int)std::min(left, steps));
         if (s) return s;
-        left--;
+        left -= std::min(left, steps);
     }
     // no sort is left pending when the run returns
     gl_status ap = b->fp64 ? batch_apply_pending<double>(b) : batch_apply_pending<float>(b);

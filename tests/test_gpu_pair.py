@@ -100,3 +100,36 @@ def test_batch_after_paired_runs(gl):
         a.run(5)
         _separate(b, 5)
         assert _same(_outputs(a), _outputs(b))
+
+
+@pytest.mark.parametrize("prec,shape", [(64, 0), (32, 1), (32, 2)])
+def test_paired_batch_equals_its_phases_apart(gl, prec, shape):
+    """A batch of small lattices pairs its launches (grid_mult 0); a persistent
+    walk runs the phases one after another.  Calls of every length modulo the
+    three field states, with and without a graph, across sorts; one event fails
+    and is masked from the same step on."""
+    def batch(mult):
+        evs = [_event(gl, N, prec, n) for N, n in ((31, 257), (40, 600), (4, 1), (64, 300))]
+        d = evs[1].get_particles()
+        d["p"][0, 123] = np.nan
+        evs[1].set_particles([(1.27, 2.0, gl.KIND_HEAVY_QUARK, 0.01), (0.0, 10.0, gl.KIND_JET, 0.0)],
+                             *[d[k] for k in ("cell", "off", "eta", "p", "Q", "p0", "species")])
+        b = gl.Batch(evs)
+        b.config(shape=shape, grid_mult=mult, sort_every=16, graph_steps=32)
+        return evs, b
+    (ea, a), (eb, b) = batch(0), batch(4)
+    for k in (1, 2, 3, 33, 9, 1):
+        for x in (a, b):
+            try:
+                x.run(k)
+            except gl.GlasmaError as e:
+                assert e.status == gl.GL_ENUMERIC
+        assert np.array_equal(a.status(), b.status())
+        for i, (x, y) in enumerate(zip(ea, eb)):
+            if i != 1:
+                assert _same(_outputs(x), _outputs(y)), (k, i)
+                assert np.array_equal(x.site_fields(), y.site_fields())
+    assert (a.status() > 0).tolist() == [False, True, False, False]     # once its particles have formed
+    assert np.array_equal(ea[1].series(), eb[1].series(), equal_nan=True)
+    a.close()
+    b.close()
