@@ -111,6 +111,15 @@ __global__ void __launch_bounds__(256) k_put_weights(NetView v) {
     put_weight(v, l, o, i, v.P[p]);
 }
 
+// the wave of thread t, known to the compiler as uniform and below 8: the tests
+// for a hidden layer's blocks then fold away, and with them the waits for loads
+// that another path might have left pending
+__device__ __forceinline__ int wave_of(int t) {
+    const int w = __builtin_amdgcn_readfirstlane(t >> 6);
+    __builtin_assume(w >= 0 && w < kRowThreads / 64);
+    return w;
+}
+
 // two steps of 16 over k, ascending
 __device__ __forceinline__ floatx4 mma_pair(bf16x8 a, bf16x8 b, floatx4 c) {
     c = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_shufflevector(a, a, 0, 1, 2, 3),
@@ -316,7 +325,7 @@ k_rows_infer(NetView v, const float *__restrict__ X, int64_t n, float *__restric
 // BF16 weights (k_update).  Every sum runs in the order of the general
 // kernels (weight gradients over the rows in steps of 16, biases and loss
 // over 256 strided shares and a tree), so training is bitwise the same too.
-// A step of 4096 rows of 5 -> 256 x 3 -> 2: 1350 us in 20 launches, 39 us in two.
+// A step of 4096 rows of 5 -> 256 x 3 -> 2: 1350 us in 20 launches, 37 us in two.
 struct TrainView {
     const float *X, *Y;
     const int32_t *idx;                        // sample of each row, or null: off + row
@@ -345,6 +354,21 @@ __host__ __device__ inline size_t d_off(const NetView &, int l, int max_tiles) {
     return (size_t)max_tiles * kGradBlock * kRowTiles * (size_t)l;
 }
 
+// 16 bytes at byte `at` of an array of the training step's operands (whole offset
+// in the vector offset).  They are written through (sc1): left dirty in the L2
+// caches, the 26 MB of a step of 4096 rows are written back when the kernel ends,
+// behind its work instead of beside it.  Without any of the stores the kernel
+// takes 15.1 us, with ordinary ones 21.7, written through 19.7 (the non-temporal hint
+// 19.1, but k_update then reads them from memory: 17.3 -> 20.0).
+constexpr int kOperandStore = 16;
+template <typename V>
+__device__ __forceinline__ void store_operand(void *base, uint32_t at, V v) {
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v),
+                                           __builtin_amdgcn_make_buffer_rsrc(base, (short)0, 0x7FFFFFFF, 0x00020000),
+                                           at, 0u, kOperandStore);
+}
+
 // blocks of one row tile from their LDS fragments (k along the outputs) to
 // fragments along the rows
 __device__ __forceinline__ void store_rows(const bf16x8 *act, int blocks, bf16 *__restrict__ dst) {
@@ -357,7 +381,7 @@ __device__ __forceinline__ void store_rows(const bf16x8 *act, int blocks, bf16 *
             const int ln = 2 * (u & 31) + (e >> 2), c = ln & 15, b = 4 * (ln >> 4) + (e & 3);
             x[e] = (short)a[((ob >> 1) * 64 + b + 16 * (c >> 2)) * 8 + (ob & 1) * 4 + (c & 3)];
         }
-        *(bf16x8 *)(dst + (size_t)ob * kGradBlock + (u & 31) * 8) = x;
+        store_operand(dst, (uint32_t)(ob * kGradBlock + (u & 31) * 8) * 2, x);
     }
 }
 
@@ -376,7 +400,7 @@ k_rows_train(NetView v, TrainView a) {
     __shared__ bf16x8 act[2][kRowPairs * 64];
     __shared__ float bias[(DEPTH + 1) * kRowWidth];
     __shared__ float target[16 * kRowWidth];
-    const int t = threadIdx.x, wave = t >> 6, lane = t & 63;
+    const int t = threadIdx.x, lane = t & 63, wave = wave_of(t);
     const int tile = blockIdx.x, row = 16 * tile + (lane & 15);
     const bool valid = row < a.B;
     const int o0 = 32 * wave + 4 * (lane >> 4);          // first output of the lane's two blocks: o0, o0 + 16
@@ -457,7 +481,8 @@ k_rows_train(NetView v, TrainView a) {
         }
         *act_slot(act[cur ^ 1], ot, lane) = pack_act(g, o0 + 16 * k, v.n_out);
         if (ot < v.ot_out)
-            *(floatx4 *)(a.Dz + d_off(v, DEPTH, a.max_tiles) + ((size_t)tile * v.ot_out + ot) * kGradBlock + 4 * lane) = g;
+            store_operand(a.Dz + d_off(v, DEPTH, a.max_tiles) + (size_t)tile * v.ot_out * kGradBlock,
+                          (uint32_t)(ot * kGradBlock + 4 * lane) * 4, g);
     }
     cur ^= 1;
     __syncthreads();
@@ -477,8 +502,8 @@ k_rows_train(NetView v, TrainView a) {
                 g[j] = valid && o0 + 16 * k + j < v.width ? d : 0.f;
             }
             *act_slot(act[cur ^ 1], 2 * wave + k, lane) = pack_act(g, o0 + 16 * k, v.width);
-            *(floatx4 *)(a.Dz + d_off(v, l - 1, a.max_tiles) +
-                         ((size_t)tile * kRowTiles + 2 * wave + k) * kGradBlock + 4 * lane) = g;
+            store_operand(a.Dz + d_off(v, l - 1, a.max_tiles) + (size_t)tile * kRowTiles * kGradBlock,
+                          (uint32_t)((2 * wave + k) * kGradBlock + 4 * lane) * 4, g);
         }
         cur ^= 1;
         __syncthreads();
