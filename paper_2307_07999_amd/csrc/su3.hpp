@@ -566,6 +566,12 @@ constexpr int kLinkVals = 12;            // stored values of a link (its first t
 // 969 ms).  kStreamed<T> is the single-event choice.
 constexpr int kNonTemporal = 2;
 constexpr int stream_policy(bool streamed) { return streamed ? kNonTemporal : 0; }
+// Every 16-byte store is written through the L2 caches (sc1): what a kernel
+// leaves dirty there (up to 4 MB an XCD) is written back when it ends, behind its
+// work instead of beside it.  512^2: FP32 field step 35.9 -> 33.8 us and push 36.9 ->
+// 35.8, FP64 field step 68.6 -> 67.4; paired FP64 step at 243^2 34.0 -> 32.9; 24 FP32
+// events of 256^2 in a batch 229 -> 227.
+constexpr int kWriteThrough = 16;
 template <typename T>
 constexpr bool kStreamed = sizeof(T) == 8;
 
@@ -668,7 +674,7 @@ __device__ __forceinline__ void chunk_st16(T *p, size_t n2, size_t x, int k, con
 #pragma unroll
     for (int i = 0; i < NV; i++) r.v[i] = in[i];
     __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, r), buf(p),
-                                           (uint32_t)((x + (size_t)(k / NV) * n2) * 16), 0u, CP);
+                                           (uint32_t)((x + (size_t)(k / NV) * n2) * 16), 0u, CP | kWriteThrough);
 }
 
 
@@ -702,7 +708,7 @@ __device__ __forceinline__ void chunk_st16_l(T *p, size_t n2, size_t x, int k, c
     V r;
 #pragma unroll
     for (int i = 0; i < (int)(16 / sizeof(T)); i++) r.v[i] = in[i];
-    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, r), buf(p), chunk_off<T>(n2, x, k), 0u, CP);
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, r), buf(p), chunk_off<T>(n2, x, k), 0u, CP | kWriteThrough);
 }
 // n values k0.. (k0 and n multiples of 16 / sizeof(T)), lane-dependent k0
 template <int n, int CP = 0, typename T>
@@ -758,8 +764,8 @@ __device__ __forceinline__ void site_store_pair(T *p, size_t x, int k0, int k1, 
             b.v[i] = d ? v[k + NV + i] : even;
         }
         const uint32_t step = (uint32_t)(k / NV * kSiteGroup * 16);
-        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, a), buf(p), at0 + step, 0u, 0);
-        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, b), buf(p), at1 + step, 0u, 0);
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, a), buf(p), at0 + step, 0u, kWriteThrough);
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, b), buf(p), at1 + step, 0u, kWriteThrough);
     }
 }
 template <int n, typename T>
@@ -774,7 +780,7 @@ __device__ __forceinline__ void site_store(T *p, size_t x, int k0, const T *v) {
 #pragma unroll
         for (int i = 0; i < NV; i++) r.v[i] = v[k + i];
         __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, r), buf(p),
-                                               at + (uint32_t)(k / NV * kSiteGroup * 16), 0u, 0);
+                                               at + (uint32_t)(k / NV * kSiteGroup * 16), 0u, kWriteThrough);
     }
 }
 
