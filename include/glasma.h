@@ -455,8 +455,9 @@ gl_status gl_mlp_infer(gl_mlp *m, const float *X, float *Y, int64_t n);
  * forbid allocation): the same outputs as gl_mlp_infer, bit for bit, with its
  * staging and activation buffers in a fixed 4 MiB device array of the library
  * instead of the model's workspace.  X [n][n_in], Y [n][n_out] are device
- * FP32 arrays of the caller; rows go through in passes of as many as fit
- * (about 4000 at width 256).  The device of the model's stream must be the
+ * FP32 arrays of the caller.  A network of at most 256 inputs, outputs and hidden
+ * units and 4 hidden layers runs whole, in one launch without that array; for
+ * others rows go through in passes of as many as fit (about 4000 at width 256).  The device of the model's stream must be the
  * current device; the array's address on that device is looked up on the
  * first call there.  Every call on one device uses that device's one array,
  * so calls that overlap on a device (concurrent streams or threads) race.

@@ -3,7 +3,7 @@
 //   1. Gaussian color charges rho^a per (nucleus, sheet, site) from Philox,
 //      packed two colors per complex plane (rho^{2j} + i rho^{2j+1}).
 //   2. Poisson solve (-Lap + m^2) Lambda = rho with the 5-point Laplacian,
-//      exact in Fourier space: 2-D FFT by LDS-resident mixed-radix (8, 4, 2, 3)
+//      exact in Fourier space: 2-D FFT by LDS-resident mixed-radix (8, 4, 2, 9, 3)
 //      Stockham line transforms, several adjacent lines per workgroup; the
 //      kernel multiplication sits between the forward and inverse column
 //      transforms of one pass.  The kernel is real and even, so the packed
@@ -393,7 +393,7 @@ k_fft_tables(int N, FftPlan p, double2 *__restrict__ tw, double *__restrict__ s2
 // three back, out) the direct ends, and the last stage forward, the product and
 // the first back in registers, leave 8; and the staged twiddles meet no bank
 // twice.  Eight sheets of 512^2, 134 MB of planes: columns 84 -> 57 us, inverse
-// rows 48 -> 38, forward rows with the draw 85 -> 78 (bound by the draw's
+// rows 48 -> 38, forward rows with the draw 85 -> 76 (bound by the draw's
 // arithmetic: 172 FP64 instructions a pair, most of them the logarithm's and the
 // sine's).  3^5, both nuclei and 17 sheets: columns 136 -> 83.
 constexpr int kFftLines = 0, kFftPoisson = 1, kFftDraw = 2;
@@ -432,10 +432,8 @@ k_fft_lines(double2 *data, int N, int groups_per_plane, int sign, FftPlan fp, do
     // bound by memory is slower for it (inverse rows 38.9 -> 42.1)
     auto output = [&](int line, int i, double2 v) {
         typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-        if constexpr (MODE == kFftDraw)
-            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), gl::buf(base), place(line, i) * 16u,
-                                                   0u, kWriteThrough);
-        else base[place(line, i)] = v;
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), gl::buf(base), place(line, i) * 16u, 0u,
+                                               MODE == kFftDraw ? kWriteThrough : 0);
     };
     if constexpr (POISSON) {
         const double nn = (double)N * (double)N;

@@ -27,7 +27,8 @@ constexpr int kPushBlock = 256;   // particles per push workgroup
 // Four sites are 1 KiB a record group in FP32, and a pair of chunks of them one
 // 128-byte line, which the field step's lane pairs write together.  Push / field
 // step, us, of 24 events of 256^2 with 10^4 particles each, of ten events of
-// 128^2 to 512^2 with up to 10^6, and of 512^2 with 7 10^5 in FP32 and FP64:
+// 128^2 to 512^2 with up to 10^6, and of 512^2 with 7 10^5 in FP32 and FP64 (with
+// stores that stayed in L2; written through, the field step is 2 us shorter):
 //   planes     92 / 216   231 / 203   36.8 / 34.7   65.8 / 67.2
 //   8 sites    92 / 218   229 / 203   36.3 / 34.8   64.8 / 66.9
 //   4 sites    66 / 220   219 / 204   36.5 / 35.0   63.9 / 68.2
