@@ -456,8 +456,13 @@ gl_status sync_weights(gl_mlp *m) {
     return GL_OK;
 }
 
-// rows per workgroup of the whole-network inference: 64 once that many fill
-// the chip's workgroup slots (two a compute unit), else 32 or 16
+// Rows per workgroup of the whole-network inference: the fewest that take all
+// rows in one round of workgroups, since a round costs its own chain of layers
+// whatever it holds: 16 on the chip's 256 compute units, 32 or 48 on its 512
+// places, else 64, whose rounds cost least a row.  5 -> 256 x 3 -> 2, us with
+// 16 / 32 / 48 / 64 rows: 4096 rows 9.9 / 12.7 / 15.8 / 18.7, 5000 16.7 / 12.6 / 15.9 /
+// 18.6, 16384 31.8 / 16.2 / 20.6 / 18.7, 20000 38.9 / 24.8 / 20.7 / 23.9, 24576 46.2 / 25.1 /
+// 21.0 / 24.0, 26240 52.9 / 29.9 / 31.5 / 24.0, 65536 117 / 57.0 / 55.3 / 46.5.
 template <int RT>
 void launch_rows(gl_mlp *m, const float *X, float *Y, int64_t n) {
     hipLaunchKernelGGL((k_rows_infer<RT, RT == 1>), dim3(nb(n, 16 * RT)), dim3(kRowThreads),
@@ -469,9 +474,10 @@ gl_status infer_rows(gl_mlp *m, const float *X, float *Y, int64_t n) {
         const int64_t b = std::min(kPass, n - r0);
         const float *x = X + r0 * m->d.n_in;
         float *y = Y + r0 * m->d.n_out;
-        if (b >= 32768) launch_rows<4>(m, x, y, b);
-        else if (b > 4096) launch_rows<2>(m, x, y, b);
-        else launch_rows<1>(m, x, y, b);
+        if (b <= 256 * 16) launch_rows<1>(m, x, y, b);
+        else if (b <= 512 * 32) launch_rows<2>(m, x, y, b);
+        else if (b <= 512 * 48) launch_rows<3>(m, x, y, b);
+        else launch_rows<4>(m, x, y, b);
         MHIP(hipGetLastError());
     }
     return GL_OK;

@@ -168,3 +168,16 @@ def test_inference_does_not_depend_on_the_rows_of_a_call(gl):
     small = torch.cat([net.infer(x.contiguous()) for x in X.split(3001)])
     for n in (33000, 32767, 4097, 4096):
         assert torch.equal(net.infer(X[:n].contiguous()), small[:n])
+
+
+@pytest.mark.parametrize("shape", [(5, 256, 3, 2), (40, 33, 2, 70)])
+@pytest.mark.parametrize("n", [4097, 16384, 16385, 24576, 24577])
+def test_rows_a_workgroup(gl, shape, n):
+    """16, 32, 48 or 64 rows a workgroup by the rows of the call: on either side of
+    each line the outputs are those of calls of 16 rows a workgroup."""
+    import torch
+    net = gl.MLP(*shape, max_batch=64, max_samples=8, seed=7)
+    net.set_scaling(np.zeros(shape[0]), np.ones(shape[0]), np.full(shape[3], 0.25), np.full(shape[3], 0.5))
+    X = torch.from_numpy(np.random.default_rng(n).uniform(-1, 2, (n, shape[0])).astype(np.float32)).to("cuda")
+    parts = [net.infer(X[k:k + 4096]).cpu().numpy() for k in range(0, n, 4096)]
+    assert np.array_equal(net.infer(X).cpu().numpy(), np.concatenate(parts))
