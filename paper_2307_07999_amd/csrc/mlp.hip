@@ -469,7 +469,9 @@ void launch_rows(gl_mlp *m, const float *X, float *Y, int64_t n) {
                        (m->v.depth + 1) * kRowWidth * sizeof(float), m->st, m->v, X, n, Y);
 }
 gl_status infer_rows(gl_mlp *m, const float *X, float *Y, int64_t n) {
-    constexpr int64_t kPass = (int64_t)1 << 30;   // rows of one launch
+    // rows of one launch: its work items are counted in 32 bits
+    constexpr int64_t kPass = (int64_t)1 << 28;
+    static_assert(kPass / (16 * 4) * kRowThreads < (int64_t)1 << 32, "64 rows a workgroup");
     for (int64_t r0 = 0; r0 < n; r0 += kPass) {
         const int64_t b = std::min(kPass, n - r0);
         const float *x = X + r0 * m->d.n_in;

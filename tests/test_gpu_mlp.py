@@ -181,3 +181,17 @@ def test_rows_a_workgroup(gl, shape, n):
     X = torch.from_numpy(np.random.default_rng(n).uniform(-1, 2, (n, shape[0])).astype(np.float32)).to("cuda")
     parts = [net.infer(X[k:k + 4096]).cpu().numpy() for k in range(0, n, 4096)]
     assert np.array_equal(net.infer(X).cpu().numpy(), np.concatenate(parts))
+
+
+def test_half_a_billion_rows(gl):
+    """More rows than the work items of one launch can take (2^29 rows of 64 a
+    workgroup of 512 are 2^32): the call goes in passes, each row as in a call of
+    its own.  The input repeats, so the outputs have to as well."""
+    import torch
+    net = gl.MLP(1, 40, 1, 1, max_batch=64, max_samples=8, seed=8)
+    x = torch.rand(1 << 20, 1, generator=torch.Generator().manual_seed(3)).cuda()
+    want = net.infer(x)
+    X = x.repeat(513, 1)
+    for got in (net.infer(X), net.infer_noalloc(X)):
+        assert bool((got.view(513, 1 << 20) == want.view(1, 1 << 20)).all())
+        del got
