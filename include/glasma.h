@@ -449,15 +449,18 @@ gl_status gl_mlp_set_output_power(gl_mlp *m, int32_t col, const float *powers);
  * mean standardised MSE of each epoch. */
 gl_status gl_mlp_train(gl_mlp *m, const float *X, const float *Y, int64_t n, int32_t epochs,
                        int32_t batch, float lr, uint64_t seed, float *loss_per_epoch);
+/* Outputs Y [n][n_out] of the n rows of X.  Y may be X itself (in place) where
+ * n_out <= n_in and no output power is set; other overlaps are undefined. */
 gl_status gl_mlp_infer(gl_mlp *m, const float *X, float *Y, int64_t n);
 /* Inference that allocates nothing, for callers that cannot allocate device
  * memory (code under HIP graph capture, tight serving loops, harnesses that
  * forbid allocation): the same outputs as gl_mlp_infer, bit for bit, with its
  * staging and activation buffers in a fixed 4 MiB device array of the library
  * instead of the model's workspace.  X [n][n_in], Y [n][n_out] are device
- * FP32 arrays of the caller.  A network of at most 256 inputs, outputs and hidden
- * units and 4 hidden layers runs whole, in one launch without that array; for
- * others rows go through in passes of as many as fit (about 4000 at width 256).  The device of the model's stream must be the
+ * FP32 arrays of the caller (Y may be X as there).  A network of at most 256
+ * inputs, outputs and hidden units and 4 hidden layers runs whole, in one launch
+ * (in place through that array); for others rows go through in passes of as many
+ * as fit (about 4000 at width 256).  The device of the model's stream must be the
  * current device; the array's address on that device is looked up on the
  * first call there.  Every call on one device uses that device's one array,
  * so calls that overlap on a device (concurrent streams or threads) race.

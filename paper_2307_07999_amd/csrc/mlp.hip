@@ -208,6 +208,11 @@ k_unscale(const float *__restrict__ Z, int B, int nout, const float *__restrict_
     Y[i] = y;
 }
 
+__global__ void __launch_bounds__(256) k_copy(const float *__restrict__ from, float *__restrict__ to, int64_t n) {
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i < n) to[i] = from[i];
+}
+
 __global__ void k_zero1(float *p) {
     if (threadIdx.x == 0) *p = 0.f;
 }
@@ -485,6 +490,27 @@ gl_status infer_rows(gl_mlp *m, const float *X, float *Y, int64_t n) {
     return GL_OK;
 }
 
+// whether the outputs of n rows overlap their inputs
+bool rows_overlap(const gl_mlp *m, const float *X, const float *Y, int64_t n) {
+    const uintptr_t x = (uintptr_t)X, y = (uintptr_t)Y;
+    return y < x + (size_t)n * m->d.n_in * sizeof(float) && x < y + (size_t)n * m->d.n_out * sizeof(float);
+}
+
+// infer_rows for such arrays: a workgroup would write its rows' outputs while
+// others have not read their inputs yet, so the rows go in passes of `pass`, whose
+// outputs are copied to Y from `stage` when all inputs of the pass are read (with
+// n_out <= n_in, in place, no later pass's inputs are overwritten).
+gl_status infer_rows_over(gl_mlp *m, const float *X, float *Y, int64_t n, float *stage, int64_t pass) {
+    const int ni = m->d.n_in, no = m->d.n_out;
+    for (int64_t r0 = 0; r0 < n; r0 += pass) {
+        const int64_t b = std::min(pass, n - r0);
+        if (gl_status s = infer_rows(m, X + r0 * ni, stage, b)) return s;
+        hipLaunchKernelGGL(k_copy, dim3(nb(b * no, 256)), dim3(256), 0, m->st, (const float *)stage, Y + r0 * no, b * no);
+        MHIP(hipGetLastError());
+    }
+    return GL_OK;
+}
+
 // one pass of the whole-network training kernels over B rows (sample idx[off + r],
 // or off + r without idx): the loss is added to m->loss and the update done
 // (adam), or the gradients left in G (adam null)
@@ -660,7 +686,9 @@ gl_status gl_mlp_train(gl_mlp *m, const float *X, const float *Y, int64_t n, int
 gl_status gl_mlp_infer(gl_mlp *m, const float *X, float *Y, int64_t n) {
     if (!m || !X || !Y) return mfail(GL_EINVAL, "null argument");
     if (n < 0) return mfail(GL_EINVAL, "n must be >= 0");
-    if (m->fused) return infer_rows(m, X, Y, n);
+    // dH holds max_batch x max(width, n_in, n_out) floats
+    if (m->fused)
+        return rows_overlap(m, X, Y, n) ? infer_rows_over(m, X, Y, n, m->dH, m->d.max_batch) : infer_rows(m, X, Y, n);
     const int B = m->d.max_batch;
     for (int64_t off = 0; off < n; off += B) {
         int b = (int)std::min<int64_t>(B, n - off);
@@ -740,9 +768,11 @@ gl_status gl_mlp_infer_noalloc(gl_mlp *m, const float *X, float *Y, int64_t n) {
     hipDevice_t sdev = dev;
     if (m->st) MHIP(hipStreamGetDevice(m->st, &sdev));
     if (sdev != dev) return mfail(GL_EINVAL, "the device of the model's stream is not the current device");
-    if (m->fused) return infer_rows(m, X, Y, n);   // needs no scratch
+    const bool over = rows_overlap(m, X, Y, n);
+    if (m->fused && !over) return infer_rows(m, X, Y, n);   // needs no scratch
     void *base = nullptr;
     if (gl_status s = infer_scratch_address(dev, &base)) return s;
+    if (m->fused) return infer_rows_over(m, X, Y, n, (float *)base, R);
     char *sp = (char *)base;
     size_t off = 0;
     auto carve = [&](size_t bytes) {

@@ -195,3 +195,21 @@ def test_half_a_billion_rows(gl):
     for got in (net.infer(X), net.infer_noalloc(X)):
         assert bool((got.view(513, 1 << 20) == want.view(1, 1 << 20)).all())
         del got
+
+
+@pytest.mark.parametrize("shape", [(5, 256, 3, 2), (40, 33, 1, 40), (5, 257, 2, 2)])
+@pytest.mark.parametrize("noalloc", [False, True])
+def test_inference_in_place(gl, shape, noalloc):
+    """Outputs written over the inputs (n_out <= n_in): those of separate
+    arrays, over several passes.  The last shape runs layer by layer."""
+    import ctypes
+    import torch
+    n, ni, no = 70001, shape[0], shape[3]
+    net = gl.MLP(*shape, max_batch=2048, max_samples=8, seed=7)
+    net.set_scaling(np.zeros(ni), np.ones(ni), np.full(no, 0.25), np.full(no, 0.5))
+    X = torch.rand(n, ni, generator=torch.Generator().manual_seed(4)).cuda()
+    want = net.infer(X)
+    fn = gl.lib().gl_mlp_infer_noalloc if noalloc else gl.lib().gl_mlp_infer
+    assert fn(net._h, ctypes.c_void_p(X.data_ptr()), ctypes.c_void_p(X.data_ptr()), n) == 0
+    torch.cuda.synchronize()
+    assert torch.equal(X.view(-1)[:n * no], want.view(-1))
