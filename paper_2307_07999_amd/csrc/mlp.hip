@@ -296,6 +296,7 @@ NetView net_view(const gl_mlp_desc &d, int64_t n_w) {
     v.kp_in = (d.n_in + 31) / 32;
     v.ot_out = (d.n_out + 15) / 16;
     v.kp_out = (d.n_out + 31) / 32;
+    v.hb = (d.width + 15) / 16;
     v.pcol = -1;
     v.n_w = n_w;
     return v;
@@ -468,10 +469,24 @@ gl_status sync_weights(gl_mlp *m) {
 // 16 / 32 / 48 / 64 rows: 4096 rows 9.9 / 12.7 / 15.8 / 18.7, 5000 16.7 / 12.6 / 15.9 /
 // 18.6, 16384 31.8 / 16.2 / 20.6 / 18.7, 20000 38.9 / 24.8 / 20.7 / 23.9, 24576 46.2 / 25.1 /
 // 21.0 / 24.0, 26240 52.9 / 29.9 / 31.5 / 24.0, 65536 117 / 57.0 / 55.3 / 46.5.
-template <int RT>
+// A narrower network's workgroup takes that many rows per group (row_waves).
+template <int RT, int KP>
 void launch_rows(gl_mlp *m, const float *X, float *Y, int64_t n) {
-    hipLaunchKernelGGL((k_rows_infer<RT, RT == 1>), dim3(nb(n, 16 * RT)), dim3(kRowThreads),
+    hipLaunchKernelGGL((k_rows_infer<RT, RT == 1, KP>), dim3(nb(n, 16 * RT * (kRowPairs / KP))), dim3(kRowThreads),
                        (m->v.depth + 1) * kRowWidth * sizeof(float), m->st, m->v, X, n, Y);
+}
+template <int KP>
+void launch_rows_of(gl_mlp *m, const float *X, float *Y, int64_t n) {
+    constexpr int64_t groups = kRowPairs / KP;
+    if (n <= groups * 256 * 16) launch_rows<1, KP>(m, X, Y, n);
+    else if (n <= groups * 512 * 32) launch_rows<2, KP>(m, X, Y, n);
+    else if (n <= groups * 512 * 48) launch_rows<3, KP>(m, X, Y, n);
+    else launch_rows<4, KP>(m, X, Y, n);
+}
+// waves that hold the network's widest layer, 32 outputs each, as a power of two
+int row_waves(const gl_mlp_desc &d) {
+    const int w = std::max(d.width, std::max(d.n_in, d.n_out));
+    return w <= 32 ? 1 : w <= 64 ? 2 : w <= 128 ? 4 : 8;
 }
 gl_status infer_rows(gl_mlp *m, const float *X, float *Y, int64_t n) {
     // rows of one launch: its work items are counted in 32 bits
@@ -481,10 +496,12 @@ gl_status infer_rows(gl_mlp *m, const float *X, float *Y, int64_t n) {
         const int64_t b = std::min(kPass, n - r0);
         const float *x = X + r0 * m->d.n_in;
         float *y = Y + r0 * m->d.n_out;
-        if (b <= 256 * 16) launch_rows<1>(m, x, y, b);
-        else if (b <= 512 * 32) launch_rows<2>(m, x, y, b);
-        else if (b <= 512 * 48) launch_rows<3>(m, x, y, b);
-        else launch_rows<4>(m, x, y, b);
+        switch (row_waves(m->d)) {
+            case 1: launch_rows_of<1>(m, x, y, b); break;
+            case 2: launch_rows_of<2>(m, x, y, b); break;
+            case 4: launch_rows_of<4>(m, x, y, b); break;
+            default: launch_rows_of<8>(m, x, y, b); break;
+        }
         MHIP(hipGetLastError());
     }
     return GL_OK;
@@ -520,12 +537,17 @@ gl_status step_rows(gl_mlp *m, const float *X, const float *Y, const int32_t *id
     const int tiles = (B + 15) / 16;
     const float scale = 1.f / (float)(B * v.n_out);
     const TrainView a{X, Y, idx, off, B, scale, m->max_tiles, m->Hf, m->Df, m->Dz, m->dev};
+    const bool full = v.hb == kRowTiles;
+#define GL_TRAIN(D)                                                                                              \
+    if (full) hipLaunchKernelGGL((k_rows_train<D, true>), dim3(tiles), dim3(kRowThreads), 0, m->st, v, a);      \
+    else hipLaunchKernelGGL((k_rows_train<D, false>), dim3(tiles), dim3(kRowThreads), 0, m->st, v, a)
     switch (v.depth) {
-        case 1: hipLaunchKernelGGL(k_rows_train<1>, dim3(tiles), dim3(kRowThreads), 0, m->st, v, a); break;
-        case 2: hipLaunchKernelGGL(k_rows_train<2>, dim3(tiles), dim3(kRowThreads), 0, m->st, v, a); break;
-        case 3: hipLaunchKernelGGL(k_rows_train<3>, dim3(tiles), dim3(kRowThreads), 0, m->st, v, a); break;
-        default: hipLaunchKernelGGL(k_rows_train<4>, dim3(tiles), dim3(kRowThreads), 0, m->st, v, a); break;
+        case 1: GL_TRAIN(1); break;
+        case 2: GL_TRAIN(2); break;
+        case 3: GL_TRAIN(3); break;
+        default: GL_TRAIN(4); break;
     }
+#undef GL_TRAIN
     MHIP(hipGetLastError());
     int wgs = bias_groups(v) + 1;
     for (int l = 0; l <= v.depth; l++) wgs += weight_groups(v, l);

@@ -52,6 +52,7 @@ constexpr int kRowMaxDepth = 4;                // hidden layers of the training 
 struct NetView {
     int n_in, width, depth, n_out;
     int kp_in, ot_out, kp_out;                 // 32-wide k steps of the inputs, 16-blocks and 32-steps of the outputs
+    int hb;                                    // 16-blocks of a hidden layer
     int pcol;
     int64_t n_w;                               // weights; the biases follow in P
     const float *P, *sc;
@@ -128,25 +129,27 @@ __device__ __forceinline__ floatx4 mma_pair(bf16x8 a, bf16x8 b, floatx4 c) {
                                                      __builtin_shufflevector(b, b, 4, 5, 6, 7), c, 0, 0, 0);
 }
 
-// a wave's fragments: blocks 2 wave, 2 wave + 1 of n_blocks, kp steps
+// a wave's fragments: blocks 2 wave, 2 wave + 1 of n_blocks, the first KP of kp steps
+template <int KP = kRowPairs>
 struct WaveWeights {
-    bf16x8 w[2][kRowPairs];
+    bf16x8 w[2][KP];
 };
-__device__ __forceinline__ void load_weights(WaveWeights &r, const bf16 *__restrict__ frags, int wave, int lane,
+template <int KP>
+__device__ __forceinline__ void load_weights(WaveWeights<KP> &r, const bf16 *__restrict__ frags, int wave, int lane,
                                              int n_blocks, int kp) {
 #pragma unroll
     for (int t = 0; t < 2; t++) {
         const int ot = 2 * wave + t;
         const bf16x8 *f = (const bf16x8 *)frags + (size_t)ot * kp * 64 + lane;
 #pragma unroll
-        for (int k = 0; k < kRowPairs; k++)
+        for (int k = 0; k < KP; k++)
             if (ot < n_blocks && k < kp) r.w[t][k] = f[(size_t)k * 64];
     }
 }
 
 // acc[rt][t] = sum over k of the wave's blocks times row tile rt (LDS fragments [rt][kp][lane])
-template <int RT>
-__device__ __forceinline__ void layer_product(const WaveWeights &r, const bf16x8 *act, int act_stride, int wave,
+template <int RT, int KP>
+__device__ __forceinline__ void layer_product(const WaveWeights<KP> &r, const bf16x8 *act, int act_stride, int wave,
                                               int lane, int n_blocks, int kp, floatx4 (&acc)[RT][2]) {
 #pragma unroll
     for (int rt = 0; rt < RT; rt++)
@@ -154,7 +157,7 @@ __device__ __forceinline__ void layer_product(const WaveWeights &r, const bf16x8
         for (int t = 0; t < 2; t++) acc[rt][t] = floatx4{0.f, 0.f, 0.f, 0.f};
     if (2 * wave >= n_blocks) return;
 #pragma unroll
-    for (int k = 0; k < kRowPairs; k++)
+    for (int k = 0; k < KP; k++)
         if (k < kp) {
 #pragma unroll
             for (int rt = 0; rt < RT; rt++) {
@@ -215,7 +218,10 @@ __device__ __forceinline__ bf16x4 *act_slot(bf16x8 *act, int ot, int lane) {
 }
 
 // ---- inference -----------------------------------------------------------------
-// 16 RT rows a workgroup, all layers, outputs in physical units.
+// 16 RT rows a group of KP waves, all layers, outputs in physical units.  A group
+// holds layers (inputs and outputs too) of up to 32 KP, its waves 32 outputs each:
+// networks up to 32, 64 and 128 wide run as 8, 4 and 2 groups a workgroup, each with
+// rows of its own.
 //
 // RT = 4, many rows: bound by the SiLU (exponential and IEEE division, about 20
 // vector instructions per activation) beside the MFMAs; each weight load
@@ -225,23 +231,26 @@ __device__ __forceinline__ bf16x4 *act_slot(bf16x8 *act, int ot, int lane) {
 // weights; with the registers of one workgroup a compute unit, the next
 // layer's weights are loaded a whole layer ahead (AHEAD).
 // 5 -> 256 x 3 -> 2, against six launches per 4096 rows: 10^6 rows 20.5 -> 0.67 ms,
-// 410 rows 83 -> 11 us on the device.
-template <int RT, bool AHEAD>
+// 410 rows 83 -> 11 us on the device.  Narrow networks, 2^20 rows through 5 -> 8 x 3 -> 2
+// and 5 -> 32 x 4 -> 2: 676 and 901 us padded to 256, 83 and 97 in groups (161 and 438
+// layer by layer in one pass of all rows).
+template <int RT, bool AHEAD, int KP>
 __global__ void __launch_bounds__(kRowThreads, AHEAD ? 2 : 4)
 k_rows_infer(NetView v, const float *__restrict__ X, int64_t n, float *__restrict__ Y) {
-    __shared__ bf16x8 act[2][RT * kRowPairs * 64];
+    constexpr int kGroups = kRowPairs / KP, kStride = KP * 64;
+    __shared__ bf16x8 act[2][kGroups * RT * kStride];
     extern __shared__ float bias[];            // [depth + 1][kRowWidth]
-    constexpr int kStride = kRowPairs * 64;
-    const int t = threadIdx.x, wave = t >> 6, lane = t & 63;
-    const int64_t r0 = (int64_t)blockIdx.x * (16 * RT);
-    WaveWeights w[AHEAD ? 2 : 1];
-    auto fetch = [&](WaveWeights &r, int l) {
+    const int t = threadIdx.x, group = kGroups > 1 ? (t >> 6) / KP : 0, wave = (t >> 6) - group * KP, lane = t & 63;
+    const int64_t r0 = (int64_t)blockIdx.x * (16 * RT * kGroups);
+    const int mine = group * RT * kStride;     // the group's part of act
+    WaveWeights<KP> w[AHEAD ? 2 : 1];
+    auto fetch = [&](WaveWeights<KP> &r, int l) {
         load_weights(r, v.Wf + frag_off(v, l), wave, lane, l == v.depth ? v.ot_out : kRowTiles, layer_pairs(v, l));
     };
     fetch(w[0], 0);
     if constexpr (AHEAD) fetch(w[1], 1);
     stage_biases(v, bias);
-    for (int u = t; u < RT * v.kp_in * 64; u += kRowThreads) {
+    for (int u = t; u < kGroups * RT * v.kp_in * 64; u += kRowThreads) {
         const int ln = u & 63, kp = (u >> 6) % v.kp_in, rt = (u >> 6) / v.kp_in;
         const int64_t row = r0 + 16 * rt + (ln & 15);
         bf16x8 x = {0, 0, 0, 0, 0, 0, 0, 0};
@@ -256,8 +265,8 @@ k_rows_infer(NetView v, const float *__restrict__ X, int64_t n, float *__restric
     __syncthreads();
     floatx4 acc[RT][2];
     int cur = 0;
-    auto hidden = [&](WaveWeights &r, int l) {
-        layer_product<RT>(r, act[cur], kStride, wave, lane, kRowTiles, layer_pairs(v, l), acc);
+    auto hidden = [&](WaveWeights<KP> &r, int l) {
+        layer_product<RT>(r, act[cur] + mine, kStride, wave, lane, kRowTiles, layer_pairs(v, l), acc);
         if (l + (AHEAD ? 2 : 1) <= v.depth) fetch(r, l + (AHEAD ? 2 : 1));
 #pragma unroll
         for (int k = 0; k < 2; k++) {
@@ -266,14 +275,14 @@ k_rows_infer(NetView v, const float *__restrict__ X, int64_t n, float *__restric
 #pragma unroll
             for (int rt = 0; rt < RT; rt++) {
                 const floatx4 h = silu4(acc[rt][k] + b);
-                *act_slot(act[cur ^ 1] + rt * kStride, 2 * wave + k, lane) = pack_act(h, o, v.width);
+                *act_slot(act[cur ^ 1] + mine + rt * kStride, 2 * wave + k, lane) = pack_act(h, o, v.width);
             }
         }
         cur ^= 1;
         __syncthreads();
     };
-    auto outputs = [&](const WaveWeights &r) {
-        layer_product<RT>(r, act[cur], kStride, wave, lane, v.ot_out, kRowPairs, acc);
+    auto outputs = [&](const WaveWeights<KP> &r) {
+        layer_product<RT>(r, act[cur] + mine, kStride, wave, lane, v.ot_out, kRowPairs, acc);
     };
     if constexpr (AHEAD) {
         int l = 0;
@@ -294,7 +303,8 @@ k_rows_infer(NetView v, const float *__restrict__ X, int64_t n, float *__restric
     // a wave turns its blocks into rows through its share of the other buffer,
     // so that all its lanes work on the few real outputs
     const float *sc_out = v.sc + 2 * v.n_in;
-    float *zb = (float *)act[cur ^ 1] + wave * (16 * 16 * RT);
+    float *zb = (float *)act[cur ^ 1] + (t >> 6) * (16 * 16 * RT);
+    const int64_t g0 = r0 + group * (16 * RT);
 #pragma unroll
     for (int k = 0; k < 2; k++) {
         const int ot = 2 * wave + k;
@@ -309,7 +319,7 @@ k_rows_infer(NetView v, const float *__restrict__ X, int64_t n, float *__restric
 #pragma unroll 1
         for (int e = lane; e < 16 * RT * cols; e += 64) {
             const int r = e / cols, c = e - r * cols;
-            const int64_t row = r0 + r;
+            const int64_t row = g0 + r;
             if (row >= n) break;
             float y = zb[r * 16 + c] * sc_out[v.n_out + 16 * ot + c] + sc_out[16 * ot + c];
             if (v.pcol >= 0) y *= powf(X[row * v.n_in + v.pcol], sc_out[2 * v.n_out + 16 * ot + c]);
@@ -345,13 +355,13 @@ struct TrainView {
 
 constexpr int kGradBlock = 256;                // elements of one 16 x 16 block
 
-__host__ __device__ inline int in_blocks(const NetView &v, int l) { return l == 0 ? (v.n_in + 15) / 16 : kRowTiles; }
-__host__ __device__ inline int out_blocks(const NetView &v, int l) { return l == v.depth ? v.ot_out : kRowTiles; }
+__host__ __device__ inline int in_blocks(const NetView &v, int l) { return l == 0 ? (v.n_in + 15) / 16 : v.hb; }
+__host__ __device__ inline int out_blocks(const NetView &v, int l) { return l == v.depth ? v.ot_out : v.hb; }
 __host__ __device__ inline size_t h_off(const NetView &v, int l, int max_tiles) {
-    return l == 0 ? 0 : (size_t)max_tiles * kGradBlock * (in_blocks(v, 0) + (size_t)(l - 1) * kRowTiles);
+    return l == 0 ? 0 : (size_t)max_tiles * kGradBlock * (in_blocks(v, 0) + (size_t)(l - 1) * v.hb);
 }
-__host__ __device__ inline size_t d_off(const NetView &, int l, int max_tiles) {
-    return (size_t)max_tiles * kGradBlock * kRowTiles * (size_t)l;
+__host__ __device__ inline size_t d_off(const NetView &v, int l, int max_tiles) {
+    return (size_t)max_tiles * kGradBlock * v.hb * (size_t)l;
 }
 
 // 16 bytes at byte `at` of an array of the training step's operands (whole offset
@@ -394,7 +404,10 @@ __device__ __forceinline__ void store_rows(const bf16x8 *act, int blocks, bf16 *
 // between.  Hence the weights of a layer are loaded a whole layer ahead, the
 // biases and targets at the start, and 16 rows a workgroup spread such a batch
 // over the whole chip.
-template <int DEPTH>
+//
+// FULL: hidden layers of all 16 blocks.  Narrower ones compute on the padding
+// (their batches are bound by the same chain) but store their own blocks only.
+template <int DEPTH, bool FULL>
 __global__ void __launch_bounds__(kRowThreads, 2)
 k_rows_train(NetView v, TrainView a) {
     __shared__ bf16x8 act[2][kRowPairs * 64];
@@ -403,9 +416,10 @@ k_rows_train(NetView v, TrainView a) {
     const int t = threadIdx.x, lane = t & 63, wave = wave_of(t);
     const int tile = blockIdx.x, row = 16 * tile + (lane & 15);
     const bool valid = row < a.B;
+    const int hb = FULL ? kRowTiles : v.hb;
     const int o0 = 32 * wave + 4 * (lane >> 4);          // first output of the lane's two blocks: o0, o0 + 16
     // the chain of products: layers 0 .. DEPTH forward, then DEPTH .. 1 back
-    WaveWeights w[2];
+    WaveWeights<> w[2];
     auto fetch = [&](int s) {
         if (s <= DEPTH) {
             load_weights(w[s & 1], v.Wf + frag_off(v, s), wave, lane, s == DEPTH ? v.ot_out : kRowTiles,
@@ -459,7 +473,7 @@ k_rows_train(NetView v, TrainView a) {
         }
         cur ^= 1;
         __syncthreads();
-        store_rows(act[cur], kRowTiles, a.Hf + h_off(v, l + 1, a.max_tiles) + (size_t)tile * kRowTiles * kGradBlock);
+        store_rows(act[cur], hb, a.Hf + h_off(v, l + 1, a.max_tiles) + (size_t)tile * hb * kGradBlock);
     }
     // outputs: deviation from the target and dZ = 2 (z - y) scale
     layer_product<1>(w[DEPTH & 1], act[cur], 0, wave, lane, v.ot_out, kRowPairs, acc);
@@ -502,12 +516,13 @@ k_rows_train(NetView v, TrainView a) {
                 g[j] = valid && o0 + 16 * k + j < v.width ? d : 0.f;
             }
             *act_slot(act[cur ^ 1], 2 * wave + k, lane) = pack_act(g, o0 + 16 * k, v.width);
-            store_operand(a.Dz + d_off(v, l - 1, a.max_tiles) + (size_t)tile * kRowTiles * kGradBlock,
-                          (uint32_t)((2 * wave + k) * kGradBlock + 4 * lane) * 4, g);
+            if (FULL || 2 * wave + k < hb)
+                store_operand(a.Dz + d_off(v, l - 1, a.max_tiles) + (size_t)tile * hb * kGradBlock,
+                              (uint32_t)((2 * wave + k) * kGradBlock + 4 * lane) * 4, g);
         }
         cur ^= 1;
         __syncthreads();
-        store_rows(act[cur], kRowTiles, a.Df + d_off(v, l - 1, a.max_tiles) + (size_t)tile * kRowTiles * kGradBlock);
+        store_rows(act[cur], hb, a.Df + d_off(v, l - 1, a.max_tiles) + (size_t)tile * hb * kGradBlock);
     }
 }
 

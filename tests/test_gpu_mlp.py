@@ -213,3 +213,37 @@ def test_inference_in_place(gl, shape, noalloc):
     assert fn(net._h, ctypes.c_void_p(X.data_ptr()), ctypes.c_void_p(X.data_ptr()), n) == 0
     torch.cuda.synchronize()
     assert torch.equal(X.view(-1)[:n * no], want.view(-1))
+
+
+@pytest.mark.parametrize("shape,groups", [((1, 3, 1, 1), 8), ((5, 8, 4, 2), 8), ((32, 32, 2, 32), 8), ((33, 31, 1, 2), 4),
+                                          ((5, 33, 2, 2), 4), ((64, 64, 3, 64), 4), ((5, 65, 4, 2), 2), ((3, 9, 2, 80), 2),
+                                          ((128, 128, 3, 128), 2), ((2, 129, 2, 1), 1)])
+def test_narrow_networks(gl, shape, groups):
+    """Networks up to 32, 64 and 128 wide (inputs and outputs too) run as 8, 4 and 2
+    groups of rows a workgroup: outputs and gradients within the BF16 bound above, and
+    on either side of each line of the rows' classes the outputs of small calls."""
+    import torch
+    g = np.random.default_rng(sum(shape))
+    n, ni, no = 517, shape[0], shape[3]
+    net = gl.MLP(*shape, max_batch=n, max_samples=8, seed=9)
+    p = net.params()
+    nb = shape[1] * shape[2] + no
+    p[-nb:] = g.uniform(-0.2, 0.2, nb).astype(np.float32)
+    net.params(set_to=p)
+    lo, hi = -np.ones(ni, np.float32), np.full(ni, 2.0, np.float32)
+    net.set_scaling(lo, hi, np.full(no, 0.25), np.full(no, 0.5))
+    X = g.uniform(-1, 2, (n, ni)).astype(np.float32)
+    Y = g.uniform(-1, 1, (n, no)).astype(np.float32)
+    Xs, Ys = M.scale_inputs(X, lo, hi), (Y - 0.25) / 0.5
+    p = p.astype(np.float64)
+    Zs, _ = M.forward(p, Xs, shape, bf16=True)
+    rf = np.abs(net.infer(X).cpu().numpy() - (Zs[-1] * 0.5 + 0.25)) / (M.output_scales(p, Xs, shape, bf16=True) * 0.5 + 1e-30)
+    gr, _ = net.grads(X, Y)
+    _, go = M.loss_and_grads(p, Xs, Ys, shape, bf16=True)
+    rg = np.abs(gr - go) / (M.grad_scales(p, Xs, Ys, shape, bf16=True) + 1e-30)
+    assert rf.max() < 2.0 ** -8 and rg.max() < 2.0 ** -8
+    lines = [groups * r for r in (256 * 16, 512 * 32, 512 * 48)]
+    big = torch.rand(lines[-1] + 1, ni, generator=torch.Generator().manual_seed(5)).cuda()
+    want = torch.cat([net.infer(x.contiguous()) for x in big.split(4096)])
+    for m in [k + d for k in lines for d in (0, 1)]:
+        assert torch.equal(net.infer(big[:m].contiguous()), want[:m])
