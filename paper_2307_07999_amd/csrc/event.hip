@@ -1065,10 +1065,8 @@ static gl_status init_common(gl_event *ev, int n_sheets, double m_ir_GeV, double
 // kernels; partials in the initialisation scratch planes)
 static gl_status dipole_curve(gl_event *ev, int nucleus, int rmax, std::vector<double> &D) {
     const double *V = (const double *)(ev->ws + (nucleus == 0 ? ev->L.VA : ev->L.VB));
-    // a lattice without an MV initialisation has no Wilson lines
-    D.assign(rmax + 1, std::nan(""));
-    if (!valid_N_for_fft(ev->N)) return GL_OK;
-    double *scratch = (double *)(ev->ws + ev->L.planes), *Dd = scratch + dipole_scratch(ev->N);
+    D.assign(rmax + 1, 0.0);
+    double *scratch = (double *)(ev->ws + ev->L.planes), *Dd = scratch + dipole_scratch(ev->N, rmax);
     HIP_TRY(launch_dipole(ev->stream, ev->N, V, rmax, (const double2 *)(ev->ws + ev->L.fft_tab), scratch, Dd));
     HIP_TRY(hipMemcpyAsync(D.data(), Dd, (rmax + 1) * sizeof(double), hipMemcpyDeviceToHost, ev->stream));
     HIP_TRY(hipStreamSynchronize(ev->stream));

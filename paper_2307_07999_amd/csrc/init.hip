@@ -522,7 +522,55 @@ k_wilson_accum(int N, const double2 *__restrict__ planes, int n_sheets, int firs
 // is the autocorrelation of the nine complex entries along the lines of each
 // direction: sum_x z(x) z*(x + r) = 1/N sum_k |Z_k|^2 cos(2 pi k r / N) with Z the
 // transform of the line.  One pass over V per direction instead of one over V
-// and its neighbours per separation (256^2, r <= 128: 206 -> 24 us).
+// and its neighbours per separation (256^2, r <= 128: 206 -> 24 us).  Lattices the
+// line transforms do not take sum the sites of each separation.
+
+// Workgroup (b, r): the sum over its 256 sites of Re Tr V(x) V^dag(x + r e_d),
+// d = x, y; part[r][b]
+__global__ void __launch_bounds__(256)
+k_dipole_sites(int N, const double *__restrict__ V, double *__restrict__ part) {
+    __shared__ double red[256];
+    const size_t n2 = (size_t)N * N;
+    const size_t x = (size_t)blockIdx.x * 256 + threadIdx.x;
+    const int r = blockIdx.y;
+    double v = 0.0;
+    if (x < n2) {
+        const int ix = (int)(x % N), iy = (int)(x / N);
+        const M3<double> a = load_m(V, n2, x);
+        const size_t nb[2] = {(size_t)((ix + r) % N) + (size_t)N * iy, (size_t)ix + (size_t)N * ((iy + r) % N)};
+#pragma unroll
+        for (int d = 0; d < 2; d++) {
+            const M3<double> b = load_m(V, n2, nb[d]);
+#pragma unroll
+            for (int i = 0; i < 3; i++)
+#pragma unroll
+                for (int j = 0; j < 3; j++) v += a.re[i][j] * b.re[i][j] + a.im[i][j] * b.im[i][j];
+        }
+    }
+    red[threadIdx.x] = v;
+    __syncthreads();
+    for (int w = 128; w > 0; w >>= 1) {
+        if (threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) part[(size_t)r * gridDim.x + blockIdx.x] = red[0];
+}
+
+// D[r] = (sum of the nb partials of r in a fixed order) / (6 N^2)
+__global__ void __launch_bounds__(256)
+k_dipole_mean(int N, const double *__restrict__ part, int nb, double *__restrict__ D) {
+    __shared__ double red[256];
+    const int r = blockIdx.x;
+    double v = 0.0;
+    for (int b = threadIdx.x; b < nb; b += 256) v += part[(size_t)r * nb + b];
+    red[threadIdx.x] = v;
+    __syncthreads();
+    for (int w = 128; w > 0; w >>= 1) {
+        if (threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) D[r] = red[0] / (6.0 * (double)N * (double)N);
+}
 
 // Power spectra of C lines of entry blockIdx.y % 9 (rows for blockIdx.y < 9, else
 // columns), summed over the lines: part[y][group][N]
@@ -912,9 +960,14 @@ hipError_t launch_poisson(hipStream_t st, int N, double m2, double uv2, double2 
     return hipGetLastError();
 }
 
-size_t dipole_scratch(int N) {
+bool dipole_by_spectra(int N, int) {
     FftPlan fp;
-    if (!fft_plan(N, fp)) return 0;
+    return N <= kFftMaxN && fft_plan(N, fp);
+}
+
+size_t dipole_scratch(int N, int rmax) {
+    FftPlan fp;
+    if (!dipole_by_spectra(N, rmax) || !fft_plan(N, fp)) return (size_t)(rmax + 1) * blocks_for((size_t)N * N, 256);
     const size_t groups = (N + (1 << fp.log_c) - 1) >> fp.log_c;
     return 18 * groups * N + N;
 }
@@ -922,7 +975,12 @@ size_t dipole_scratch(int N) {
 hipError_t launch_dipole(hipStream_t st, int N, const double *V, int rmax, const double2 *tab, double *scratch,
                          double *D) {
     FftPlan fp;
-    if (N > kFftMaxN || !fft_plan(N, fp)) return hipErrorInvalidValue;
+    if (!dipole_by_spectra(N, rmax) || !fft_plan(N, fp)) {
+        const int nb = (int)blocks_for((size_t)N * N, 256);
+        hipLaunchKernelGGL(k_dipole_sites, dim3(nb, rmax + 1), dim3(256), 0, st, N, V, scratch);
+        hipLaunchKernelGGL(k_dipole_mean, dim3(rmax + 1), dim3(256), 0, st, N, (const double *)scratch, nb, D);
+        return hipGetLastError();
+    }
     const int groups = (N + (1 << fp.log_c) - 1) >> fp.log_c;
     double *S = scratch, *part = scratch + N;
     const size_t lds = ((size_t)(fp.ls << fp.log_c) + fp.n_tw) * sizeof(double2);

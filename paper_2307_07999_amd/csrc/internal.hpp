@@ -253,9 +253,11 @@ hipError_t launch_fft_tables(hipStream_t st, int N, double2 *tab);
 hipError_t launch_poisson(hipStream_t st, int N, double m2, double uv2, double2 *planes, int n_planes,
                           const double2 *tab, const MvDraw *draw = nullptr);
 hipError_t launch_wilson_init(hipStream_t st, int N, double *V);
-// dipole correlator D[0..rmax] of a Wilson line; tab the tables of launch_fft_tables,
-// dipole_scratch(N) doubles of scratch
-size_t dipole_scratch(int N);
+// dipole correlator D[0..rmax] of a Wilson line, from the spectra of its lines
+// (dipole_by_spectra; tab then the tables of launch_fft_tables) or site by site;
+// dipole_scratch doubles of scratch
+bool dipole_by_spectra(int N, int rmax);
+size_t dipole_scratch(int N, int rmax);
 hipError_t launch_dipole(hipStream_t st, int N, const double *V, int rmax, const double2 *tab, double *scratch,
                          double *D);
 hipError_t launch_wilson_accum(hipStream_t st, int N, const double2 *planes /* [n_nuclei][n_sheets][4][n2] */,
