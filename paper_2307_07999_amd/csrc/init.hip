@@ -523,7 +523,8 @@ k_wilson_accum(int N, const double2 *__restrict__ planes, int n_sheets, int firs
 // direction: sum_x z(x) z*(x + r) = 1/N sum_k |Z_k|^2 cos(2 pi k r / N) with Z the
 // transform of the line.  One pass over V per direction instead of one over V
 // and its neighbours per separation (256^2, r <= 128: 206 -> 24 us).  Lattices the
-// line transforms do not take sum the sites of each separation.
+// line transforms do not take and calls for a few separations (dipole_by_spectra) sum
+// the sites of each separation.
 
 // Workgroup (b, r): the sum over its 256 sites of Re Tr V(x) V^dag(x + r e_d),
 // d = x, y; part[r][b]
@@ -960,9 +961,13 @@ hipError_t launch_poisson(hipStream_t st, int N, double m2, double uv2, double2 
     return hipGetLastError();
 }
 
-bool dipole_by_spectra(int N, int) {
+// The spectra cost the same for any rmax, the sums over sites two reads of V a
+// separation, and one launch less: a call for rmax = 1, 2, 4 by sums and by spectra,
+// 256^2 29.6, 32.0, 37 and 37.5 us, 512^2 44, 55, 71 and 75, 1024^2 118, 155, 232 and 291;
+// 64^2 28.8 to 31.5 up to rmax = 32 and 31.6 to 33.5.
+bool dipole_by_spectra(int N, int rmax) {
     FftPlan fp;
-    return N <= kFftMaxN && fft_plan(N, fp);
+    return N > 64 && rmax > 4 && N <= kFftMaxN && fft_plan(N, fp);
 }
 
 size_t dipole_scratch(int N, int rmax) {

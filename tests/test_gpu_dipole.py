@@ -33,3 +33,18 @@ def test_every_lattice(gl, N):
     for rmax in sorted({1, max(1, N // 4), N // 2}):
         assert np.abs(ev.dipole(0, rmax) - 6.0).max() < 1e-12 * 6
     ev.close()
+
+
+@pytest.mark.parametrize("N", [64, 72, 81, 256])
+def test_few_separations_agree_with_the_whole_curve(gl, N):
+    """Sums over sites (rmax <= 4, N <= 64) and spectra of the lines on either side of
+    the line between them, on MV lines.  Both sum entries of magnitude <= 1, the
+    spectra through transforms of some 10 eps a stage."""
+    ev = gl.Event(N, 10.0 * N / 512)
+    ev.init_glasma(2.767, 0.2, 5, 11)
+    for nuc in (0, 1):
+        D = ev.dipole(nuc, N // 2)
+        assert abs(D[0] - 1.0) < 1e-13
+        for rmax in (1, 4, 5, 6):
+            assert np.abs(ev.dipole(nuc, rmax) - D[:rmax + 1]).max() < 1e-13
+    ev.close()
