@@ -163,6 +163,7 @@ struct gl_event {
     int cur = 0;                // current field state (0 or 1), the other holds the one before
     int fmap[3] = {0, 1, 2};    // buffers of states 0 and 1 and the spare one of run_paired
     int fcur = 0;               // current site-field record
+    bool fft_tables = false;    // the line transforms' tables are in the workspace
     int64_t n = 0;
     bool ready = false, push_due = false;
     int64_t rows = 0;           // series rows written
@@ -1024,6 +1025,13 @@ void gl_event_destroy(gl_event *ev) {
     delete ev;
 }
 
+// the tables of the line transforms
+static gl_status fft_tables(gl_event *ev) {
+    HIP_TRY(launch_fft_tables(ev->stream, ev->N, (double2 *)(ev->ws + ev->L.fft_tab)));
+    ev->fft_tables = true;
+    return GL_OK;
+}
+
 // the Wilson lines of both nuclei into VA, VB (steps 1-3 of the MV initialisation)
 static gl_status wilson_lines(gl_event *ev, int n_sheets, double m_ir_GeV, double uv_GeV, const double *rho_dev,
                               double sigma, uint64_t seed) {
@@ -1035,7 +1043,7 @@ static gl_status wilson_lines(gl_event *ev, int n_sheets, double m_ir_GeV, doubl
     double *V[2] = {(double *)(ev->ws + ev->L.VA), (double *)(ev->ws + ev->L.VB)};
     double2 *planes = (double2 *)(ev->ws + ev->L.planes);
     double2 *tab = (double2 *)(ev->ws + ev->L.fft_tab);
-    HIP_TRY(launch_fft_tables(ev->stream, N, tab));
+    if (gl_status s = fft_tables(ev)) return s;
     // both nuclei together where a launch holds the sheets of more than one
     // chunk of the paper's lattice (their chains of products are independent)
     const int chunk = sheet_chunk(ev->n2), nn = chunk >= 2 * kSheetChunkMin ? 2 : 1, per = chunk / nn;
@@ -1066,6 +1074,8 @@ static gl_status init_common(gl_event *ev, int n_sheets, double m_ir_GeV, double
 static gl_status dipole_curve(gl_event *ev, int nucleus, int rmax, std::vector<double> &D) {
     const double *V = (const double *)(ev->ws + (nucleus == 0 ? ev->L.VA : ev->L.VB));
     D.assign(rmax + 1, 0.0);
+    if (dipole_by_spectra(ev->N, rmax) && !ev->fft_tables)
+        if (gl_status s = fft_tables(ev)) return s;
     double *scratch = (double *)(ev->ws + ev->L.planes), *Dd = scratch + dipole_scratch(ev->N, rmax);
     HIP_TRY(launch_dipole(ev->stream, ev->N, V, rmax, (const double2 *)(ev->ws + ev->L.fft_tab), scratch, Dd));
     HIP_TRY(hipMemcpyAsync(D.data(), Dd, (rmax + 1) * sizeof(double), hipMemcpyDeviceToHost, ev->stream));

@@ -26,9 +26,10 @@ def _event_of_ones(gl, N):
     return ev
 
 
-@pytest.mark.parametrize("N", [5, 10, 50, 130, 250])
+@pytest.mark.parametrize("N", [5, 10, 50, 130, 250, 8, 64, 96, 243])
 def test_every_lattice(gl, N):
-    """Lattices that are not 2^a 3^b (no MV initialisation) included."""
+    """Lattices that are not 2^a 3^b (no MV initialisation) included, and lattices
+    whose line transforms nothing has prepared."""
     ev = _event_of_ones(gl, N)
     for rmax in sorted({1, max(1, N // 4), N // 2}):
         assert np.abs(ev.dipole(0, rmax) - 6.0).max() < 1e-12 * 6
