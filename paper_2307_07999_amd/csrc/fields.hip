@@ -352,6 +352,27 @@ hipError_t launch_correlators(hipStream_t st, int N, const T *F, const T *U, con
     return hipGetLastError();
 }
 
+// chunk c of site x of the records, and of the chunk planes [chunk][n2]
+template <typename T>
+__global__ void __launch_bounds__(256)
+k_site_planes(size_t n2, uint4 *__restrict__ records, uint4 *__restrict__ planes, int to_planes) {
+    constexpr size_t chunks = kSiteRec * sizeof(T) / 16;
+    const size_t at = (size_t)blockIdx.x * 256 + threadIdx.x;
+    if (at >= chunks * n2) return;
+    const size_t c = at / n2, x = at - c * n2;
+    uint4 &r = records[(x / kSiteGroup * chunks + c) * kSiteGroup + x % kSiteGroup];
+    if (to_planes) planes[at] = r;
+    else r = planes[at];
+}
+
+template <typename T>
+hipError_t launch_site_planes(hipStream_t st, size_t n2, T *records, void *planes, bool to_planes) {
+    constexpr size_t chunks = kSiteRec * sizeof(T) / 16;
+    hipLaunchKernelGGL(k_site_planes<T>, dim3((unsigned)((chunks * n2 + 255) / 256)), dim3(256), 0, st, n2,
+                       (uint4 *)records, (uint4 *)planes, to_planes ? 1 : 0);
+    return hipGetLastError();
+}
+
 template <typename T>
 hipError_t launch_diag(hipStream_t st, int N, FieldPtrs<T> f, double tau, double *partials,
                        int *n_blocks_out) {
@@ -365,6 +386,7 @@ hipError_t launch_diag(hipStream_t st, int N, FieldPtrs<T> f, double tau, double
     template hipError_t launch_field_step<T>(hipStream_t, int, FieldPtrs<T>, FieldPtrs<T>, T *,    \
                                              double, double, int, const KernelTimer &);      \
     template hipError_t launch_diag<T>(hipStream_t, int, FieldPtrs<T>, double, double *, int *);     \
+    template hipError_t launch_site_planes<T>(hipStream_t, size_t, T *, void *, bool);                 \
     template hipError_t launch_check_finite<T>(hipStream_t, const T *, int64_t, int64_t, int, int *);   \
     template hipError_t launch_correlators<T>(hipStream_t, int, const T *, const T *, const CorrCall &, double, bool);
 // the FP64 instantiations come from fields_f64.hip, which includes this file

@@ -214,6 +214,10 @@ inline int corr_blocks(size_t n2) { return (int)((n2 + 255) / 256); }
 template <typename T>
 hipError_t launch_correlators(hipStream_t st, int N, const T *F, const T *U, const CorrCall &c, double dtau,
                               bool streamed);
+// the site-field records of n2 sites to chunk planes (chunk c of site x at
+// c n2 + x), as the host and the checkpoints have them, or back
+template <typename T>
+hipError_t launch_site_planes(hipStream_t st, size_t n2, T *records, void *planes, bool to_planes);
 template <typename T>
 hipError_t launch_diag(hipStream_t st, int N, FieldPtrs<T> f, double tau, double *partials,
                        int *n_blocks_out);
