@@ -632,6 +632,9 @@ gl_status graph_block(gl_event *ev, int32_t count, bool has_particles) {
     HIP_TRY(hipStreamBeginCapture(ev->stream, hipStreamCaptureModeRelaxed));
     gl_status s = GL_OK;
     for (int32_t k = 0; k < count && !s; k++) s = one_step(ev, has_particles);
+    // the correlators' reductions end with the block, so that blocks of fields and
+    // correlators alone are alike whatever their length
+    if (!s) s = flush_correlators(ev);
     hipGraph_t g = nullptr;
     const hipError_t e = hipStreamEndCapture(ev->stream, &g);
     if (s || e != hipSuccess) {

@@ -105,3 +105,32 @@ def test_graph_replay_is_off_while_checking_and_needs_a_stream(gl):
             ev.set_graph_steps(8)
         assert e.value.status == gl.GL_EINVAL
         ev.close()
+
+
+@pytest.mark.parametrize("G", [3, 10, 16, 20])
+def test_blocks_of_fields_and_correlators_are_alike(gl, G):
+    """Without particles nothing in a block depends on where it falls: after the
+    two executable graphs exist every block updates one in place, and the results
+    are those of direct steps."""
+    import torch
+    evs = []
+    for steps in (0, G):
+        ev = gl.Event(32, 4.0, 0.125, precision=64, max_steps=300, stream=torch.cuda.Stream(),
+                      static_correlator=True, lightlike_correlator=True)
+        ev.init_glasma(1.0, 0.2, 2, 91)
+        ev.static_start(0.02)
+        ev.lightlike_start(0.02)
+        ev.run(5)                        # past the correlators' start
+        ev.set_graph_steps(steps)
+        for n in (8 * G, 4 * G + 1):
+            ev.run(n)
+        evs.append(ev)
+    torch.cuda.synchronize()
+    for x, y in zip(*[ev.get_state() for ev in evs]):
+        assert np.array_equal(x, y)
+    for name in ("static_broadening", "lightlike_broadening"):
+        assert np.array_equal(*[getattr(ev, name)() for ev in evs])
+    launches, inst = evs[1].graph_stats()
+    assert launches == 12 and inst == 2
+    for ev in evs:
+        ev.close()
