@@ -234,7 +234,13 @@ k_batch_reduce(const BatchEv<T> *__restrict__ evs, int off, const BatchCtl *__re
 }
 
 // the batch's finite-value check: entry (event, chunk) tests values
-// [chunk * kCheckChunk, ...) of the event's whole field state at parity fpar
+// [chunk * kCheckChunk, ...) of the event's whole field state at parity fpar.
+//
+// Bound: by latency on small lattices, whose states are a chunk or two: the field
+// step writes through L2, so every load comes from beyond it.  Hence 16 bytes a
+// lane and kCheckAhead loads in flight (a value a lane and one load in flight took
+// 77 us for eight events of 32^2, and 28 with their states in L2; now 8.6).
+constexpr int kCheckAhead = 8;
 template <typename T>
 __global__ void __launch_bounds__(256)
 k_batch_check(const BatchEv<T> *__restrict__ evs, const int2 *__restrict__ entries, int fpar,
@@ -244,8 +250,21 @@ k_batch_check(const BatchEv<T> *__restrict__ evs, const int2 *__restrict__ entri
     const int64_t nvals = (int64_t)kStateVals * e.N * e.N;
     const int64_t lo = (int64_t)w.y * kCheckChunk, hi = lo + kCheckChunk < nvals ? lo + kCheckChunk : nvals;
     const T *a = e.f[fpar].U;   // the state's arrays lie contiguous from U on
+    struct __align__(16) V { T v[16 / sizeof(T)]; };
+    constexpr int NV = 16 / (int)sizeof(T);
+    static_assert(kStateVals % NV == 0 && kCheckChunk % NV == 0, "whole vectors");
+    const V *p = reinterpret_cast<const V *>(a + lo);
+    const int64_t nv = (hi - lo) / NV;
     bool bad = false;
-    for (int64_t i = lo + threadIdx.x; i < hi; i += 256) bad |= !isfinite(a[i]);
+    for (int64_t i0 = threadIdx.x; i0 < nv; i0 += 256 * kCheckAhead) {
+        V x[kCheckAhead];
+#pragma unroll
+        for (int u = 0; u < kCheckAhead; u++) x[u] = p[i0 + 256 * u < nv ? i0 + 256 * u : nv - 1];
+#pragma unroll
+        for (int u = 0; u < kCheckAhead; u++)
+#pragma unroll
+            for (int k = 0; k < NV; k++) bad |= !isfinite(x[u].v[k]);
+    }
     if (bad) atomicMin(e.fail, (int32_t)(ctl->n < kNotFailed ? ctl->n : kNotFailed - 1));
 }
 

@@ -258,3 +258,36 @@ def test_batch_equals_single_events_at_batched_workload_sizes(gl):
         for k in ("cell", "p", "Q"):
             assert np.array_equal(ps[k], pb[k])
     b.close()
+
+
+@pytest.mark.parametrize("prec", [64, 32])
+@pytest.mark.parametrize("N", [2, 5, 32, 38])
+def test_the_check_sees_every_end_of_a_state(gl, N, prec):
+    """One NaN or Inf in the first or last values of each array of a state (48 N^2
+    values in chunks of 65536, read as 16-byte vectors several at a time), in one
+    event of two."""
+    n2 = N * N
+    evs = [gl.Event(N, N * 0.125, 0.125, precision=prec, max_steps=1) for _ in range(2)]
+    for ev in evs:
+        ev.init_glasma(1.0, 0.2, 1, 5) if N in (2, 32) else ev.set_state(
+            np.tile(np.eye(3).reshape(9, 1, 1) * [[1.0], [0.0]], (2, 1, 1, 1)).reshape(2, 18, 1) * np.ones(n2),
+            np.zeros((2, 8, n2)), np.zeros((8, n2)), np.zeros((8, n2)), 1)
+    good = evs[1].get_state()
+    spots = [(a, i) for a, rows in ((1, 16), (2, 8), (3, 8)) for i in (0, n2 - 1, rows * n2 - n2, rows * n2 - 1)]
+    spots += [(0, 0), (0, n2 - 1), (0, 18 * n2), (0, 29 * n2 + n2 - 1)]     # rows 0 and 1 of both links
+    for a, i in spots:
+        for bad in (np.nan, -np.inf):
+            s = [x.copy() for x in good[:4]]
+            s[a].reshape(-1)[i] = bad
+            evs[1].set_state(*s, 1)
+            b = gl.Batch(evs)
+            with pytest.raises(gl.GlasmaError) as e:
+                b.run(0)
+            assert e.value.status == gl.GL_ENUMERIC and list(b.status()) == [-1, 1]
+            b.close()
+    evs[1].set_state(*good[:4], 1)
+    b = gl.Batch(evs)
+    b.run(0)
+    b.close()
+    for ev in evs:
+        ev.close()
