@@ -37,7 +37,7 @@ constexpr int SX = 32, SY = 4;     // site tiles of the step: 2 lanes per site
 
 // FP64: two waves per SIMD at the cost of a few spilled registers is faster
 // than one wave with everything in registers.
-template <typename T>
+template <typename T, bool WT>
 __global__ void __launch_bounds__(2 * SX * SY) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 ? 2 : 4, 8)))
 k_field_step(int N, FieldPtrs<T> in, FieldPtrs<T> out, T *__restrict__ F, T tau, T dtau, T tau_h, int reunit) {
     __shared__ LinkTile<T, SX, SY> tile;
@@ -51,7 +51,8 @@ k_field_step(int N, FieldPtrs<T> in, FieldPtrs<T> out, T *__restrict__ F, T tau,
     // every thread takes part (the step synchronises the workgroup); both
     // lanes of a pair are on or off the lattice together
     const bool active = x0 + lx < N && y0 + ly < N;
-    field_step_link(tile, N, in, out, F, x0, y0, lx, ly, threadIdx.x & 1, tid, active, tau, dtau, tau_h, reunit);
+    field_step_link<T, SX, SY, kStreamed<T>, WT>(tile, N, in, out, F, x0, y0, lx, ly, threadIdx.x & 1, tid, active, tau,
+                                                 dtau, tau_h, reunit);
 }
 
 // The two field correlators at tau_n, FP64, from one read of the site fields
@@ -322,12 +323,23 @@ hipError_t launch_check_finite(hipStream_t st, const T *a, int64_t n, int64_t va
     return hipGetLastError();
 }
 
+// Whether a field step alone writes its state through the L2 caches.  Small FP32
+// states are better left there for the next step (64 steps of fields, left and
+// written through: 32^2 436 and 458 us, 64^2 429 and 454, 128^2 455 and 462, 144^2 470 and
+// 477, but 162^2 497 and 487, 256^2 640 and 630, 324^2 973 and 891).  In FP64, rows of sites
+// that do not fill 64-byte sectors are shared by two tiles and better joined in L2
+// (162^2 584 and 625 us, 243^2 935 and 1005, 486^2 3066 and 3233); whole ones are written
+// through (128^2 546 and 526, 256^2 980 and 953, 324^2 1665 and 1588).
+template <typename T>
+bool written_through(int N) { return sizeof(T) == 8 ? N % 4 == 0 : N > 144; }
+
 template <typename T>
 hipError_t launch_field_step(hipStream_t st, int N, FieldPtrs<T> in, FieldPtrs<T> out, T *F, double tau,
                              double dtau, int reunit, const KernelTimer &kt) {
-    dim3 grid(field_tiles(N)), block(2 * SX, SY);
-    GL_LAUNCH_TIMED(kt, k_field_step<T>, grid, block, 0, st, N, in, out, F, (T)tau, (T)dtau, (T)(tau + 0.5 * dtau),
-                    reunit);
+    const dim3 grid(field_tiles(N)), block(2 * SX, SY);
+    const T th = (T)(tau + 0.5 * dtau);
+    if (written_through<T>(N)) GL_LAUNCH_TIMED(kt, (k_field_step<T, true>), grid, block, 0, st, N, in, out, F, (T)tau, (T)dtau, th, reunit);
+    else GL_LAUNCH_TIMED(kt, (k_field_step<T, false>), grid, block, 0, st, N, in, out, F, (T)tau, (T)dtau, th, reunit);
     return hipGetLastError();
 }
 

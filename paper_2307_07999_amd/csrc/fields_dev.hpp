@@ -27,10 +27,10 @@ constexpr bool kEarlyEP = sizeof(T) == 8;
 // (ST) the lanes trade chunks so that whole cache lines are written (24 events
 // of 256^2: field step 226 -> 222 us, FP64 512^2 69.2 -> 68.2); a cached FP32
 // event, bound by its arithmetic, stores its own (+ 0.3 us with the trade).
-template <bool ST, typename T>
+template <bool ST, bool WT, typename T>
 __device__ __forceinline__ void store_recs(T *__restrict__ F, size_t x, int k0, int k1, const T *v, int d) {
-    if constexpr (ST) site_store_pair<8>(F, x, k0, k1, v, d);
-    else site_store<8>(F, x, d ? k1 : k0, v);
+    if constexpr (ST) site_store_pair<8, store_policy(false, WT)>(F, x, k0, k1, v, d);
+    else site_store<8, store_policy(false, WT)>(F, x, d ? k1 : k0, v);
 }
 
 struct Nbr {
@@ -79,20 +79,20 @@ __device__ __forceinline__ M3<T> pair_swap(const M3<T> &m) {
 
 // Four values of each lane of a site's pair into a record slot, lane h's at 4h
 // (one chunk a lane in FP32, so that the pair already writes neighbours).
-template <bool ST, typename T>
+template <bool ST, bool WT, typename T>
 __device__ __forceinline__ void store_halves(T *__restrict__ F, size_t x, int slot, const T *w, int h) {
-    if constexpr (sizeof(T) == 4 || !ST) site_store<4>(F, x, slot + 4 * h, w);
-    else site_store_pair<4>(F, x, slot, slot + 4, w, h);
+    if constexpr (sizeof(T) == 4 || !ST) site_store<4, store_policy(false, WT)>(F, x, slot + 4 * h, w);
+    else site_store_pair<4, store_policy(false, WT)>(F, x, slot, slot + 4, w, h);
 }
 
 // Components 4h..4h+3 of an algebra vector v into a record slot (the two
 // lanes of a site store one half each).
-template <bool ST, typename T>
+template <bool ST, bool WT, typename T>
 __device__ __forceinline__ void store_half(T *__restrict__ F, size_t x, int slot, const T *v, int h) {
     T w[4];
 #pragma unroll
     for (int k = 0; k < 4; k++) w[k] = h ? v[4 + k] : v[k];
-    store_halves<ST>(F, x, slot, w, h);
+    store_halves<ST, WT>(F, x, slot, w, h);
 }
 
 // Links of a block of SX x SY sites and a one-site halo, staged in LDS;
@@ -214,7 +214,7 @@ __device__ __forceinline__ void stage_tile(LinkTile<T, SX, SY> &t, int N, const 
 // force fe and U_i(x) = u; with F, also this site's half of the electric
 // site field (eb) and the half transported to x+i (t), which the caller
 // stores or exchanges
-template <typename T, bool ST>
+template <typename T, bool ST, bool WT>
 __device__ __forceinline__ void update_link(const T *ein, T *__restrict__ Eout, const M3<T> &u,
                                             T *__restrict__ Uout, size_t n2, size_t x, int d, const T *fe, T dtau,
                                             T s, int reunit, bool site_fields, T inv_tau, T *eb, T *t) {
@@ -225,7 +225,7 @@ __device__ __forceinline__ void update_link(const T *ein, T *__restrict__ Eout, 
         eb[a] = e[a];
         e[a] += dtau * fe[a];
     }
-    chunk_store_n_l<8, stream_policy(ST)>(Eout, n2, x, 8 * d, e);   // the new state is streamed (ST)
+    chunk_store_n_l<8, store_policy(ST, WT)>(Eout, n2, x, 8 * d, e);   // the new state is streamed (ST)
     M3<T> un = mul(expi_alg(e, s), u);
     if (reunit) un = reunitarize(un);
     T uv[18];
@@ -238,7 +238,7 @@ __device__ __forceinline__ void update_link(const T *ein, T *__restrict__ Eout, 
         }
     // the new links stay cached: the next step stages them, halo included,
     // into its tiles (streaming them cost the FP64 step 4.5 us)
-    chunk_store_link_l(Uout, n2, x, d, uv);
+    chunk_store_link_l<store_policy(false, WT)>(Uout, n2, x, d, uv);
     if (site_fields) {
 #pragma unroll
         for (int a = 0; a < 8; a++) eb[a] = T(0.25) * inv_tau * (eb[a] + e[a]);   // Ebar / (2 tau)
@@ -274,8 +274,9 @@ __device__ __forceinline__ void update_link(const T *ein, T *__restrict__ Eout, 
 // The second half of E_i at x+i needs U_i(x) and Ebar_i(x), which lane d
 // owns: it hands that half to the lane of x+i through LDS, which adds it to
 // its own, or, at the sites of half_stored, stores it in x+i's slots 48..63
-// for the readers to add.
-template <typename T, int SX, int SY, bool ST = kStreamed<T>>
+// for the readers to add.  ST: the state is streamed past the caches; WT: state and
+// site fields are written through them.
+template <typename T, int SX, int SY, bool ST = kStreamed<T>, bool WT = true>
 __device__ __forceinline__ void field_step_link(LinkTile<T, SX, SY> &tl, int N, const FieldPtrs<T> &in,
                                                 const FieldPtrs<T> &out, T *__restrict__ F, int x0, int y0, int lx,
                                                 int ly, int d, int tid, bool active, T tau, T dtau, T tau_h,
@@ -356,7 +357,7 @@ __device__ __forceinline__ void field_step_link(LinkTile<T, SX, SY> &tl, int N, 
             transport_dn<kHermPlaq>(mul(tl.m(0, rz), tl.m(1, rz + 1)), pa, t);
 #pragma unroll
             for (int a = 0; a < 8; a++) t[a] = T(-0.25) * (cl[a] + t[a]);
-            store_half<ST>(F, x, 40, t, d);   // B_z
+            store_half<ST, WT>(F, x, 40, t, d);   // B_z
         }
         // E_i(x) and this lane's half of pi, read once per step (streamed)
         T ein[8], pv[4];
@@ -379,10 +380,10 @@ __device__ __forceinline__ void field_step_link(LinkTile<T, SX, SY> &tl, int N, 
                 pf[a] = T(0.5) * sgn * inv_tau * (pf[a] - pb[a]);
             }
             // B_y = D_1 phi / tau (lane 0, slot 32), B_x = -D_2 phi / tau (lane 1, slot 24)
-            if (F) store_recs<ST>(F, x, 32, 24, pf, d);
+            if (F) store_recs<ST, WT>(F, x, 32, 24, pf, d);
         }
         if constexpr (!kEarlyEP<T>) chunk_load_n_l<8, stream_policy(ST)>(in.E, n2, x, 8 * d, ein);
-        update_link<T, ST>(ein, out.E, ui, out.U, n2, x, d, fe, dtau, dtau / tau_h, reunit, F != nullptr, inv_tau, eb,
+        update_link<T, ST, WT>(ein, out.E, ui, out.U, n2, x, d, fe, dtau, dtau / tau_h, reunit, F != nullptr, inv_tau, eb,
                            tr);
         // pi, phi and E_z: lane d takes colour components 4d..4d+3
         T pn[4], phn[4], ez[4];
@@ -393,9 +394,9 @@ __device__ __forceinline__ void field_step_link(LinkTile<T, SX, SY> &tl, int N, 
             phn[k] = (d0 ? ph[k] : ph[4 + k]) + dtau * tau_h * pn[k];
             ez[k] = T(0.5) * (pv[k] + pn[k]);
         }
-        chunk_store_n_l<4, stream_policy(ST)>(out.pi, n2, x, 4 * d, pn);
-        chunk_store_n_l<4, stream_policy(ST)>(out.phi, n2, x, 4 * d, phn);
-        if (F) store_halves<ST>(F, x, 16, ez, d);
+        chunk_store_n_l<4, store_policy(ST, WT)>(out.pi, n2, x, 4 * d, pn);
+        chunk_store_n_l<4, store_policy(ST, WT)>(out.phi, n2, x, 4 * d, phn);
+        if (F) store_halves<ST, WT>(F, x, 16, ez, d);
     }
     if (F) {
         // E_i site fields: the half transported from x - i is added here when
@@ -409,7 +410,7 @@ __device__ __forceinline__ void field_step_link(LinkTile<T, SX, SY> &tl, int N, 
         if (active) {
             const int ixt = d0 ? ixp : ix, iyt = d0 ? iy : iyp;
             if (half_stored(d, ixt, iyt)) {
-                site_store<8>(F, xpi, 48 + 8 * d, tr);
+                site_store<8, store_policy(false, WT)>(F, xpi, 48 + 8 * d, tr);
             } else {   // x+i lies in this tile (the rule keeps x+i off tile edges)
                 const int st = (lx + (d0 ? 1 : 0)) + SX * (ly + (d0 ? 0 : 1));
 #pragma unroll
@@ -423,7 +424,7 @@ __device__ __forceinline__ void field_step_link(LinkTile<T, SX, SY> &tl, int N, 
 #pragma unroll
                 for (int a = 0; a < 8; a++) eb[a] = eb[a] + ex[(d * 8 + a) * S + so];
             }
-            store_recs<ST>(F, x, 0, 8, eb, d);
+            store_recs<ST, WT>(F, x, 0, 8, eb, d);
         }
     }
 }

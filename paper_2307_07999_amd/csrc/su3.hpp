@@ -566,12 +566,15 @@ constexpr int kLinkVals = 12;            // stored values of a link (its first t
 // 969 ms).  kStreamed<T> is the single-event choice.
 constexpr int kNonTemporal = 2;
 constexpr int stream_policy(bool streamed) { return streamed ? kNonTemporal : 0; }
-// Every 16-byte store is written through the L2 caches (sc1): what a kernel
-// leaves dirty there (up to 4 MB an XCD) is written back when it ends, behind its
-// work instead of beside it.  512^2: FP32 field step 35.9 -> 33.8 us and push 36.9 ->
+// 16-byte stores are written through the L2 caches (sc1) unless their caller says
+// otherwise: what a kernel leaves dirty there (up to 4 MB an XCD) is written back
+// when it ends, behind its work instead of beside it.  512^2: FP32 field step 35.9 -> 33.8 us and push 36.9 ->
 // 35.8, FP64 field step 68.6 -> 67.4; paired FP64 step at 243^2 34.0 -> 32.9; 24 FP32
 // events of 256^2 in a batch 229 -> 227.
 constexpr int kWriteThrough = 16;
+constexpr int store_policy(bool streamed, bool through = true) {
+    return stream_policy(streamed) | (through ? kWriteThrough : 0);
+}
 template <typename T>
 constexpr bool kStreamed = sizeof(T) == 8;
 
@@ -665,7 +668,7 @@ __device__ __forceinline__ void chunk_ld16(const T *p, size_t n2, size_t x, int 
 // hazard is also there with one: the data of a 16-byte store was overwritten
 // by the next instruction in a few lanes.  Every 16-byte store therefore puts
 // its whole offset in the vector offset and passes a constant zero soffset.
-template <int CP = 0, typename T>
+template <int CP = kWriteThrough, typename T>
 __device__ __forceinline__ void chunk_st16(T *p, size_t n2, size_t x, int k, const T *in) {
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
     struct V { T v[16 / sizeof(T)]; };
@@ -674,7 +677,7 @@ __device__ __forceinline__ void chunk_st16(T *p, size_t n2, size_t x, int k, con
 #pragma unroll
     for (int i = 0; i < NV; i++) r.v[i] = in[i];
     __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, r), buf(p),
-                                           (uint32_t)((x + (size_t)(k / NV) * n2) * 16), 0u, CP | kWriteThrough);
+                                           (uint32_t)((x + (size_t)(k / NV) * n2) * 16), 0u, CP);
 }
 
 
@@ -701,14 +704,14 @@ __device__ __forceinline__ void chunk_ld16_l(const T *p, size_t n2, size_t x, in
 #pragma unroll
     for (int i = 0; i < (int)(16 / sizeof(T)); i++) out[i] = r.v[i];
 }
-template <int CP = 0, typename T>
+template <int CP = kWriteThrough, typename T>
 __device__ __forceinline__ void chunk_st16_l(T *p, size_t n2, size_t x, int k, const T *in) {
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
     struct V { T v[16 / sizeof(T)]; };
     V r;
 #pragma unroll
     for (int i = 0; i < (int)(16 / sizeof(T)); i++) r.v[i] = in[i];
-    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, r), buf(p), chunk_off<T>(n2, x, k), 0u, CP | kWriteThrough);
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, r), buf(p), chunk_off<T>(n2, x, k), 0u, CP);
 }
 // n values k0.. (k0 and n multiples of 16 / sizeof(T)), lane-dependent k0
 template <int n, int CP = 0, typename T>
@@ -716,14 +719,14 @@ __device__ __forceinline__ void chunk_load_n_l(const T *p, size_t n2, size_t x, 
 #pragma unroll
     for (int k = 0; k < n; k += 16 / (int)sizeof(T)) chunk_ld16_l<CP>(p, n2, x, k0 + k, v + k);
 }
-template <int n, int CP = 0, typename T>
+template <int n, int CP = kWriteThrough, typename T>
 __device__ __forceinline__ void chunk_store_n_l(T *p, size_t n2, size_t x, int k0, const T *v) {
 #pragma unroll
     for (int k = 0; k < n; k += 16 / (int)sizeof(T)) chunk_st16_l<CP>(p, n2, x, k0 + k, v + k);
 }
 // the stored rows of link d + 1 of site x (values 12d .. 12d + 11) from the
 // first 12 of the link's 18 values v, d lane-dependent
-template <int CP = 0, typename T>
+template <int CP = kWriteThrough, typename T>
 __device__ __forceinline__ void chunk_store_link_l(T *p, size_t n2, size_t x, int d, const T *v) {
     chunk_store_n_l<kLinkVals, CP>(p, n2, x, kLinkVals * d, v);
 }
@@ -747,7 +750,7 @@ __device__ __forceinline__ void site_load(const T *p, size_t x, int k0, T *v) {
 // n values of each lane of a pair (d = 0, 1), lane 0's to k0 .. and lane 1's to
 // k1 .. of site x's record: the lanes trade chunks so that each store writes two
 // neighbouring chunks of the site, and with kSiteGroup = 4 whole cache lines.
-template <int n, typename T>
+template <int n, int CP, typename T>
 __device__ __forceinline__ void site_store_pair(T *p, size_t x, int k0, int k1, const T *v, int d) {
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
     struct V { T v[16 / sizeof(T)]; };
@@ -764,11 +767,11 @@ __device__ __forceinline__ void site_store_pair(T *p, size_t x, int k0, int k1, 
             b.v[i] = d ? v[k + NV + i] : even;
         }
         const uint32_t step = (uint32_t)(k / NV * kSiteGroup * 16);
-        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, a), buf(p), at0 + step, 0u, kWriteThrough);
-        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, b), buf(p), at1 + step, 0u, kWriteThrough);
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, a), buf(p), at0 + step, 0u, CP);
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, b), buf(p), at1 + step, 0u, CP);
     }
 }
-template <int n, typename T>
+template <int n, int CP, typename T>
 __device__ __forceinline__ void site_store(T *p, size_t x, int k0, const T *v) {
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
     struct V { T v[16 / sizeof(T)]; };
@@ -780,7 +783,7 @@ __device__ __forceinline__ void site_store(T *p, size_t x, int k0, const T *v) {
 #pragma unroll
         for (int i = 0; i < NV; i++) r.v[i] = v[k + i];
         __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, r), buf(p),
-                                               at + (uint32_t)(k / NV * kSiteGroup * 16), 0u, kWriteThrough);
+                                               at + (uint32_t)(k / NV * kSiteGroup * 16), 0u, CP);
     }
 }
 

@@ -133,3 +133,24 @@ def test_paired_batch_equals_its_phases_apart(gl, prec, shape):
     assert np.array_equal(ea[1].series(), eb[1].series(), equal_nan=True)
     a.close()
     b.close()
+
+
+@pytest.mark.parametrize("prec,N,copies", [(64, 54, 2), (64, 27, 4), (32, 48, 4), (32, 144, 2)])
+def test_fields_of_a_tiled_lattice(gl, prec, N, copies):
+    """A periodic lattice tiled from a smaller one evolves as that one does, bit for
+    bit: on one side of the line the field step's stores stay in the L2 caches, on
+    the other they are written through them."""
+    ev = gl.Event(N, 0.02 * N, precision=prec, max_steps=8)
+    M = N * copies
+    big = gl.Event(M, 0.02 * M, precision=prec, max_steps=8)
+    ev.init_glasma(2.0, 0.2, 1, 5)
+    tile = lambda a: np.tile(a.reshape(a.shape[:-1] + (N, N)), (1,) * (a.ndim - 1) + (copies, copies)).reshape(
+        a.shape[:-1] + (M * M,))
+    s = ev.get_state()
+    big.set_state(*[tile(a) for a in s[:4]], s[4])
+    for e in (ev, big):
+        e.evolve_fields(5)
+    for a, b in zip(ev.get_state()[:4], big.get_state()[:4]):
+        assert np.array_equal(tile(a), b)
+    ev.close()
+    big.close()
