@@ -65,7 +65,7 @@ __device__ __forceinline__ void permute_one(const PartPtrs<T> &src, const PartPt
 
 template <typename T>
 hipError_t launch_batch_fields(hipStream_t st, int shape, const BatchEv<T> *evs, const int2 *tiles, int64_t total,
-                               const BatchAt &at, const BatchCtl *ctl, double dtau, int grid);
+                               const BatchAt &at, const BatchCtl *ctl, double dtau, int grid, bool whole_rows);
 // the particle sort of every event, one launch per phase; pblocks (event,
 // particle block) and stiles (event, sort tile) cover each event's used
 // slots.  The sorted order of buffer parity ppar goes to each event's sort

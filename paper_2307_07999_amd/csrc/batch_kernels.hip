@@ -29,7 +29,7 @@ __device__ __forceinline__ int64_t xcd_first(int64_t total, int64_t &stride, int
 }
 
 // one tile of an event: stage its links and phi, then the step of its sites
-template <typename T, int TX, int TY>
+template <typename T, int TX, int TY, bool WT = true>
 __device__ __forceinline__ void batch_field_tile(LinkTile<T, TX, TY> &tile, const BatchEv<T> &e, int2 w,
                                                  const BatchAt &at, int tid, int64_t n, T tau, T dtau, T tau_h) {
     const int lx = (tid % (2 * TX)) >> 1, ly = tid / (2 * TX);
@@ -42,11 +42,11 @@ __device__ __forceinline__ void batch_field_tile(LinkTile<T, TX, TY> &tile, cons
     const int reunit = e.reunit_every > 0 && (n % e.reunit_every) == e.reunit_every - 1;
     // a batch's working set overflows the last-level cache in either
     // precision: its streamed arrays take the non-temporal hint
-    field_step_link<T, TX, TY, true>(tile, e.N, e.f[at.in], e.f[at.out], e.n_species > 0 ? e.F[at.F] : nullptr, x0,
-                                     y0, lx, ly, tid & 1, tid, active, tau, dtau, tau_h, reunit);
+    field_step_link<T, TX, TY, true, WT>(tile, e.N, e.f[at.in], e.f[at.out], e.n_species > 0 ? e.F[at.F] : nullptr, x0,
+                                         y0, lx, ly, tid & 1, tid, active, tau, dtau, tau_h, reunit);
 }
 
-template <typename T, int TX, int TY>
+template <typename T, int TX, int TY, bool WT>
 __global__ void __launch_bounds__(2 * TX *TY)
 k_batch_field(const BatchEv<T> *__restrict__ evs, const int2 *__restrict__ tiles, int64_t total, BatchAt at,
               const BatchCtl *__restrict__ ctl, T dtau) {
@@ -59,14 +59,14 @@ k_batch_field(const BatchEv<T> *__restrict__ evs, const int2 *__restrict__ tiles
         const int2 w = tiles[t];
         if (*evs[w.x].fail != kNotFailed) continue;   // a failed event is masked (uniform per workgroup)
         __syncthreads();   // the previous tile's reads are done
-        batch_field_tile(tile, evs[w.x], w, at, tid, n, tau, dtau, tau_h);
+        batch_field_tile<T, TX, TY, WT>(tile, evs[w.x], w, at, tid, n, tau, dtau, tau_h);
     }
 }
 
 // One workgroup per table entry (grid = entries), numbered so that each XCD
 // takes one contiguous run of the table: the walk of the persistent kernel
 // without its loop, which holds registers the step can use.
-template <typename T, int TX, int TY>
+template <typename T, int TX, int TY, bool WT>
 __global__ void __launch_bounds__(2 * TX *TY) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 ? 2 : 4, 8)))
 k_batch_field_flat(const BatchEv<T> *__restrict__ evs, const int2 *__restrict__ tiles, int64_t total, BatchAt at,
                    const BatchCtl *__restrict__ ctl, T dtau) {
@@ -76,7 +76,7 @@ k_batch_field_flat(const BatchEv<T> *__restrict__ evs, const int2 *__restrict__ 
     const T tau = dtau * (T)n, tau_h = dtau * ((T)n + T(0.5));
     const int2 w = tiles[xcd_remap(blockIdx.x, gridDim.x)];
     if (*evs[w.x].fail != kNotFailed) return;   // a failed event is masked (uniform per workgroup)
-    batch_field_tile(tile, evs[w.x], w, at, tid, n, tau, dtau, tau_h);
+    batch_field_tile<T, TX, TY, WT>(tile, evs[w.x], w, at, tid, n, tau, dtau, tau_h);
 }
 
 // one block of an event's particles; with PERM, position i takes the particle
@@ -274,17 +274,28 @@ __global__ void k_batch_advance(BatchCtl *ctl, int steps) {
 
 template <typename T>
 hipError_t launch_batch_fields(hipStream_t st, int shape, const BatchEv<T> *evs, const int2 *tiles, int64_t total,
-                               const BatchAt &at, const BatchCtl *ctl, double dtau, int grid) {
+                               const BatchAt &at, const BatchCtl *ctl, double dtau, int grid, bool whole_rows) {
     if (total <= 0) return hipSuccess;
     unsigned g = (unsigned)(grid > 0 && grid < total ? grid : total);
+    // Written through the L2 caches where every lattice's rows fill whole 64-byte
+    // sectors (whole_rows: N a multiple of four), else left there for the tiles that
+    // share a sector to be joined, as in one event's step; 64 steps, left and
+    // written through: FP64 8 of 162^2 5.90 and 6.13 ms, 6 of 243^2 12.75 and 13.50, 2 of
+    // 486^2 11.85 and 12.73, and on the persistent walk 14.14 and 15.93, FP32 there 6.98 and
+    // 7.23.  The FP32 step without the walk is at most 1 % longer written through,
+    // and shorter in small batches (20 of 81^2 2.70 and 2.66).
+#define GL_FIELD(K, TXv, TYv, WT)                                                                             \
+    hipLaunchKernelGGL((K<T, TXv, TYv, WT>), dim3(g), dim3(2 * TXv, TYv), 0, st, evs, tiles, total, at, ctl,  \
+                       (T)dtau)
 #define GL_SHAPE(TXv, TYv)                                                                                    \
     {                                                                                                         \
-        if (g == total)                                                                                       \
-            hipLaunchKernelGGL((k_batch_field_flat<T, TXv, TYv>), dim3(g), dim3(2 * TXv, TYv), 0, st, evs,    \
-                               tiles, total, at, ctl, (T)dtau);                                               \
-        else                                                                                                  \
-            hipLaunchKernelGGL((k_batch_field<T, TXv, TYv>), dim3(g), dim3(2 * TXv, TYv), 0, st, evs, tiles,  \
-                               total, at, ctl, (T)dtau);                                                      \
+        if (g == total) {                                                                                     \
+            if (sizeof(T) == 4 || whole_rows) GL_FIELD(k_batch_field_flat, TXv, TYv, true);                   \
+            else GL_FIELD(k_batch_field_flat, TXv, TYv, sizeof(T) == 4);                                      \
+        } else {                                                                                              \
+            if (whole_rows) GL_FIELD(k_batch_field, TXv, TYv, true);                                          \
+            else GL_FIELD(k_batch_field, TXv, TYv, false);                                                    \
+        }                                                                                                     \
     }
     switch (shape) {
         case 0: GL_SHAPE(32, 4) break;
@@ -293,6 +304,7 @@ hipError_t launch_batch_fields(hipStream_t st, int shape, const BatchEv<T> *evs,
         default: return hipErrorInvalidValue;
     }
 #undef GL_SHAPE
+#undef GL_FIELD
     return hipGetLastError();
 }
 
@@ -368,7 +380,7 @@ hipError_t launch_batch_check(hipStream_t st, const BatchEv<T> *evs, const int2 
     template hipError_t launch_batch_check<T>(hipStream_t, const BatchEv<T> *, const int2 *, int64_t, int,      \
                                               const BatchCtl *);                                             \
     template hipError_t launch_batch_fields<T>(hipStream_t, int, const BatchEv<T> *, const int2 *, int64_t,      \
-                                               const BatchAt &, const BatchCtl *, double, int);              \
+                                               const BatchAt &, const BatchCtl *, double, int, bool);        \
     template hipError_t launch_batch_push<T>(hipStream_t, const BatchEv<T> *, const int2 *, int64_t,            \
                                              const BatchAt &, int, const BatchCtl *, double, int, bool);     \
     template hipError_t launch_batch_pair<T>(hipStream_t, int, const BatchEv<T> *, const int2 *, int64_t,       \

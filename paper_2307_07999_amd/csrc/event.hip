@@ -1985,6 +1985,7 @@ struct gl_batch {
     int sort_every = 16;
     int graph_steps = 32;             // two sort periods
     bool any_particles = false;
+    bool whole_rows = true;           // every lattice's sites are a multiple of four a side
     // captured step loops, keyed by the state they start from, with the
     // state they leave (the parities and the pending sort)
     struct Graph {
@@ -2132,7 +2133,8 @@ gl_status batch_steps(gl_batch *b, int steps) {
                                          at(i - 1), b->ppar, ctl, b->dtau, b->sort_pending));
             if (gl_status s = pushed(i - 1)) return s;
         } else {
-            HIP_TRY(launch_batch_fields<T>(b->stream, b->shape, d, tiles, n_tiles, at(i), ctl, b->dtau, grid));
+            HIP_TRY(launch_batch_fields<T>(b->stream, b->shape, d, tiles, n_tiles, at(i), ctl, b->dtau, grid,
+                                           b->whole_rows));
         }
         if (!pair || i == steps - 1) {
             HIP_TRY(launch_batch_push<T>(b->stream, d, blocks, b->total_pblocks, at(i), b->ppar, ctl, b->dtau, grid,
@@ -2288,11 +2290,13 @@ gl_status time_fields(gl_batch *b, int shape, int mult, float *ms) {
     HIP_TRY(hipEventCreate(&e1));
     // the field phases read the state at parity fpar and only write the
     // next-step buffer and the site fields: repeating them changes nothing
-    HIP_TRY(launch_batch_fields<T>(b->stream, shape, d, tiles, b->total_tiles[shape], at, ctl, b->dtau, grid));
+    HIP_TRY(launch_batch_fields<T>(b->stream, shape, d, tiles, b->total_tiles[shape], at, ctl, b->dtau, grid,
+                                       b->whole_rows));
     HIP_TRY(hipEventRecord(e0, b->stream));
     const int reps = 3;
     for (int r = 0; r < reps; r++)
-        HIP_TRY(launch_batch_fields<T>(b->stream, shape, d, tiles, b->total_tiles[shape], at, ctl, b->dtau, grid));
+        HIP_TRY(launch_batch_fields<T>(b->stream, shape, d, tiles, b->total_tiles[shape], at, ctl, b->dtau, grid,
+                                       b->whole_rows));
     HIP_TRY(hipEventRecord(e1, b->stream));
     HIP_TRY(hipEventSynchronize(e1));
     HIP_TRY(hipEventElapsedTime(ms, e0, e1));
@@ -2384,6 +2388,7 @@ gl_status gl_batch_create(gl_event *const *evs, int32_t n_events, void *workspac
         b->cur0.push_back(ev->cur);
         b->pbuf0.push_back(ev->pbuf);
         b->any_particles |= ev->slots_used > 0;
+        b->whole_rows &= ev->N % 4 == 0;
         b->total_pblocks += ev->slots_used / kPushBlock;
     }
     b->paired = pairs(b);

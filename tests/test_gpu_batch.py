@@ -291,3 +291,30 @@ def test_the_check_sees_every_end_of_a_state(gl, N, prec):
     b.close()
     for ev in evs:
         ev.close()
+
+
+@pytest.mark.parametrize("prec", [64, 32])
+@pytest.mark.parametrize("shape,grid_mult", [(0, 0), (1, 0), (2, 0), (0, 1), (1, 1), (2, 1)])
+def test_lattices_whose_rows_share_sectors(gl, prec, shape, grid_mult):
+    """A lattice that is not a multiple of four a side puts the batch on the field
+    kernels whose stores stay in the L2 caches: bitwise the single events.  The
+    128^2 event gives the persistent walk more tiles than workgroups."""
+    def make():
+        evs = []
+        for k, (N, n) in enumerate([(27, 300), (54, 900), (128, 2000), (162, 700)]):
+            ev = gl.Event(N, 0.02 * N, precision=prec, max_steps=24, max_particles=n)
+            ev.init_glasma(2.0, 0.2, 1, 700 + k)
+            ev.add_species(1.27, 2.0, gl.KIND_HEAVY_QUARK, n, 800 + k, tau_form_fm=0.0)
+            evs.append(ev)
+        return evs
+    single, evs = make(), make()
+    b = gl.Batch(evs)
+    b.config(shape=shape, grid_mult=grid_mult, sort_every=8, graph_steps=16)
+    b.run(21)
+    for a, e in zip(single, evs):
+        a.set_sort_period(8)
+        a.run(21)
+        for x, y in zip(a.get_state()[:4], e.get_state()[:4]):
+            assert np.array_equal(x, y)
+        assert np.array_equal(a.series(), e.series())
+    b.close()
