@@ -121,3 +121,48 @@ def test_wilson_lines_of_every_transform(gl, N):
         V = orc.wilson_line(N, sigma, m2, 2, SEED, nuc)
         assert np.abs(ev.wilson_line(nuc) - V.T).max() < 1e-12
     ev.close()
+
+
+def test_many_sheets_match_oracle(gl):
+    """70 sheets of a 32^2 lattice, whose launches hold 32 of each nucleus: a
+    second and a shorter third chunk, both entry points."""
+    import torch
+    N, sheets = 32, 70
+    L, _, _ = _params(N, sheets)
+    rho = torch.from_numpy(np.ascontiguousarray(_oracle(N, sheets)[2])).to("cuda")
+    for label in ("MV draw", "caller charges"):
+        ev = gl.Event(N, L, 0.125, precision=64, max_steps=1)
+        if label == "MV draw":
+            ev.init_glasma(G2MU, M_IR, sheets, SEED)
+        else:
+            ev.init_glasma_from_charges(rho, M_IR)
+        _compare(gl, ev, N, sheets, label)
+        ev.close()
+
+
+@pytest.mark.parametrize("N,sheets", [(32, 70), (192, 35), (384, 16), (512, 17)])
+def test_chunks_of_sheets_multiply_in_order(gl, N, sheets):
+    """The Wilson lines of many sheets are the products, first sheet leftmost, of
+    those of single sheets.  Both nuclei in a launch (32^2, 192^2) and one (384^2,
+    512^2); every case crosses chunks and ends in a shorter one.  The lines' entries
+    are below one, and a product of k factors adds some 10 k eps."""
+    import torch
+    L, sigma, _ = _params(N, sheets)
+    ev = gl.Event(N, L, 0.125, precision=64, max_steps=1)
+    rho = np.stack([np.stack([ev.draw_charges(SEED, nuc, sh, sigma) for sh in range(sheets)]) for nuc in (0, 1)])
+    rho = torch.from_numpy(rho).to("cuda")
+    V = [np.broadcast_to(np.eye(3, dtype=complex), (N * N, 3, 3))] * 2
+    for sh in range(sheets):
+        ev.init_glasma_from_charges(rho[:, sh:sh + 1].contiguous(), M_IR)
+        for nuc in (0, 1):
+            w = ev.wilson_line(nuc).reshape(9, 2, N * N)
+            V[nuc] = V[nuc] @ (w[:, 0] + 1j * w[:, 1]).T.reshape(N * N, 3, 3)
+    for draw in (True, False):
+        if draw:
+            ev.init_glasma(G2MU, M_IR, sheets, SEED)
+        else:
+            ev.init_glasma_from_charges(rho, M_IR)
+        for nuc in (0, 1):
+            w = ev.wilson_line(nuc).reshape(9, 2, N * N)
+            assert np.abs((w[:, 0] + 1j * w[:, 1]).T.reshape(N * N, 3, 3) - V[nuc]).max() < 1e-12
+    ev.close()
