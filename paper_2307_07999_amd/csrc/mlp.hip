@@ -551,8 +551,8 @@ gl_status step_rows(gl_mlp *m, const float *X, const float *Y, const int32_t *id
     MHIP(hipGetLastError());
     int wgs = bias_groups(v) + 1;
     for (int l = 0; l <= v.depth; l++) wgs += weight_groups(v, l);
-    hipLaunchKernelGGL(k_update, dim3(wgs), dim3(64), 0, m->st, v, a, m->P, m->Mo, m->Vo, adam ? nullptr : m->G,
-                       m->loss, tiles, adam ? *adam : AdamArgs{});
+    hipLaunchKernelGGL(full ? k_update<true> : k_update<false>, dim3(wgs), dim3(64), 0, m->st, v, a, m->P, m->Mo, m->Vo,
+                       adam ? nullptr : m->G, m->loss, tiles, adam ? *adam : AdamArgs{});
     MHIP(hipGetLastError());
     return GL_OK;
 }

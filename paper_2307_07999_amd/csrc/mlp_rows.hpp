@@ -416,7 +416,8 @@ k_rows_train(NetView v, TrainView a) {
     const int t = threadIdx.x, lane = t & 63, wave = wave_of(t);
     const int tile = blockIdx.x, row = 16 * tile + (lane & 15);
     const bool valid = row < a.B;
-    const int hb = FULL ? kRowTiles : v.hb;
+    if (FULL) v.hb = kRowTiles;                          // known to the compiler
+    const int hb = v.hb;
     const int o0 = 32 * wave + 4 * (lane >> 4);          // first output of the lane's two blocks: o0, o0 + 16
     // the chain of products: layers 0 .. DEPTH forward, then DEPTH .. 1 back
     WaveWeights<> w[2];
@@ -560,9 +561,11 @@ __host__ __device__ inline int bias_groups(const NetView &v) { return v.depth * 
 // blocks one after another: its L2 then holds the layer's H once and its own share
 // of dZ, instead of all operands passing through every L2.
 constexpr int kUpdateAhead = 32;
+template <bool FULL>
 __global__ void __launch_bounds__(64)
 k_update(NetView v, TrainView a, float *__restrict__ P, float *__restrict__ Mo, float *__restrict__ Vo,
          float *__restrict__ G, float *__restrict__ loss, int tiles, AdamArgs aa) {
+    if (FULL) v.hb = kRowTiles;
     const int lane = threadIdx.x;
     int l = 0, q = 0, n_groups = 0;
     for (int k = 0; k <= v.depth; k++) n_groups += weight_groups(v, k);
