@@ -113,7 +113,10 @@ typedef struct {
     int32_t nonfinite;       /* 1 if any NaN/Inf in the fields          */
 } gl_diag;
 
-/* Workspace size for an event.  Pure function. */
+/* Workspace size for an event.  Pure function.  Small lattices take room for
+ * up to 64 sheets of the initial condition and, with particles, a third field
+ * state and a second set of site fields: 26, 99 and 256 MB at 64^2, 128^2 and
+ * 256^2 in FP32 with 10^4 particles. */
 gl_status gl_required_bytes(const gl_lattice_desc *desc, size_t *bytes);
 
 /* Largest max_particles an event of this precision (64 or 32) accepts: the
@@ -219,14 +222,15 @@ gl_status gl_set_check_period(gl_event *ev, int32_t every);
  * graph.  Blocks alternate between two executable graphs: the one due waits
  * on the host for its previous launch (two blocks back) to finish, then is
  * updated in place when the launches match or instantiated anew when they do
- * not (a block whose sort or series flush falls elsewhere).  Steps left over (fewer than
- * G) are launched directly, and so is every step while kernel timing
- * (gl_profile_enable) or the finite checks are on.  The launches and their
- * results are those of direct stepping, bit for bit.  Needs an event created
- * on a stream other than the null stream (GL_EINVAL otherwise).  0 (default)
- * launches every step directly and frees the graphs (after the stream is done
- * with them).  A recording or launch
- * error returns GL_EDEVICE and leaves the event uninitialised. */
+ * not (a block whose sort or series flush falls elsewhere).  Steps left over
+ * (fewer than G) are launched directly, and so is every step while kernel
+ * timing (gl_profile_enable) or the finite checks are on.  On small lattices a
+ * plain gl_run launches each field step together with the push before it;
+ * replay, timing and checks launch them apart.  The results are those of direct
+ * stepping, bit for bit.  Needs an event created on a stream other than the
+ * null stream (GL_EINVAL otherwise).  0 (default) launches every step directly
+ * and frees the graphs (after the stream is done with them).  A recording or
+ * launch error returns GL_EDEVICE and leaves the event uninitialised. */
 gl_status gl_set_graph_steps(gl_event *ev, int32_t steps);
 /* Graphs launched by gl_run since the event was created, and how many of them
  * had to be instantiated (the rest updated one of the two in place). */

@@ -40,8 +40,9 @@ __device__ __forceinline__ void batch_field_tile(LinkTile<T, TX, TY> &tile, cons
     // every thread takes part (the step synchronises the workgroup)
     const bool active = x0 + lx < e.N && y0 + ly < e.N;
     const int reunit = e.reunit_every > 0 && (n % e.reunit_every) == e.reunit_every - 1;
-    // a batch's working set overflows the last-level cache in either
-    // precision: its streamed arrays take the non-temporal hint
+    // a large batch's working set overflows the last-level cache in either
+    // precision: its streamed arrays take the non-temporal hint (a paired batch's
+    // does not, and takes the hint all the same)
     field_step_link<T, TX, TY, true, WT>(tile, e.N, e.f[at.in], e.f[at.out], e.n_species > 0 ? e.F[at.F] : nullptr, x0,
                                          y0, lx, ly, tid & 1, tid, active, tau, dtau, tau_h, reunit);
 }

@@ -2238,7 +2238,8 @@ std::string batch_key(const gl_batch *b) {
     return k.str();
 }
 
-// the largest grid multiple the tuner tries (workgroups per CU of a persistent launch)
+// the largest grid multiple of a cache entry that is honoured (workgroups per CU
+// of a persistent launch; the tuner itself writes 0)
 constexpr int kMaxGridMult = 8;
 
 bool cache_lookup(const char *path, const std::string &key, int *shape, int *mult) {

@@ -155,7 +155,7 @@ inline hipError_t timer_skip(hipStream_t st, const KernelTimer &kt) {
     return e != hipSuccess ? e : hipEventRecord(kt.stop, st);
 }
 
-// F: site-field records at tau_n in chunked planes, written when non-null
+// F: site-field records at tau_n (site_chunk), written when non-null
 template <typename T>
 hipError_t launch_field_step(hipStream_t st, int N, FieldPtrs<T> in, FieldPtrs<T> out, T *F,
                              double tau, double dtau, int reunit, const KernelTimer &kt);

@@ -1,8 +1,7 @@
 // mlp_rows.hpp -- the surrogate network as whole-network kernels: a workgroup
 // takes a few tiles of 16 rows through every layer, so that one launch is an
 // inference (k_rows_infer) or the forward and backward pass of a training
-// step (k_rows_train), which leaves the weight gradients' operands for
-// k_weight_grads and k_update.
+// step (k_rows_train), which leaves the gradients' operands for k_update.
 //
 // Layout.  All products run as W x^T: the MFMA's A operand is a 16 x 16 block
 // of weights (row o), its B operand 16 rows of activations (column b).  The
@@ -13,7 +12,8 @@
 // a lane, two steps over k), so that a wave's load is one contiguous KiB.
 //
 // Each of the 8 waves owns two blocks of 16 outputs (a hidden layer is padded
-// to 256 outputs), holds their weights of the whole layer in registers (64
+// to 256 outputs; narrow networks infer in groups of fewer waves, see
+// k_rows_infer), holds their weights of the whole layer in registers (64
 // VGPRs, loaded while the previous layer finishes) and reads every row's
 // activations from LDS.
 //
@@ -180,9 +180,11 @@ __device__ __forceinline__ void stage_biases(const NetView &v, float *bias) {
 __device__ __forceinline__ float silu(float v) { return v / (1.f + __expf(-v)); }
 
 // silu of four values.  For |v| <= 80 numerator and denominator (1 to 2^116)
-// need no scaling, and the division is the compiler's own sequence without its
-// three scaling instructions, rounded the same (a fifth of the vector time of
-// an activation); a wave with a larger value takes the division itself.
+// need no scaling, and the division is one Newton-Raphson step on the hardware's
+// reciprocal and two residual corrections of the quotient, which is what a
+// division does between its three scaling instructions, and rounds the same
+// while the quotient is a normal number (a fifth of the vector time of an
+// activation); a wave with a larger value takes the division itself.
 __device__ __forceinline__ floatx4 silu4(floatx4 v) {
     floatx4 h;
     const float big = fmaxf(fmaxf(fabsf(v[0]), fabsf(v[1])), fmaxf(fabsf(v[2]), fabsf(v[3])));
@@ -550,8 +552,8 @@ __host__ __device__ inline int bias_groups(const NetView &v) { return v.depth * 
 // dZ[o]; the loss.  Then Adam and the new weights in both fragment orders (G
 // null), or the gradients to G.
 //
-// Bound: by the way of the operands (dZ and H of all layers, 15 MB at 4096 rows,
-// and 16 MB of FP32 dZ for the biases) from the other XCDs' L2 and by their
+// Bound: by the way of the operands (dZ and H of all layers, 12.8 MB at 4096
+// rows, and 12.8 MB of FP32 dZ for the biases) from the other XCDs' L2 and by their
 // latency; the MFMA chain itself is under 2 us.  So every block is a workgroup of
 // one wave, which spreads the loads over all compute units, with kUpdateAhead row
 // tiles in flight, and the biases' shares are fetched 16 at a time: a step of 4096

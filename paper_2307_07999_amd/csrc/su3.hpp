@@ -304,6 +304,12 @@ __device__ __forceinline__ M3<T> herm_square(const M3<T> &Q) {
     return r;
 }
 
+// Sine and cosine of one argument from one reduction, which sin() and cos()
+// apart would each do: a third of the instructions of the exponential's closed
+// form (50 MV sheets at 512^2 almost all take that form).
+__device__ __forceinline__ void sin_cos(double x, double &s, double &c) { sincos(x, &s, &c); }
+__device__ __forceinline__ void sin_cos(float x, float &s, float &c) { sincosf(x, &s, &c); }
+
 // ---- exponential of i Q for hermitian traceless Q ---------------------------
 // Cayley-Hamilton form exp(iQ) = f0 + f1 Q + f2 Q^2.  For c1 = Tr(Q^2)/2 up
 // to 0.12 (spectral norm |Q| <= sqrt(4 c1 / 3) <= 0.4) the f_j are the power
@@ -312,12 +318,6 @@ __device__ __forceinline__ M3<T> herm_square(const M3<T> &Q) {
 // after K terms its error is below |Q|^(K+1) e^|Q| / (K+1)!: 8e-19 for
 // K = 14 (double), 1e-9 for K = 8 (float).  Larger Q take the closed form of
 // C. Morningstar and M. Peardon, Phys. Rev. D 69 (2004) 054501, Sec. III.
-// Sine and cosine of one argument from one reduction: a function apart from
-// the other half of sin() and cos() would reduce it again, a third of the
-// closed form's instructions (50 MV sheets at 512^2 almost all take that form).
-__device__ __forceinline__ void sin_cos(double x, double &s, double &c) { sincos(x, &s, &c); }
-__device__ __forceinline__ void sin_cos(float x, float &s, float &c) { sincosf(x, &s, &c); }
-
 template <typename T>
 __device__ __forceinline__ M3<T> expi_herm(const M3<T> &Q) {
     M3<T> Q2 = herm_square(Q);
