@@ -38,9 +38,9 @@ constexpr int SX = 32, SY = 4;     // site tiles of the step: 2 lanes per site
 // FP64: two waves per SIMD at the cost of a few spilled registers is faster
 // than one wave with everything in registers.
 template <typename T, bool WT>
-__global__ void __launch_bounds__(2 * SX * SY) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 ? 2 : 4, 8)))
-k_field_step(int N, FieldPtrs<T> in, FieldPtrs<T> out, T *__restrict__ F, T tau, T dtau, T tau_h, int reunit) {
-    __shared__ LinkTile<T, SX, SY> tile;
+__device__ __forceinline__ void field_step_tile(LinkTile<T, SX, SY> &tile, int N, FieldPtrs<T> in,
+                                                FieldPtrs<T> out, T *F, T tau, T dtau, T tau_h,
+                                                int reunit) {
     const int tx = (N + SX - 1) / SX;
     const int l = (int)xcd_remap(blockIdx.x, gridDim.x);
     const int x0 = (l % tx) * SX, y0 = (l / tx) * SY;
@@ -53,6 +53,19 @@ k_field_step(int N, FieldPtrs<T> in, FieldPtrs<T> out, T *__restrict__ F, T tau,
     const bool active = x0 + lx < N && y0 + ly < N;
     field_step_link<T, SX, SY, kStreamed<T>, WT>(tile, N, in, out, F, x0, y0, lx, ly, threadIdx.x & 1, tid, active, tau,
                                                  dtau, tau_h, reunit);
+}
+template <typename T>
+__global__ void __launch_bounds__(2 * SX * SY) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 ? 2 : 4, 8)))
+k_field_step(int N, FieldPtrs<T> in, FieldPtrs<T> out, T *__restrict__ F, T tau, T dtau, T tau_h, int reunit) {
+    __shared__ LinkTile<T, SX, SY> tile;
+    field_step_tile<T, true>(tile, N, in, out, F, tau, dtau, tau_h, reunit);
+}
+// the step whose stores stay in the L2 caches (written_through)
+template <typename T>
+__global__ void __launch_bounds__(2 * SX * SY) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 ? 2 : 4, 8)))
+k_field_step_cached(int N, FieldPtrs<T> in, FieldPtrs<T> out, T *__restrict__ F, T tau, T dtau, T tau_h, int reunit) {
+    __shared__ LinkTile<T, SX, SY> tile;
+    field_step_tile<T, false>(tile, N, in, out, F, tau, dtau, tau_h, reunit);
 }
 
 // The two field correlators at tau_n, FP64, from one read of the site fields
@@ -338,8 +351,8 @@ hipError_t launch_field_step(hipStream_t st, int N, FieldPtrs<T> in, FieldPtrs<T
                              double dtau, int reunit, const KernelTimer &kt) {
     const dim3 grid(field_tiles(N)), block(2 * SX, SY);
     const T th = (T)(tau + 0.5 * dtau);
-    if (written_through<T>(N)) GL_LAUNCH_TIMED(kt, (k_field_step<T, true>), grid, block, 0, st, N, in, out, F, (T)tau, (T)dtau, th, reunit);
-    else GL_LAUNCH_TIMED(kt, (k_field_step<T, false>), grid, block, 0, st, N, in, out, F, (T)tau, (T)dtau, th, reunit);
+    if (written_through<T>(N)) GL_LAUNCH_TIMED(kt, k_field_step<T>, grid, block, 0, st, N, in, out, F, (T)tau, (T)dtau, th, reunit);
+    else GL_LAUNCH_TIMED(kt, k_field_step_cached<T>, grid, block, 0, st, N, in, out, F, (T)tau, (T)dtau, th, reunit);
     return hipGetLastError();
 }
 
