@@ -263,7 +263,7 @@ def test_batch_equals_single_events_at_batched_workload_sizes(gl):
 @pytest.mark.parametrize("prec", [64, 32])
 @pytest.mark.parametrize("N", [2, 5, 32, 38])
 def test_the_check_sees_every_end_of_a_state(gl, N, prec):
-    """One NaN or Inf in the first or last values of each array of a state (48 N^2
+    """One NaN or Inf in the first or last values of each array of a state (56 N^2
     values in chunks of 65536, read as 16-byte vectors several at a time), in one
     event of two."""
     n2 = N * N

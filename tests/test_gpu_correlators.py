@@ -19,8 +19,8 @@ def gl():
 @pytest.mark.parametrize("prec", [64, 32])
 @pytest.mark.parametrize("static,light", [(True, False), (False, True), (True, True)])
 def test_streamed_correlators_of_a_tiled_lattice(gl, prec, static, light):
-    """A 576^2 lattice (270 MB and more of arrays in FP32) tiled from one of 144^2 (a
-    tenth of the cache): every site does what its image does, so the means agree to
+    """A 576^2 lattice (300 MB and more of arrays) tiled from one of 144^2 (a sixteenth of
+    that): every site does what its image does, so the means agree to
     the rounding of sums of 3 10^5 FP64 terms in another order."""
     N, copies, steps = 144, 4, 20
     ev = [gl.Event(n, 0.02 * n, precision=prec, max_steps=steps, static_correlator=static, lightlike_correlator=light)
