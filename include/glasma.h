@@ -115,7 +115,7 @@ typedef struct {
 
 /* Workspace size for an event.  Pure function.  Small lattices take room for
  * up to 64 sheets of the initial condition and, with particles, a third field
- * state and a second set of site fields: 26, 99 and 256 MB at 64^2, 128^2 and
+ * state and a second set of site fields: 27, 99 and 256 MB at 64^2, 128^2 and
  * 256^2 in FP32 with 10^4 particles. */
 gl_status gl_required_bytes(const gl_lattice_desc *desc, size_t *bytes);
 
